@@ -20,7 +20,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmdwf.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
-SOURCES = ["dslash.hip", "blas.hip", "layout.hip", "core.cpp", "ops.cpp", "solver.cpp"]
+SOURCES = ["dslash.hip", "dslash_quad.hip", "blas.hip", "layout.hip", "core.cpp", "ops.cpp", "solver.cpp"]
 
 # gfx950 only; packed-FP32 instructions are disabled (plain float code is
 # never turned into packed FP32 arithmetic).

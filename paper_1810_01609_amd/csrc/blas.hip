@@ -3,8 +3,7 @@
 // The paper ("Performance Measurement Method", Linear Solver Performance)
 // counts 50-100 flops per site for these operations, i.e. they are purely
 // bandwidth bound, and does every reduction in double precision.  Here each
-// thread owns one 4D site and walks its L5 slices (coalesced [s][group][cb]
-// accesses across the wavefront), the updates are fused so each vector is
+// thread owns one site of one slice, the updates are fused so each vector is
 // read and written once, and every reduction accumulates in FP64 with a
 // fixed summation tree (DPP moves within each 16-lane row, shuffles across
 // the four rows of a wavefront, then LDS across wavefronts, then one
@@ -30,60 +29,80 @@ __device__ __forceinline__ double block_sum_256(double v) {
   return t;
 }
 
-// p = r + beta p on every slice of a 4D site, and pt = M_phi p from the
-// new p: (M_phi p)_s = b5 p_s + c5 (P5 p)_s, P5 taking spins 0,1 from slice
-// s - 1 and spins 2,3 from slice s + 1, the wall hop carrying -mq.  pt is the
-// input of the first stencil launch of the next iteration, which then needs
-// no fifth-dimension prologue on its eight neighbours.
+// Threads are laid over the stored units (16 places each) of one half-field:
+// consecutive threads touch consecutive memory whatever the layout, and a
+// field gives 16 x units threads rather than one per 4D site, which keeps
+// small lattices from walking L5 dependent loads.
+__device__ __forceinline__ int blas_units(const Geom& g) { return ((g.Vh + 15) >> 4) * g.L5; }
+// whether a place holds a site (the last tile of a ragged lattice is padded)
+__device__ __forceinline__ bool holds_site(const Geom& g, int unit, int at) {
+  const int u = unit - ((g.Vh - 1) >> 4) * g.L5;
+  if (u < 0) return true;
+  int in, s;
+  place_site(u, at, g.L5, in, s);
+  return ((g.Vh - 1) & ~15) + in < g.Vh;
+}
+
+// p = r + beta p, and pt = M_phi p from the new p: (M_phi p)_s = b5 p_s +
+// c5 (P5 p)_s, P5 taking spins 0,1 from slice s - 1 and spins 2,3 from slice
+// s + 1, the wall hop carrying -mq.  pt is the input of the first stencil
+// launch of the next iteration, which then needs no fifth-dimension prologue
+// on its eight neighbours.  One thread per site and slice, a workgroup holds
+// whole columns, and the neighbouring slices' halves pass through LDS (both
+// halves at once in FP32; FP64 takes them one after the other).
 template <int PS>
-__global__ __launch_bounds__(kBlasThreads) void k_cg_p(BlasArgs A) {
+__global__ __launch_bounds__(512) void k_cg_p(BlasArgs A, int tiles) {
   using RS = typename PrecTraits<PS>::Real;
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr bool kBoth = sizeof(RS) == 4;
+  constexpr int kRow = kBoth ? 24 : 12;
   const int slot = blockIdx.y;
   const CGState& S = A.st[slot];
   if (!S.active) return;
-  const int cb = blockIdx.x * kBlasThreads + threadIdx.x;
-  if (cb >= A.g.Vh) return;
-  const FieldDesc f{A.g.Vh, A.g.L5};
   const int L5 = A.g.L5;
+  const int ul = threadIdx.x >> 4, at = threadIdx.x & 15;  // unit of the workgroup, place
+  const int tl = ul / L5, u = ul - tl * L5;
+  const int tile = blockIdx.x * tiles + tl;
+  int in, s;
+  place_site(u, at, L5, in, s);
+  const bool valid = tile * 16 + in < A.g.Vh;
+  const FieldDesc f{A.g.Vh, L5};
+  const Place pl{(size_t)tile * L5 + u, at};
   const RS beta = (RS)S.beta;
-  const Coef5 c = A.coef[slot];
+  const Coef5& c = A.coef[slot];
   const RS b5 = (RS)c.b5, c5 = (RS)c.c5, wall = (RS)(-c.c5 * c.mq);
-  char* p = A.a[slot];
-  const char* r = A.b[slot];
-  char* pt = A.c[slot];
-  RS cur[24], rv[24];
-  // spins 0,1 of the new p on slice L5 - 1 feed slice 0 across the wall
-  SpinorIO<PS>::load(p, f, cb, L5 - 1, cur);
-  SpinorIO<PS>::load(r, f, cb, L5 - 1, rv);
-  RS up[12];  // c5 (P5 p)_s, spins 0,1
-#pragma unroll
-  for (int k = 0; k < 12; ++k) up[k] = wall * (rv[k] + beta * cur[k]);
-  RS first_dn[12], pend[24];
-  for (int s = 0; s < L5; ++s) {
-    SpinorIO<PS>::load(p, f, cb, s, cur);
-    SpinorIO<PS>::load(r, f, cb, s, rv);
+  RS cur[24], out[24];
+  if (valid) {
+    RS rv[24];
+    SpinorAt<PS>::load(A.a[slot], f, pl, cur);
+    SpinorAt<PS>::load(A.b[slot], f, pl, rv);
 #pragma unroll
     for (int k = 0; k < 24; ++k) cur[k] = rv[k] + beta * cur[k];
-    SpinorIO<PS>::store(p, f, cb, s, cur, A.nt_store);
-    if (s == 0) {
+    SpinorAt<PS>::store(A.a[slot], f, pl, cur, A.nt_store);
+  } else {
 #pragma unroll
-      for (int k = 0; k < 12; ++k) first_dn[k] = cur[12 + k];
-    } else {
-      // finish pt_{s-1}: spins 2,3 take c5 p_s
+    for (int k = 0; k < 24; ++k) cur[k] = 0;
+  }
+  constexpr int kSlice = 16 * kRow + 4;  // the 4 spread a quad's rows over the banks
+  RS* lds = reinterpret_cast<RS*>(smem) + (size_t)tl * L5 * kSlice;
+  const int up = s == 0 ? L5 - 1 : s - 1, dn = s == L5 - 1 ? 0 : s + 1;
+  const RS cu = s == 0 ? wall : c5, cd = s == L5 - 1 ? wall : c5;
+  RS* mine = lds + s * kSlice + in * kRow;
+  const RS *ru = lds + up * kSlice + in * kRow, *rd = lds + dn * kSlice + in * kRow + (kBoth ? 12 : 0);
 #pragma unroll
-      for (int k = 0; k < 12; ++k) pend[12 + k] += c5 * cur[12 + k];
-      SpinorIO<PS>::store(pt, f, cb, s - 1, pend, A.nt_store);
-    }
+  for (int k = 0; k < kRow; ++k) mine[k] = cur[k];
+  __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      pend[k] = b5 * cur[k] + up[k];
-      pend[12 + k] = b5 * cur[12 + k];
-      up[k] = c5 * cur[k];
-    }
+  for (int k = 0; k < 12; ++k) out[k] = b5 * cur[k] + cu * ru[k];
+  if constexpr (!kBoth) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 12; ++k) mine[k] = cur[12 + k];
+    __syncthreads();
   }
 #pragma unroll
-  for (int k = 0; k < 12; ++k) pend[12 + k] += wall * first_dn[k];
-  SpinorIO<PS>::store(pt, f, cb, L5 - 1, pend, A.nt_store);
+  for (int k = 0; k < 12; ++k) out[12 + k] = b5 * cur[12 + k] + cd * rd[k];
+  if (valid) SpinorAt<PS>::store(A.c[slot], f, pl, out, A.nt_store);
 }
 
 template <int PI, int PO>
@@ -93,29 +112,29 @@ __global__ __launch_bounds__(kBlasThreads) void k_axpby(BlasArgs A) {
   using RC = typename PrecTraits<(PI == F64 || PO == F64) ? F64 : F32>::Real;
   const int slot = blockIdx.y;
   if (A.st != nullptr && !A.st[slot].active) return;
-  const int cb = blockIdx.x * kBlasThreads + threadIdx.x;
+  const int idx = blockIdx.x * kBlasThreads + threadIdx.x;
+  const int unit = idx >> 4, at = idx & 15;
   const FieldDesc f{A.g.Vh, A.g.L5};
   double loc = 0;
-  if (cb < A.g.Vh) {
+  if (unit < blas_units(A.g) && holds_site(A.g, unit, at)) {
+    const Place pl{(size_t)unit, at};
     const char* in = A.a[slot];
     char* out = A.b[slot];
     const RC ca = (RC)A.ca, cbeta = (RC)A.cb;
-    for (int s = 0; s < A.g.L5; ++s) {
-      RI iv[24];
-      RO ov[24];
-      SpinorIO<PI>::load(in, f, cb, s, iv);
-      if (A.cb != 0.0) {
-        SpinorIO<PO>::load(out, f, cb, s, ov);
+    RI iv[24];
+    RO ov[24];
+    SpinorAt<PI>::load(in, f, pl, iv);
+    if (A.cb != 0.0) {
+      SpinorAt<PO>::load(out, f, pl, ov);
 #pragma unroll
-        for (int k = 0; k < 24; ++k) ov[k] = (RO)(ca * (RC)iv[k] + cbeta * (RC)ov[k]);
-      } else {
+      for (int k = 0; k < 24; ++k) ov[k] = (RO)(ca * (RC)iv[k] + cbeta * (RC)ov[k]);
+    } else {
 #pragma unroll
-        for (int k = 0; k < 24; ++k) ov[k] = (RO)(ca * (RC)iv[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < 24; ++k) loc += (double)ov[k] * (double)ov[k];
-      SpinorIO<PO>::store(out, f, cb, s, ov);
+      for (int k = 0; k < 24; ++k) ov[k] = (RO)(ca * (RC)iv[k]);
     }
+#pragma unroll
+    for (int k = 0; k < 24; ++k) loc += (double)ov[k] * (double)ov[k];
+    SpinorAt<PO>::store(out, f, pl, ov);
   }
   if (A.partials != nullptr) {
     const double t = block_sum_256(loc);
@@ -127,29 +146,29 @@ template <int P>
 __global__ __launch_bounds__(kBlasThreads) void k_norm_diff(BlasArgs A) {
   using R = typename PrecTraits<P>::Real;
   const int slot = blockIdx.y;
-  const int cb = blockIdx.x * kBlasThreads + threadIdx.x;
+  const int idx = blockIdx.x * kBlasThreads + threadIdx.x;
+  const int unit = idx >> 4, at = idx & 15;
   const FieldDesc f{A.g.Vh, A.g.L5};
   double loc = 0;
-  if (cb < A.g.Vh) {
-    const char* a = A.a[slot];
-    const char* b = A.b != nullptr ? A.b[slot] : nullptr;
-    for (int s = 0; s < A.g.L5; ++s) {
-      R av[24], bv[24];
-      SpinorIO<P>::load(a, f, cb, s, av);
-      if (b != nullptr) {
-        SpinorIO<P>::load(b, f, cb, s, bv);
+  if (unit < blas_units(A.g) && holds_site(A.g, unit, at)) {
+    const Place pl{(size_t)unit, at};
+    R av[24], bv[24];
+    SpinorAt<P>::load(A.a[slot], f, pl, av);
+    if (A.b != nullptr) {
+      SpinorAt<P>::load(A.b[slot], f, pl, bv);
 #pragma unroll
-        for (int k = 0; k < 24; ++k) av[k] -= bv[k];
-      }
-#pragma unroll
-      for (int k = 0; k < 24; ++k) loc += (double)av[k] * (double)av[k];
+      for (int k = 0; k < 24; ++k) av[k] -= bv[k];
     }
+#pragma unroll
+    for (int k = 0; k < 24; ++k) loc += (double)av[k] * (double)av[k];
   }
   const double t = block_sum_256(loc);
   if (threadIdx.x == 0) A.partials[(size_t)slot * A.nblk + blockIdx.x] = t;
 }
 
-int blas_nblk(const Geom& g) { return (g.Vh + kBlasThreads - 1) / kBlasThreads; }
+int blas_nblk(const Geom& g) {
+  return (int)(((size_t)((g.Vh + 15) / 16) * g.L5 * 16 + kBlasThreads - 1) / kBlasThreads);
+}
 
 static dim3 blas_grid(BlasArgs& A) {
   A.nblk = blas_nblk(A.g);
@@ -157,18 +176,25 @@ static dim3 blas_grid(BlasArgs& A) {
 }
 
 
-hipError_t blas_cg_p(BlasArgs A, int ps, hipStream_t st) {
-  const dim3 grid = blas_grid(A);
-  const dim3 blk(kBlasThreads);
-  switch (ps) {
-    case F64: launch_k(k_cg_p<F64>, grid, blk, 0, st, A); break;
-    case F32: launch_k(k_cg_p<F32>, grid, blk, 0, st, A); break;
-    case F16: launch_k(k_cg_p<F16>, grid, blk, 0, st, A); break;
-    case BF16: launch_k(k_cg_p<BF16>, grid, blk, 0, st, A); break;
-    case I16: launch_k(k_cg_p<I16>, grid, blk, 0, st, A); break;
-    default: return hipErrorInvalidValue;
-  }
+template <int PS> static hipError_t cg_p_launch(const BlasArgs& A, hipStream_t st) {
+  using RS = typename PrecTraits<PS>::Real;
+  const int column = 16 * A.g.L5;  // threads of one 16-site tile
+  const int tiles = column >= 256 ? 1 : 256 / column;
+  const int ntile = (A.g.Vh + 15) / 16;
+  const size_t lds = (size_t)tiles * A.g.L5 * (16 * (sizeof(RS) == 4 ? 24 : 12) + 4) * sizeof(RS);
+  launch_k(k_cg_p<PS>, dim3((ntile + tiles - 1) / tiles, A.nslots), dim3(tiles * column), lds, st, A, tiles);
   return hipGetLastError();
+}
+
+hipError_t blas_cg_p(BlasArgs A, int ps, hipStream_t st) {
+  switch (ps) {
+    case F64: return cg_p_launch<F64>(A, st);
+    case F32: return cg_p_launch<F32>(A, st);
+    case F16: return cg_p_launch<F16>(A, st);
+    case BF16: return cg_p_launch<BF16>(A, st);
+    case I16: return cg_p_launch<I16>(A, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int PI>

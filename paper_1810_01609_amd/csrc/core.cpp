@@ -388,7 +388,8 @@ static int default_stage() {
 // candidate gives the same result.
 constexpr int kTravBtShift = 12, kTravYbShift = 16, kRhsOrderShift = 24;
 
-static void candidates(const Geom& g, int prec, DslashArgs A, bool hop, std::vector<int>& out, int& dflt) {
+static void candidates(const Geom& g, int prec, DslashArgs A, bool hop, bool dag, bool pro, std::vector<int>& out,
+                       int& dflt) {
   out.clear();
   dflt = -1;
   const int stage = hop ? default_stage() : 0;
@@ -411,7 +412,7 @@ static void candidates(const Geom& g, int prec, DslashArgs A, bool hop, std::vec
     const int CB = 1 << lg;
     if (CB * g.L5 > dslash_max_threads(prec)) break;
     if (CB > 2 * g.Vh && lg > 4) break;
-    const size_t lds = dslash_lds_bytes(A, prec, lg, hop);
+    const size_t lds = dslash_lds_bytes(A, prec, lg, hop, dag, pro);
     if (lds > 160 * 1024) break;
     for (int t : trav) out.push_back(lg | (stage << 8) | t);
   }
@@ -490,7 +491,7 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   }
   std::vector<int> cand;
   int dflt = 4;
-  candidates(geom, prec, A, pr.hop, cand, dflt);
+  candidates(geom, prec, A, pr.hop, pr.dag, pr.pro, cand, dflt);
   if (cand.empty()) return hipErrorInvalidValue;
   int lg = dflt;
   const std::string key = tune_key(geom, prec, pr, nslots, fuse != nullptr ? fuse->mode : 0);

@@ -3,11 +3,12 @@
 // arithmetic.  gfx950 only.
 //
 // Internal layouts (one parity, "half-field"; cb = lexicographic 4D index
-// of the site divided by 2, which enumerates one parity when Lx is even):
-//   spinor F64 : double2 [s][12 groups][cb]      group g = complex comp g
-//   spinor F32 : float4  [s][6 groups][cb]       group g = comps 2g, 2g+1
-//   spinor F16/BF16/I16 : 16-byte groups of 8 16-bit values [s][3][cb]
-//              (comps 4g..4g+3), then (256-byte aligned) float scale [s][cb]:
+// of the site divided by 2, which enumerates one parity when Lx is even),
+// groups of 16 bytes per site and slice, tiled as described at kSiteTile:
+//   spinor F64 : 12 x double2                    group g = complex comp g
+//   spinor F32 : 6 x float4                      group g = comps 2g, 2g+1
+//   spinor F16/BF16/I16 : 3 groups of 8 16-bit values (comps 4g..4g+3), then
+//              (256-byte aligned) one float scale per site and slice:
 //              value = half*scale, or int16/32767*scale (fixed point)
 //   gauge  : 12 reals (rows 0,1) per link, [parity][mu][group][cb]
 //            F64 6 x double2, F32 3 x float4, F16/BF16/I16 3 x 4 x 16 bits (8 bytes);
@@ -32,28 +33,45 @@ template <> struct PrecTraits<I16> { using Real = float; };
 
 __host__ __device__ __forceinline__ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Spinor fields are stored in tiles of kSiteTile consecutive sites: a tile
-// holds all L5 slices and all 16-byte groups of its sites, site fastest
-// ([tile][s][group][site in tile]).  With 16-site tiles (the stencil's
-// workgroup width) the loads of one wavefront (16 sites x 4 slices) cover one
-// contiguous block of memory, and a workgroup's whole 5D column is one
-// contiguous block, instead of one short run per (slice, group) stream.
-#ifndef MDWF_SITE_TILE
-#define MDWF_SITE_TILE 16
-#endif
-constexpr int kSiteTile = MDWF_SITE_TILE;  // a power of two
+// Spinor fields are stored in tiles of 16 consecutive sites: a tile holds all
+// L5 slices and all 16-byte groups of its sites as units of 16 places,
+// [tile][unit][group][place], so a unit's group is 256 contiguous bytes and
+// the group stride is the same everywhere.  With L5 a multiple of 4 a unit is
+// 4 sites x 4 slices (slice fastest): the quad of lanes that shares a site in
+// the stencil reads 64 contiguous bytes and 16 lanes read 256.  Otherwise a
+// unit is one slice of the 16 sites.
+constexpr int kSiteTile = 16;
 __host__ __device__ __forceinline__ size_t padded_vh(int Vh) { return round_up((size_t)Vh, kSiteTile); }
-// index, in 16-byte units, of group g of slice s of site cb (G groups per site).
-// 64-bit arithmetic: the constant group offsets fold into the loads'
-// immediate offsets (32-bit unsigned arithmetic, which may wrap, blocks that
-// and cost the 16-bit stencils 5-11 %).
-__host__ __device__ __forceinline__ size_t tile_index(int cb, int s, int g, int L5, int G) {
-  return ((size_t)(cb / kSiteTile) * L5 + s) * (size_t)(G * kSiteTile) + (size_t)g * kSiteTile + (cb % kSiteTile);
+__host__ __device__ __forceinline__ bool quad_layout(int L5) { return (L5 & 3) == 0; }
+// Unit (over the whole field) and place of slice s of site cb.  64-bit
+// arithmetic: the constant group offsets fold into the loads' immediate
+// offsets (32-bit unsigned arithmetic, which may wrap, blocks that and cost
+// the 16-bit stencils 5-11 %).
+struct Place {
+  size_t unit;
+  int at;
+};
+__host__ __device__ __forceinline__ Place place_of(int cb, int s, int L5) {
+  const int in = cb % kSiteTile;
+  const bool q = quad_layout(L5);
+  const int u = q ? (s & ~3) | (in >> 2) : s;
+  return {(size_t)(cb / kSiteTile) * L5 + u, q ? ((in & 3) << 2) | (s & 3) : in};
 }
-// index of the per-site scale of (cb, s) in the 16-bit scale array
-__host__ __device__ __forceinline__ size_t tile_scale_index(int cb, int s, int L5) {
-  return ((size_t)(cb / kSiteTile) * L5 + s) * kSiteTile + (cb % kSiteTile);
+// slice and site in the tile of place `at` of a tile's unit u
+__host__ __device__ __forceinline__ void place_site(int u, int at, int L5, int& in, int& s) {
+  if (quad_layout(L5)) {
+    in = ((u & 3) << 2) | (at >> 2);
+    s = (u & ~3) | (at & 3);
+  } else {
+    in = at;
+    s = u;
+  }
 }
+// index, in 16-byte groups, of group g (of G) of a place
+__host__ __device__ __forceinline__ size_t group_index(const Place& p, int g, int G) {
+  return p.unit * (size_t)(G * kSiteTile) + (size_t)g * kSiteTile + p.at;
+}
+__host__ __device__ __forceinline__ size_t scale_index(const Place& p) { return p.unit * kSiteTile + p.at; }
 
 // Byte offset of the per-site scale array inside a 16-bit spinor field.
 __host__ __device__ __forceinline__ size_t half_scale_offset(int L5, int Vh) {
@@ -101,6 +119,14 @@ struct Geom {
 
 __host__ __device__ __forceinline__ uint32_t fastdiv_magic(uint32_t d) {
   return d <= 1 ? 0u : (uint32_t)((1ull << 32) / d + 1ull);
+}
+// magic of d for all n < nmax, or 0 where the quotient would not be exact
+__host__ __device__ __forceinline__ uint32_t div_magic(uint32_t d, uint64_t nmax) {
+  return d <= 1 || nmax * d >= (1ull << 32) ? 0u : fastdiv_magic(d);
+}
+// n / d with the magic of d (0: divide)
+__device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
+  return d == 1 ? n : m != 0 ? (int)__umulhi((uint32_t)n, m) : n / d;
 }
 __device__ __forceinline__ int fastdiv(int n, uint32_t m) { return m == 0 ? n : (int)__umulhi((uint32_t)n, m); }
 
@@ -244,12 +270,12 @@ struct FieldDesc {
   int Vh, L5;
 };
 
-template <int P> struct SpinorIO;
+template <int P> struct SpinorAt;
 
-template <> struct SpinorIO<F64> {
+template <> struct SpinorAt<F64> {
   using R = double;
-  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, int cb, int s, R v[24]) {
-    const double2* p = reinterpret_cast<const double2*>(base) + tile_index(cb, s, 0, f.L5, 12);
+  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, const Place& at, R v[24]) {
+    const double2* p = reinterpret_cast<const double2*>(base) + group_index(at, 0, 12);
 #pragma unroll
     for (int g = 0; g < 12; ++g) {
       const v2d d = ldg<v2d>(p + (size_t)g * kSiteTile);
@@ -258,8 +284,8 @@ template <> struct SpinorIO<F64> {
     }
   }
   // h = 0: comps 0..5 (spins 0,1); h = 1: comps 6..11 (spins 2,3)
-  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, int cb, int s, int h, R v[12]) {
-    const double2* p = reinterpret_cast<const double2*>(base) + tile_index(cb, s, 6 * h, f.L5, 12);
+  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, const Place& at, int h, R v[12]) {
+    const double2* p = reinterpret_cast<const double2*>(base) + group_index(at, 6 * h, 12);
 #pragma unroll
     for (int g = 0; g < 6; ++g) {
       const v2d d = ldg<v2d>(p + (size_t)g * kSiteTile);
@@ -267,18 +293,18 @@ template <> struct SpinorIO<F64> {
       v[2 * g + 1] = d.y;
     }
   }
-  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, int cb, int s, const R v[24],
+  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, const Place& at, const R v[24],
                                                 bool nt = false) {
-    double2* p = reinterpret_cast<double2*>(base) + tile_index(cb, s, 0, f.L5, 12);
+    double2* p = reinterpret_cast<double2*>(base) + group_index(at, 0, 12);
 #pragma unroll
     for (int g = 0; g < 12; ++g) stg<v2d>(p + (size_t)g * kSiteTile, v2d{v[2 * g], v[2 * g + 1]}, nt);
   }
 };
 
-template <> struct SpinorIO<F32> {
+template <> struct SpinorAt<F32> {
   using R = float;
-  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, int cb, int s, R v[24]) {
-    const float4* p = reinterpret_cast<const float4*>(base) + tile_index(cb, s, 0, f.L5, 6);
+  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, const Place& at, R v[24]) {
+    const float4* p = reinterpret_cast<const float4*>(base) + group_index(at, 0, 6);
 #pragma unroll
     for (int g = 0; g < 6; ++g) {
       const v4f d = ldg<v4f>(p + (size_t)g * kSiteTile);
@@ -288,8 +314,8 @@ template <> struct SpinorIO<F32> {
       v[4 * g + 3] = d.w;
     }
   }
-  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, int cb, int s, int h, R v[12]) {
-    const float4* p = reinterpret_cast<const float4*>(base) + tile_index(cb, s, 3 * h, f.L5, 6);
+  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, const Place& at, int h, R v[12]) {
+    const float4* p = reinterpret_cast<const float4*>(base) + group_index(at, 3 * h, 6);
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
       const v4f d = ldg<v4f>(p + (size_t)g * kSiteTile);
@@ -299,9 +325,9 @@ template <> struct SpinorIO<F32> {
       v[4 * g + 3] = d.w;
     }
   }
-  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, int cb, int s, const R v[24],
+  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, const Place& at, const R v[24],
                                                 bool nt = false) {
-    float4* p = reinterpret_cast<float4*>(base) + tile_index(cb, s, 0, f.L5, 6);
+    float4* p = reinterpret_cast<float4*>(base) + group_index(at, 0, 6);
 #pragma unroll
     for (int g = 0; g < 6; ++g) stg<v4f>(p + (size_t)g * kSiteTile, v4f{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]}, nt);
   }
@@ -309,13 +335,13 @@ template <> struct SpinorIO<F32> {
 
 constexpr float kMinNormalF32 = 1.17549435e-38f;
 
-template <int P> struct SpinorIO16 {
+template <int P> struct SpinorAt16 {
   using R = float;
-  static __device__ __forceinline__ float scale(const char* base, const FieldDesc& f, int cb, int s) {
-    return ldg<float>(reinterpret_cast<const float*>(base + half_scale_offset(f.L5, f.Vh)) + tile_scale_index(cb, s, f.L5));
+  static __device__ __forceinline__ float scale(const char* base, const FieldDesc& f, const Place& at) {
+    return ldg<float>(reinterpret_cast<const float*>(base + half_scale_offset(f.L5, f.Vh)) + scale_index(at));
   }
-  static __device__ __forceinline__ void group(const char* base, const FieldDesc& f, int cb, int s, int g, float sc, R* v) {
-    const v4u q = ldg<v4u>(reinterpret_cast<const uint4*>(base) + tile_index(cb, s, g, f.L5, 3));
+  static __device__ __forceinline__ void group(const char* base, const FieldDesc& f, const Place& at, int g, float sc, R* v) {
+    const v4u q = ldg<v4u>(reinterpret_cast<const uint4*>(base) + group_index(at, g, 3));
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
     if constexpr (P == I16) {
       // q/32767 * sc as q * (sc/32767): one multiply per value
@@ -332,30 +358,30 @@ template <int P> struct SpinorIO16 {
       for (int k = 0; k < 8; ++k) v[k] *= sc;
     }
   }
-  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, int cb, int s, R v[24]) {
-    const float sc = scale(base, f, cb, s);
+  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, const Place& at, R v[24]) {
+    const float sc = scale(base, f, at);
 #pragma unroll
-    for (int g = 0; g < 3; ++g) group(base, f, cb, s, g, sc, v + 8 * g);
+    for (int g = 0; g < 3; ++g) group(base, f, at, g, sc, v + 8 * g);
   }
   // the 12 stored complex numbers as (re, im) 16-bit pairs, and the site's scale
-  static __device__ __forceinline__ void load_packed(const char* base, const FieldDesc& f, int cb, int s, uint32_t q[12],
+  static __device__ __forceinline__ void load_packed(const char* base, const FieldDesc& f, const Place& at, uint32_t q[12],
                                                      float& sc) {
-    sc = scale(base, f, cb, s);
+    sc = scale(base, f, at);
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
-      const v4u d = ldg<v4u>(reinterpret_cast<const uint4*>(base) + tile_index(cb, s, g, f.L5, 3));
+      const v4u d = ldg<v4u>(reinterpret_cast<const uint4*>(base) + group_index(at, g, 3));
       q[4 * g] = d.x;
       q[4 * g + 1] = d.y;
       q[4 * g + 2] = d.z;
       q[4 * g + 3] = d.w;
     }
   }
-  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, int cb, int s, int h, R v[12]) {
-    const float sc = scale(base, f, cb, s);
+  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, const Place& at, int h, R v[12]) {
+    const float sc = scale(base, f, at);
     R t[16];
     // reals 0..11 live in groups 0 and 1 (first half), reals 12..23 in group 1 (second half) and 2
-    group(base, f, cb, s, h, sc, t);
-    group(base, f, cb, s, h + 1, sc, t + 8);
+    group(base, f, at, h, sc, t);
+    group(base, f, at, h + 1, sc, t + 8);
     if (h == 0) {
 #pragma unroll
       for (int k = 0; k < 12; ++k) v[k] = t[k];
@@ -364,7 +390,7 @@ template <int P> struct SpinorIO16 {
       for (int k = 0; k < 12; ++k) v[k] = t[k + 4];
     }
   }
-  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, int cb, int s, const R v[24],
+  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, const Place& at, const R v[24],
                                                 bool nt = false) {
     float m = 0.f;
 #pragma unroll
@@ -374,7 +400,7 @@ template <int P> struct SpinorIO16 {
     const bool keep = m >= kMinNormalF32;
     const float inv = keep ? 1.0f / m : 0.f;
     if (!keep) m = 0.f;
-    uint4* p = reinterpret_cast<uint4*>(base) + tile_index(cb, s, 0, f.L5, 3);
+    uint4* p = reinterpret_cast<uint4*>(base) + group_index(at, 0, 3);
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
       const R* w = v + 8 * g;
@@ -382,12 +408,39 @@ template <int P> struct SpinorIO16 {
                   pack2<P>(w[4] * inv, w[5] * inv), pack2<P>(w[6] * inv, w[7] * inv)};
       stg<v4u>(p + (size_t)g * kSiteTile, q, nt);
     }
-    stg<float>(reinterpret_cast<float*>(base + half_scale_offset(f.L5, f.Vh)) + tile_scale_index(cb, s, f.L5), m, nt);
+    stg<float>(reinterpret_cast<float*>(base + half_scale_offset(f.L5, f.Vh)) + scale_index(at), m, nt);
   }
 };
-template <> struct SpinorIO<F16> : SpinorIO16<F16> {};
-template <> struct SpinorIO<BF16> : SpinorIO16<BF16> {};
-template <> struct SpinorIO<I16> : SpinorIO16<I16> {};
+template <> struct SpinorAt<F16> : SpinorAt16<F16> {};
+template <> struct SpinorAt<BF16> : SpinorAt16<BF16> {};
+template <> struct SpinorAt<I16> : SpinorAt16<I16> {};
+
+// the same by checkerboard index and slice
+template <int P> struct SpinorIO : SpinorAt<P> {
+  using A = SpinorAt<P>;
+  using R = typename A::R;
+  static __device__ __forceinline__ Place at(const FieldDesc& f, int cb, int s) { return place_of(cb, s, f.L5); }
+  static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, int cb, int s, R v[24]) {
+    A::load(base, f, at(f, cb, s), v);
+  }
+  static __device__ __forceinline__ void load_half(const char* base, const FieldDesc& f, int cb, int s, int h, R v[12]) {
+    A::load_half(base, f, at(f, cb, s), h, v);
+  }
+  static __device__ __forceinline__ void store(char* base, const FieldDesc& f, int cb, int s, const R v[24],
+                                               bool nt = false) {
+    A::store(base, f, at(f, cb, s), v, nt);
+  }
+  static __device__ __forceinline__ void load_packed(const char* base, const FieldDesc& f, int cb, int s, uint32_t q[12],
+                                                     float& sc) {
+    A::load_packed(base, f, at(f, cb, s), q, sc);
+  }
+  static __device__ __forceinline__ float scale(const char* base, const FieldDesc& f, int cb, int s) {
+    return A::scale(base, f, at(f, cb, s));
+  }
+  static __device__ __forceinline__ void group(const char* base, const FieldDesc& f, int cb, int s, int g, float sc, R* v) {
+    A::group(base, f, at(f, cb, s), g, sc, v);
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Gauge links: 12 stored reals, row 2 = conj(row0 x row1).

@@ -1,0 +1,754 @@
+// The fused stencil for fifth dimensions of a multiple of four slices, 32- and
+// 16-bit storage: the same launches as dslash5_kernel without the M_phi
+// prologue, with the work of a site laid over quads of lanes.
+//
+// A wavefront owns 16 consecutive sites x 4 consecutive slices, lane
+// 4 * site + (slice & 3); a site's L5 / 4 wavefronts form one workgroup (times
+// CB / 16 tiles).  Four lanes of a quad therefore share a site and its links,
+// and hold neighbouring slices:
+//  * the colour product of 16-bit storage runs on the matrix cores.  A quad is
+//    one block of the 16-block 4x4x4 MFMA: A = rows of the site's link as a
+//    real 6 x 6 matrix (one row per lane), B = the four lanes' projected
+//    colour vectors, D = the four lanes' products, every lane's own;
+//  * the fifth-dimension operators run in registers.  M5^-1 is the recurrence
+//    S_i = x_i - kappa S_{i-1}: two DPP steps inside the quad, then one
+//    exchange of the wavefronts' last values through LDS (which also carries
+//    the -mq wall), so a chain costs one barrier and no column ever passes
+//    through LDS;
+//  * a neighbour is addressed by a 32-bit byte offset staged in LDS, on a
+//    uniform base that holds the wavefront's slices.
+//
+// What bounds it (32^3 x 64, L5 = 12, FP16, the plain hop, 434 us against 465
+// of dslash5_kernel; 24^3 x 64 x 16: 259 against 291, 16^3 x 32 x 12: 29
+// against 36): no single unit.  600 VALU instructions per wavefront take 200
+// us by themselves, the neighbour loads add 170, the stores 130 and the link
+// stage 25; the L1 answers 0.41 accesses of 64 bytes per clock.  With lanes on
+// 16 sites of one slice (256 contiguous bytes per 16 lanes) replaced by a quad
+// reading 64-byte pieces of four slices the same kernel took 680 us, which is
+// why the fields are stored quad by quad (dev_common.h).  Fewer or more
+// neighbours in flight per lane (1, 4, 8) and 3-7 waves per SIMD were no
+// faster; FP16 at 6 waves spills (+12 %).
+#include "dev_common.h"
+#include "hop.h"
+#include "kernels.h"
+
+namespace mdwf {
+
+namespace {
+
+// ---------------------------------------------------------------------------
+// storage: 16-byte groups per site and slice, and the place of a lane's own
+// site inside its wavefront's 16 sites x 4 slices
+// ---------------------------------------------------------------------------
+template <int P> constexpr int kGroups = P == F32 ? 6 : 3;
+template <int P> constexpr int kSliceBytes = kGroups<P> * 16 * kSiteTile;  // one slice of a tile
+constexpr bool is16(int p) { return p == F16 || p == BF16 || p == I16; }
+
+template <class T> __device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
+}
+
+// A load or store at (uniform base) + (32-bit lane offset) + constant.
+template <class V> __device__ __forceinline__ V ldo(const char* base, uint32_t off, int imm) {
+  return *(const MDWF_GLOBAL V*)((const MDWF_GLOBAL char*)(base) + (size_t)off + imm);
+}
+template <class V> __device__ __forceinline__ void sto(char* base, uint32_t off, int imm, V v, bool nt) {
+  MDWF_GLOBAL V* p = (MDWF_GLOBAL V*)((MDWF_GLOBAL char*)(base) + (size_t)off + imm);
+  if (nt) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// One spinor as it is stored.
+template <int P> struct Raw {
+  v4u g[kGroups<P>];
+  float sc;
+};
+
+// Bases of one half-field for this wavefront: its data and its scales, both
+// at tile 0 and slice 4 w.
+struct Base {
+  char* d;
+  char* s;
+};
+template <int P> __device__ __forceinline__ Base field_base(char* const* table, int slot, const Geom& g, int w) {
+  char* p = uniform_ptr(table[slot]);
+  Base b;
+  b.d = p + (size_t)w * 4 * kSliceBytes<P>;
+  b.s = p;
+  if constexpr (is16(P)) b.s = p + half_scale_offset(g.L5, g.Vh) + (size_t)w * 4 * 4 * kSiteTile;
+  return b;
+}
+// the same moved to tile `tile`
+template <int P> __device__ __forceinline__ Base at_tile(Base b, int tile, int L5) {
+  b.d += (size_t)tile * L5 * kSliceBytes<P>;
+  b.s += (size_t)tile * L5 * 4 * kSiteTile;
+  return b;
+}
+
+template <int P> __device__ __forceinline__ void load_raw(const Base& b, uint32_t off, uint32_t soff, Raw<P>& r) {
+  if constexpr (is16(P)) r.sc = ldo<float>(b.s, soff, 0);
+#pragma unroll
+  for (int k = 0; k < kGroups<P>; ++k) r.g[k] = ldo<v4u>(b.d, off, k * 16 * kSiteTile);
+}
+template <int P> __device__ __forceinline__ void pin_raw(Raw<P>& r) {
+#pragma unroll
+  for (int k = 0; k < kGroups<P>; ++k) asm volatile("" : "+v"(r.g[k]) : : "memory");
+  if constexpr (is16(P)) asm volatile("" : "+v"(r.sc) : : "memory");
+}
+template <int P> __device__ __forceinline__ void unpack(const Raw<P>& r, float v[24]) {
+#pragma unroll
+  for (int k = 0; k < kGroups<P>; ++k) {
+    const uint32_t w[4] = {r.g[k].x, r.g[k].y, r.g[k].z, r.g[k].w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (P == F32) {
+        v[4 * k + j] = __uint_as_float(w[j]);
+      } else if constexpr (P == I16) {
+        const float scq = r.sc * (1.0f / 32767.0f);
+        v[8 * k + 2 * j] = (float)(int16_t)(uint16_t)(w[j] & 0xffffu) * scq;
+        v[8 * k + 2 * j + 1] = (float)(int16_t)(uint16_t)(w[j] >> 16) * scq;
+      } else {
+        float a, b;
+        unpack2<P>(w[j], a, b);
+        v[8 * k + 2 * j] = a * r.sc;
+        v[8 * k + 2 * j + 1] = b * r.sc;
+      }
+    }
+  }
+}
+template <int P>
+__device__ __forceinline__ void store_own(const Base& b, uint32_t off, uint32_t soff, const float v[24], bool nt) {
+  if constexpr (P == F32) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+      sto<v4f>(b.d, off, k * 16 * kSiteTile, v4f{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]}, nt);
+  } else {
+    // as SpinorIO16::store
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < 24; ++k) m = fmaxf(m, fabsf(v[k]));
+    const bool keep = m >= kMinNormalF32;
+    const float inv = keep ? 1.0f / m : 0.f;
+    if (!keep) m = 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float* w = v + 8 * k;
+      sto<v4u>(b.d, off, k * 16 * kSiteTile,
+               v4u{pack2<P>(w[0] * inv, w[1] * inv), pack2<P>(w[2] * inv, w[3] * inv), pack2<P>(w[4] * inv, w[5] * inv),
+                   pack2<P>(w[6] * inv, w[7] * inv)},
+               nt);
+    }
+    sto<float>(b.s, soff, 0, m, nt);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Stage: neighbour offsets and links of the workgroup's sites in LDS.
+//   neighbours: per site 8 x (data offset, scale offset), rows of 18 words
+//   links, 16-bit storage (matrix cores): per direction the real 6 x 6 matrix
+//     of V = U or U^+ (antiperiodic sign included): row 2a = (Re V_ab, -Im V_ab),
+//     row 2a + 1 = (Im V_ab, Re V_ab), one 16-bit pair per b, three pairs and a
+//     zero word per row; site rows of 208 words (16-byte reads, no conflicts)
+//   links, other storage: per direction the 18 reals of U, 20 words; site rows
+//     of 164 words
+// ---------------------------------------------------------------------------
+constexpr int kNbrRow = 18;
+template <int P> constexpr int kLinkDir = Packed<P>::enabled ? 24 : 20;
+template <int P> constexpr int kLinkRow = Packed<P>::enabled ? 208 : 164;
+constexpr int kTotRow = 24;
+
+template <int P> constexpr size_t stage_bytes(int CB) { return (size_t)CB * (kNbrRow + kLinkRow<P>) * 4; }
+constexpr size_t totals_bytes(int CB, int L5) { return (size_t)CB * (L5 / 4) * kTotRow * 4; }
+// one area of wavefront totals (a second chain's totals overlay the stage,
+// which is dead once the first chain's barrier has passed), and the partial
+// sums of the reduction
+template <int P> constexpr size_t lds_bytes(int CB, int L5) {
+  return stage_bytes<P>(CB) + totals_bytes(CB, L5) + (size_t)(CB / 16) * (L5 / 4) * 8;
+}
+
+template <int P>
+__device__ __forceinline__ void fill_stage(const DslashArgs& A, uint32_t* nbr, uint32_t* lnk, int CB, int cb_log2,
+                                           int cb0, int tid, int nthr) {
+  const Geom& g = A.g;
+  for (int task = tid; task < CB * 8; task += nthr) {
+    const int cbl = task & (CB - 1);
+    const int dir = task >> cb_log2;
+    const int cb = cb0 + cbl;
+    int nb = 0;
+    float r[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) r[k] = 0;
+    bool flip = false;
+    if (cb < g.Vh) {
+      int X[4];
+      site_coords(g, A.out_par, cb, X[0], X[1], X[2], X[3]);
+      const int mu = dir & 3;
+      const int Lmu = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
+      const int xm = mu == 0 ? X[0] : mu == 1 ? X[1] : mu == 2 ? X[2] : X[3];
+      const bool fwd = dir < 4;
+      const int xn = fwd ? (xm + 1 == Lmu ? 0 : xm + 1) : (xm == 0 ? Lmu : xm) - 1;
+      flip = mu == 3 && g.tap && xm == (fwd ? Lmu - 1 : 0);
+      nb = cb_index(g, mu == 0 ? xn : X[0], mu == 1 ? xn : X[1], mu == 2 ? xn : X[2], mu == 3 ? xn : X[3]);
+      LinkIO<P>::load_raw(A.gauge, g.Vh, fwd ? A.out_par : 1 - A.out_par, mu, fwd ? cb : nb, r);
+    }
+    Cplx<float> U[3][3];
+    link_from_raw(r, U);
+    const float sg = flip ? -1.f : 1.f;
+    const uint32_t tile = (uint32_t)nb / kSiteTile, in = (uint32_t)nb % kSiteTile;
+    nbr[cbl * kNbrRow + 2 * dir] = (tile * (uint32_t)g.L5 + in / 4) * kSliceBytes<P> + in % 4 * 64;
+    nbr[cbl * kNbrRow + 2 * dir + 1] = (tile * (uint32_t)g.L5 + in / 4) * (4 * kSiteTile) + in % 4 * 16;
+    uint32_t* row = lnk + cbl * kLinkRow<P> + dir * kLinkDir<P>;
+    if constexpr (Packed<P>::enabled) {
+      using K = Packed<P>;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        v4u re{0, 0, 0, 0}, im{0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          const Cplx<float> u = dir < 4 ? U[a][b] : Cplx<float>{U[b][a].re, -U[b][a].im};
+          const float vr = sg * u.re, vi = sg * u.im;
+          re[b] = __builtin_bit_cast(uint32_t, K::make(vr, -vi));
+          im[b] = __builtin_bit_cast(uint32_t, K::make(vi, vr));
+        }
+        *reinterpret_cast<v4u*>(row + 8 * a) = re;
+        *reinterpret_cast<v4u*>(row + 8 * a + 4) = im;
+      }
+    } else {
+      float* fr = reinterpret_cast<float*>(row);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        fr[2 * k] = sg * U[k / 3][k % 3].re;
+        fr[2 * k + 1] = sg * U[k / 3][k % 3].im;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the hop
+// ---------------------------------------------------------------------------
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// D += A B for the quad's block: a = this lane's row of the link matrix (four
+// of its columns), b = this lane's colour vector (the same four components)
+template <int P> __device__ __forceinline__ v4f mfma4(uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1, v4f c) {
+  const v2u a{a0, a1}, b{b0, b1};
+  if constexpr (P == F16)
+    return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
+}
+
+template <int P, bool DAG, int D>
+__device__ __forceinline__ void hop_compute(const uint32_t* lnk, int q, const Raw<P>& n, Cplx<float> acc[4][3]) {
+  constexpr int MU = D / 2, FB = D % 2;
+  constexpr int DIR = MU + 4 * FB;
+  constexpr int SG = (FB == 0) == DAG ? +1 : -1;  // projector 1 + SG g_mu
+  Cplx<float> w[2][3];
+  if constexpr (Packed<P>::enabled) {
+    using T2 = typename Packed<P>::T2;
+    T2 psi[4][3], h[2][3];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = __builtin_bit_cast(T2, (uint32_t)n.g[k / 4][k % 4]);
+    project<MU, SG>(psi, h);
+    const v4u r0 = *reinterpret_cast<const v4u*>(lnk + DIR * kLinkDir<P> + 4 * q);
+    const v4u r1 = *reinterpret_cast<const v4u*>(lnk + DIR * kLinkDir<P> + 16 + 4 * (q & 1));
+    v4f d[2][2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const uint32_t h0 = __builtin_bit_cast(uint32_t, h[k][0]), h1 = __builtin_bit_cast(uint32_t, h[k][1]);
+      d[k][0] = mfma4<P>(r0.x, r0.y, h0, h1, v4f{0, 0, 0, 0});
+      d[k][1] = mfma4<P>(r1.x, r1.y, h0, h1, v4f{0, 0, 0, 0});
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const uint32_t h2 = __builtin_bit_cast(uint32_t, h[k][2]);
+      d[k][0] = mfma4<P>(r0.z, r0.w, h2, 0u, d[k][0]);
+      d[k][1] = mfma4<P>(r1.z, r1.w, h2, 0u, d[k][1]);
+      w[k][0] = {d[k][0].x, d[k][0].y};
+      w[k][1] = {d[k][0].z, d[k][0].w};
+      w[k][2] = {d[k][1].x, d[k][1].y};
+    }
+    accumulate_scaled<MU, SG>(acc, w, n.sc);
+  } else {
+    Cplx<float> U[3][3], psi[4][3], h[2][3];
+    const float* row = reinterpret_cast<const float*>(lnk) + DIR * kLinkDir<P>;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const v4f u = *reinterpret_cast<const v4f*>(row + 4 * k);
+      U[2 * k / 3][2 * k % 3] = {u.x, u.y};
+      U[(2 * k + 1) / 3][(2 * k + 1) % 3] = {u.z, u.w};
+    }
+    const float2 u8 = *reinterpret_cast<const float2*>(row + 16);
+    U[2][2] = {u8.x, u8.y};
+    if constexpr (P == I16) {  // unscaled integers, the scale joins the accumulation
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        const uint32_t v = n.g[k / 4][k % 4];
+        psi[k / 3][k % 3] = {(float)(int16_t)(uint16_t)(v & 0xffffu), (float)(int16_t)(uint16_t)(v >> 16)};
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 12; ++k)
+        psi[k / 3][k % 3] = {__uint_as_float(n.g[k / 2][2 * (k % 2)]), __uint_as_float(n.g[k / 2][2 * (k % 2) + 1])};
+    }
+    project<MU, SG>(psi, h);
+    colour_mul<FB == 1>(U, h, w);
+    if constexpr (P == I16) accumulate_scaled<MU, SG>(acc, w, n.sc * (1.0f / 32767.0f));
+    else accumulate<MU, SG>(acc, w);
+  }
+}
+
+// Neighbours loaded together per thread.
+constexpr int kQuadBatch = 2;
+
+template <int P, bool DAG, int D, int END, int B0> struct HopRun {
+  static __device__ __forceinline__ void load(const Base& in, const uint32_t* nbr, uint32_t lo, uint32_t ls, Raw<P>* n) {
+    if constexpr (D < END) {
+      constexpr int DIR = D / 2 + 4 * (D % 2);
+      const uint2 o = *reinterpret_cast<const uint2*>(nbr + 2 * DIR);
+      load_raw<P>(in, o.x + lo, o.y + ls, n[D - B0]);
+      HopRun<P, DAG, D + 1, END, B0>::load(in, nbr, lo, ls, n);
+    }
+  }
+  static __device__ __forceinline__ void compute(const uint32_t* lnk, int q, const Raw<P>* n, Cplx<float> acc[4][3]) {
+    if constexpr (D < END) {
+      hop_compute<P, DAG, D>(lnk, q, n[D - B0], acc);
+      HopRun<P, DAG, D + 1, END, B0>::compute(lnk, q, n, acc);
+    }
+  }
+};
+
+template <int P, bool DAG, int NB, int B0>
+__device__ __forceinline__ void hop_all(const Base& in, const uint32_t* nbr, const uint32_t* lnk, int q, uint32_t lo,
+                                        uint32_t ls, Cplx<float> acc[4][3]) {
+  if constexpr (B0 < 8) {
+    Raw<P> n[NB];
+    HopRun<P, DAG, B0, B0 + NB, B0>::load(in, nbr, lo, ls, n);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) pin_raw<P>(n[j]);
+    HopRun<P, DAG, B0, B0 + NB, B0>::compute(lnk, q, n, acc);
+    pin_acc(acc);
+    hop_all<P, DAG, NB, B0 + NB>(in, nbr, lnk, q, lo, ls, acc);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// fifth-dimension chains over the quad
+// ---------------------------------------------------------------------------
+// Multiply-adds whose first factor comes from another lane of the quad
+// (v_fmac_f32_dpp; the compiler keeps a separate move for each).  A DPP source
+// must not have been written by the two preceding VALU instructions: each
+// block starts with the two wait states, and inside a block a register is read
+// at least five instructions after it was written.
+
+// Two steps of the recurrence on six columns, in place: v += k1 * (one slice
+// back), then v += k2 * (two slices back).  "Back" is slice s - 1 for columns
+// walked upwards (LOWER), s + 1 for the others; the quad's ends read
+// themselves with a zero coefficient.
+template <bool LOWER> __device__ __forceinline__ void quad_scan6(float* v, float k1, float k2) {
+  if constexpr (LOWER)
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %0, %6 quad_perm:[0,0,1,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %6 quad_perm:[0,0,1,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %6 quad_perm:[0,0,1,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %6 quad_perm:[0,0,1,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %6 quad_perm:[0,0,1,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %6 quad_perm:[0,0,1,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %7 quad_perm:[0,0,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %7 quad_perm:[0,0,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %7 quad_perm:[0,0,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %7 quad_perm:[0,0,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %7 quad_perm:[0,0,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %7 quad_perm:[0,0,0,1] row_mask:0xf bank_mask:0xf"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5])
+        : "v"(k1), "v"(k2));
+  else
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %0, %6 quad_perm:[1,2,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %6 quad_perm:[1,2,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %6 quad_perm:[1,2,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %6 quad_perm:[1,2,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %6 quad_perm:[1,2,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %6 quad_perm:[1,2,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %7 quad_perm:[2,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %7 quad_perm:[2,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %7 quad_perm:[2,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %7 quad_perm:[2,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %7 quad_perm:[2,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %7 quad_perm:[2,3,3,3] row_mask:0xf bank_mask:0xf"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5])
+        : "v"(k1), "v"(k2));
+}
+
+// o[i] += k * perm(x[i]), i < 6
+#define MDWF_QUAD_FMA6(PERM, o, x, k)                                                                            \
+  asm("s_nop 1\n\t"                                                                                              \
+      "v_fmac_f32_dpp %0, %6, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                             \
+      "v_fmac_f32_dpp %1, %7, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                             \
+      "v_fmac_f32_dpp %2, %8, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                             \
+      "v_fmac_f32_dpp %3, %9, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                             \
+      "v_fmac_f32_dpp %4, %10, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                            \
+      "v_fmac_f32_dpp %5, %11, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf"                                \
+      : "+v"((o)[0]), "+v"((o)[1]), "+v"((o)[2]), "+v"((o)[3]), "+v"((o)[4]), "+v"((o)[5])                       \
+      : "v"((x)[0]), "v"((x)[1]), "v"((x)[2]), "v"((x)[3]), "v"((x)[4]), "v"((x)[5]), "v"(k))
+
+struct QuadPos {
+  int q;       // lane's slice inside the quad
+  int w, nw;   // wavefront's place along the fifth dimension, and how many
+  int site;    // 0..15
+  float* tot;  // [w][site][24] of this 16-site tile
+};
+
+// Walks the columns of v: with SCAN first y = the recurrence S_i = x_i -
+// kappa S_{i-1} (alpha M5 y without the wall), then
+//   out_i = add_i + t0 y_i + t1 y_{i-1}   (without SCAN, add_i + t1 y_{i-1}),
+// where y includes the wall (y_{-1} = -mq y_{L5-1}).  DAG exchanges the walk
+// directions of the two chiralities (spins 0,1: reals 0..11; 2,3: 12..23).
+// In the quad S takes two steps; the wavefronts' last values T_w then give
+// every wavefront the value E before its first slice,
+//   E_w = sum_{w' < w} k4^(w-1-w') T_w' - mq/c k4^w sum_w' k4^(nw-1-w') T_w'
+// (k4 = kappa^4, c = 1 + mq (-kappa)^L5), and y_i = S_i + (-kappa)^(i+1) E.
+// Each lane forms E of six of the 24 reals and the quad shares them by DPP.
+template <bool SCAN, bool SHIFT, bool DAG>
+__device__ __forceinline__ void quad_chain(float v[24], const float* add, const QuadPos& Q, float kappa, float mq,
+                                           float inv_c, float t0, float t1) {
+  const int pl = Q.q, pu = 3 - Q.q;  // place along the walk
+  const float nk = -kappa, k2 = kappa * kappa;
+  if constexpr (SCAN) {
+    const float l1 = pl >= 1 ? nk : 0.f, l2 = pl >= 2 ? k2 : 0.f;
+    const float u1 = pu >= 1 ? nk : 0.f, u2 = pu >= 2 ? k2 : 0.f;
+    constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;  // first lower and upper real
+    quad_scan6<true>(v + lc, l1, l2);
+    quad_scan6<true>(v + lc + 6, l1, l2);
+    quad_scan6<false>(v + uc, u1, u2);
+    quad_scan6<false>(v + uc + 6, u1, u2);
+  }
+  // last values along the walk: lane 3 holds those of the lower comps, lane 0
+  // those of the upper ones
+  {
+    float* t = Q.tot + ((size_t)Q.w * 16 + Q.site) * kTotRow;
+    constexpr int lo = DAG ? 12 : 0, up = DAG ? 0 : 12;
+    if (Q.q == 3) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        *reinterpret_cast<v4f*>(t + lo + 4 * k) = v4f{v[lo + 4 * k], v[lo + 4 * k + 1], v[lo + 4 * k + 2], v[lo + 4 * k + 3]};
+    }
+    if (Q.q == 0) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        *reinterpret_cast<v4f*>(t + up + 4 * k) = v4f{v[up + 4 * k], v[up + 4 * k + 1], v[up + 4 * k + 2], v[up + 4 * k + 3]};
+    }
+  }
+  // what needs no neighbour wavefront goes before the barrier
+  float out[24];
+  const float l1 = pl >= 1 ? t1 : 0.f, u1 = pu >= 1 ? t1 : 0.f;
+#pragma unroll
+  for (int k = 0; k < 24; ++k) out[k] = add == nullptr ? t0 * v[k] : SCAN ? fmaf(t0, v[k], add[k]) : add[k];
+  if constexpr (SHIFT) {
+    constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;
+    MDWF_QUAD_FMA6("[0,0,1,2]", out + lc, v + lc, l1);
+    MDWF_QUAD_FMA6("[0,0,1,2]", out + lc + 6, v + lc + 6, l1);
+    MDWF_QUAD_FMA6("[1,2,3,3]", out + uc, v + uc, u1);
+    MDWF_QUAD_FMA6("[1,2,3,3]", out + uc + 6, v + uc + 6, u1);
+  }
+  __syncthreads();
+  // E of reals 6q .. 6q+5
+  const bool lower6 = (Q.q < 2) != DAG;
+  const int wl = lower6 ? Q.w : Q.nw - 1 - Q.w;  // place along these reals' walk
+  const float* t = Q.tot + Q.site * kTotRow + 6 * Q.q;
+  float E[6] = {0, 0, 0, 0, 0, 0};
+  if constexpr (SCAN) {
+    const float k4 = k2 * k2;
+    float wall = -mq * inv_c;
+    for (int j = 0; j < wl; ++j) wall *= k4;
+    float carry = 1.f;
+    for (int o = Q.nw - 1; o >= 0; --o) {
+      const float c = wall + (o < wl ? carry : 0.f);
+      const float* x = t + (size_t)(lower6 ? o : Q.nw - 1 - o) * 16 * kTotRow;
+      const float2 a = *reinterpret_cast<const float2*>(x), b = *reinterpret_cast<const float2*>(x + 2),
+                   d = *reinterpret_cast<const float2*>(x + 4);
+      E[0] = fmaf(c, a.x, E[0]);
+      E[1] = fmaf(c, a.y, E[1]);
+      E[2] = fmaf(c, b.x, E[2]);
+      E[3] = fmaf(c, b.y, E[3]);
+      E[4] = fmaf(c, d.x, E[4]);
+      E[5] = fmaf(c, d.y, E[5]);
+      wall *= k4;
+      carry = o < wl ? carry * k4 : carry;
+    }
+  } else {
+    const int prev = wl == 0 ? Q.nw - 1 : wl - 1;
+    const float c = wl == 0 ? -mq : 1.f;
+    const float* x = t + (size_t)(lower6 ? prev : Q.nw - 1 - prev) * 16 * kTotRow;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) E[k] = c * x[k];
+  }
+  // y_i = S_i + (-kappa)^(i+1) E enters out_i with t0, y_{i-1} with t1
+  float el, eu;
+  if constexpr (SCAN) {
+    const float k3 = nk * k2, k4 = k2 * k2;
+    const float pw[5] = {1.f, nk, k2, k3, k4};
+    auto pick = [&](int p, int d) {  // (-kappa)^(p + d)
+      return p == 0 ? pw[d] : p == 1 ? pw[1 + d] : p == 2 ? pw[2 + d] : pw[3 + d];
+    };
+    el = t0 * pick(pl, 1);
+    eu = t0 * pick(pu, 1);
+    if constexpr (SHIFT) {
+      el = fmaf(t1, pick(pl, 0), el);
+      eu = fmaf(t1, pick(pu, 0), eu);
+    }
+  } else {
+    el = pl == 0 ? t1 : 0.f;
+    eu = pu == 0 ? t1 : 0.f;
+  }
+  MDWF_QUAD_FMA6("[0,0,0,0]", out, E, DAG ? eu : el);
+  MDWF_QUAD_FMA6("[1,1,1,1]", out + 6, E, DAG ? eu : el);
+  MDWF_QUAD_FMA6("[2,2,2,2]", out + 12, E, DAG ? el : eu);
+  MDWF_QUAD_FMA6("[3,3,3,3]", out + 18, E, DAG ? el : eu);
+#pragma unroll
+  for (int k = 0; k < 24; ++k) v[k] = out[k];
+}
+
+// Fixed-order FP64 sum over a wavefront: DPP rows, then across the rows.
+__device__ __forceinline__ double wave_sum(double v) {
+  v = row_sum16(v);
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+
+// What a launch computes after the hop h (see DslashArgs for the operators).
+enum QuadProg : int {
+  QP_HOP = 0,   // h
+  QP_A1 = 1,    // M_phi M5^-1 h
+  QP_A2 = 2,    // aux + coef_y M5^-1 h
+  QP_A2C = 3,   // M5^-T (aux + coef_y M5^-1 h)
+  QP_B1 = 4,    // M_phi^T M5^-T h
+  QP_B2 = 5,    // M5^T aux + coef_y M_phi^T h
+  QP_B2C = 6,   // the same into r -= alpha (.) instead of out
+};
+constexpr bool prog_dag(int p) { return p == QP_B1 || p == QP_B2 || p == QP_B2C; }
+
+constexpr int kQuadThreads = 1024;
+// Resident waves per SIMD the register allocation must leave room for.
+template <int P> constexpr int kQuadWaves = is16(P) ? 5 : 4;
+
+template <int P, int PROG, bool DAG>
+__global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQuadWaves<P>))) void dslash_quad_kernel(
+    DslashArgs A) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int CB = 1 << A.cb_log2;
+  const int L5 = A.g.L5, nw = L5 >> 2;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  if (lb >= A.nslots * A.nblk) return;
+  int slot, blk;
+  block_slot(A, lb, slot, blk);
+  if (A.active != nullptr && A.active[(size_t)slot * A.active_stride] == 0) return;
+  const int cb0 = block_first_site(A, blk, CB);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sub = wave / nw;  // 16-site tile of the workgroup
+  const int w = wave - sub * nw;
+  const int lane = tid & 63, site = lane >> 2, q = lane & 3;
+  const int cbl = sub * 16 + site;
+  const int tile = __builtin_amdgcn_readfirstlane((cb0 >> 4) + sub);
+  const bool valid = cb0 + cbl < A.g.Vh;
+  const uint32_t lo = q * 16, ls = q * 4;  // the lane's slice
+  const uint32_t oo = (lane >> 4) * kSliceBytes<P> + (lane & 15) * 16, os = lane * 4;  // its own site and slice
+  const Coef5& cf = A.coef[slot];
+  const float mq = (float)cf.mq;
+
+  uint32_t* nbr = reinterpret_cast<uint32_t*>(smem + CB * kLinkRow<P> * 4);
+  uint32_t* lnk = reinterpret_cast<uint32_t*>(smem);
+  float* tot = reinterpret_cast<float*>(smem + stage_bytes<P>(CB));
+  double* red = reinterpret_cast<double*>(smem + stage_bytes<P>(CB) + totals_bytes(CB, L5));
+  const size_t tot_tile = (size_t)sub * nw * 16 * kTotRow;
+
+  fill_stage<P>(A, nbr, lnk, CB, A.cb_log2, cb0, tid, nthr);
+  __syncthreads();
+
+  float v[24];
+  {
+    Cplx<float> acc[4][3];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) acc[a][b] = {0, 0};
+    const Base in = field_base<P>(A.in, slot, A.g, w);
+    hop_all<P, DAG, kQuadBatch, 0>(in, nbr + cbl * kNbrRow, lnk + cbl * kLinkRow<P>, q, lo, ls, acc);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      v[2 * k] = acc[k / 3][k % 3].re;
+      v[2 * k + 1] = acc[k / 3][k % 3].im;
+    }
+  }
+
+  // a lane of a ragged tile's tail works on padding: its own site of the
+  // last tile is allocated, so its reads stay inside the field
+  const QuadPos Q{q, w, nw, site, tot + tot_tile};
+  const float kappa = (float)cf.kappa, inv_c = (float)cf.inv_c;
+  // M_phi M5^-1 and its transpose: coefficients rounded to FP32 once
+  const float b5a = (float)(cf.b5 * cf.inv_alpha), c5a = (float)(cf.c5 * cf.inv_alpha);
+  const bool in_tile = tile < ((A.g.Vh + 15) >> 4);
+  if constexpr (PROG == QP_A1) {
+    quad_chain<true, true, false>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+  } else if constexpr (PROG == QP_B1) {
+    quad_chain<true, true, true>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+  } else if constexpr (PROG == QP_A2 || PROG == QP_A2C) {
+    Raw<P> ar{};
+    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(A.aux, slot, A.g, w), tile, L5), oo, os, ar);
+    float aux[24];
+    unpack<P>(ar, aux);
+    quad_chain<true, false, false>(v, aux, Q, kappa, mq, inv_c, (float)(A.coef_y * cf.inv_alpha), 0.f);
+  } else if constexpr (PROG == QP_B2 || PROG == QP_B2C) {
+    // M5^T aux + coef_y M_phi^T h = (alpha aux + coef_y b5 h) + shift(beta aux + coef_y c5 h)
+    Raw<P> ar{};
+    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(A.aux, slot, A.g, w), tile, L5), oo, os, ar);
+    float aux[24], add[24];
+    unpack<P>(ar, aux);
+    const float al = (float)cf.alpha, be = (float)cf.beta;
+    const float b5y = (float)(A.coef_y * cf.b5), c5y = (float)(A.coef_y * cf.c5);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) {
+      add[k] = fmaf(al, aux[k], b5y * v[k]);
+      v[k] = fmaf(be, aux[k], c5y * v[k]);
+    }
+    quad_chain<false, true, true>(v, add, Q, 0.f, mq, 1.f, 0.f, 1.f);
+  }
+
+  if constexpr (PROG == QP_B2C) {
+    if (valid) {
+      const float alpha = (float)A.cg_st[slot].alpha;
+      const Base rb = at_tile<P>(field_base<P>(A.cg_r, slot, A.g, w), tile, L5);
+      Raw<P> rr;
+      load_raw<P>(rb, oo, os, rr);
+      float rv[24];
+      unpack<P>(rr, rv);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = rv[k] - alpha * v[k];
+      store_own<P>(rb, oo, os, v, A.nt_store);
+    }
+  }
+
+  if (A.reduce) {
+    // 24 squares per thread in FP32, everything above in FP64, one sum per
+    // wavefront; the tile's wavefronts are added in order, so the partial of a
+    // tile does not depend on the workgroup's width
+    float lr = 0;
+#pragma unroll
+    for (int k = 0; k < 24; ++k) lr += v[k] * v[k];
+    const double sum = wave_sum(valid ? (double)lr : 0.0);
+    if (lane == 0) red[wave] = sum;
+    __syncthreads();
+    if (w == 0 && lane == 0 && in_tile) {
+      double s = 0;
+      for (int k = 0; k < nw; ++k) s += red[wave + k];
+      A.partials[(size_t)slot * A.ntiles + tile] = s;
+    }
+  }
+
+  if constexpr (PROG == QP_A2C) {
+    QuadPos Q2 = Q;
+    Q2.tot = reinterpret_cast<float*>(smem) + tot_tile;  // over the stage, dead since the first chain's barrier
+    quad_chain<true, false, true>(v, nullptr, Q2, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
+  }
+  if constexpr (PROG != QP_B2C) {
+    if (valid) store_own<P>(at_tile<P>(field_base<P>(A.out, slot, A.g, w), tile, L5), oo, os, v, A.nt_store);
+  }
+  if ((PROG == QP_B1 && A.cg_update == 3) || (PROG == QP_B2C && A.cg_update == 1)) {
+    if (valid) {  // x += alpha p
+      const float alpha = (float)A.cg_st[slot].alpha;
+      Raw<P> pr;
+      Raw<F32> xr;
+      const Base xb = at_tile<F32>(field_base<F32>(A.cg_x, slot, A.g, w), tile, L5);
+      const uint32_t xo = (lane >> 4) * kSliceBytes<F32> + (lane & 15) * 16;
+      load_raw<P>(at_tile<P>(field_base<P>(A.cg_p, slot, A.g, w), tile, L5), oo, os, pr);
+      load_raw<F32>(xb, xo, 0, xr);
+      float pv[24], xv[24];
+      unpack<P>(pr, pv);
+      unpack<F32>(xr, xv);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) xv[k] += alpha * pv[k];
+      store_own<F32>(xb, xo, 0, xv, A.nt_store);
+    }
+  }
+}
+
+template <int P, int PROG, bool DAG>
+hipError_t launch_q(const DslashArgs& A, int threads, int grid, hipStream_t st) {
+  const size_t smem = lds_bytes<P>(1 << A.cb_log2, A.g.L5);
+  auto k = dslash_quad_kernel<P, PROG, DAG>;
+  if (smem > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  launch_k(k, dim3(grid), dim3(threads), smem, st, A);
+  return hipGetLastError();
+}
+
+// the program of a launch, or -1 where it has none here
+int quad_prog(const DslashArgs& A, bool dag) {
+  if (!dag) {
+    if (A.cg_update != 0) return -1;
+    if (A.c1 == CH_NONE && A.c2 == CH_NONE && A.aux_mode == AUX_NONE && A.coef_y == 1.0) return QP_HOP;
+    if (A.c1 == CH_MPHI_M5INV && A.c2 == CH_NONE && A.aux_mode == AUX_NONE && A.coef_y == 1.0) return QP_A1;
+    if (A.c1 == CH_M5INV && A.aux_mode == AUX_PLAIN && (A.c2 == CH_NONE || A.c2 == CH_M5INV_DAG))
+      return A.c2 == CH_NONE ? QP_A2 : QP_A2C;
+    return -1;
+  }
+  if (A.c2 != CH_NONE) return -1;
+  if (A.c1 == CH_NONE && A.aux_mode == AUX_NONE && A.coef_y == 1.0 && A.cg_update == 0) return QP_HOP;
+  if (A.c1 == CH_MPHIDAG_M5INVDAG && A.aux_mode == AUX_NONE && A.coef_y == 1.0 && (A.cg_update == 0 || A.cg_update == 3))
+    return QP_B1;
+  if (A.c1 == CH_MPHI_DAG && A.aux_mode == AUX_M5DAG) return A.cg_update == 0 ? QP_B2 : A.cg_update <= 2 ? QP_B2C : -1;
+  return -1;
+}
+
+template <int P> hipError_t launch_qp(const DslashArgs& A, bool dag, int threads, int grid, hipStream_t st) {
+  switch (quad_prog(A, dag)) {
+    case QP_HOP: return dag ? launch_q<P, QP_HOP, true>(A, threads, grid, st) : launch_q<P, QP_HOP, false>(A, threads, grid, st);
+    case QP_A1: return launch_q<P, QP_A1, false>(A, threads, grid, st);
+    case QP_A2: return launch_q<P, QP_A2, false>(A, threads, grid, st);
+    case QP_A2C: return launch_q<P, QP_A2C, false>(A, threads, grid, st);
+    case QP_B1: return launch_q<P, QP_B1, true>(A, threads, grid, st);
+    case QP_B2: return launch_q<P, QP_B2, true>(A, threads, grid, st);
+    case QP_B2C: return launch_q<P, QP_B2C, true>(A, threads, grid, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// The launches this kernel takes: the staged hop without the M_phi prologue
+// or the split, 32- and 16-bit storage, L5 a multiple of 4, neighbour offsets
+// that fit 32 bits (fields under 4 GB), and a second chain's totals that fit
+// the stage they overlay (all but L5 = 32 of FP32 and int16).
+bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag, bool pro) {
+  if (!hop || pro || !A.stage || A.split_mask != 0 || prec == F64 || A.g.L5 % 4 != 0 || kSiteTile != 16) return false;
+  if (spinor_field_bytes(prec, A.g.L5, A.g.Vh) >= ((size_t)1 << 32)) return false;
+  const size_t stage = prec == F32 || prec == I16 ? stage_bytes<F32>(16) : stage_bytes<F16>(16);
+  if (totals_bytes(16, A.g.L5) > stage) return false;
+  return quad_prog(A, dag) >= 0;
+}
+
+size_t dslash_quad_lds_bytes(int prec, int CB, int L5) {
+  return prec == F32 || prec == I16 ? lds_bytes<F32>(CB, L5) : lds_bytes<F16>(CB, L5);
+}
+
+hipError_t dslash_quad_launch(const DslashArgs& A, int prec, bool dag, int threads, int grid, hipStream_t st) {
+  switch (prec) {
+    case F32: return launch_qp<F32>(A, dag, threads, grid, st);
+    case F16: return launch_qp<F16>(A, dag, threads, grid, st);
+    case BF16: return launch_qp<BF16>(A, dag, threads, grid, st);
+    case I16: return launch_qp<I16>(A, dag, threads, grid, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace mdwf

@@ -79,6 +79,11 @@ struct DslashArgs {
   // grid; 2 = each XCD's eighth of the site blocks, RHS by RHS inside it
   // (needs nblk % 8 == 0; the launcher falls back to 0 otherwise).
   int rhs_order;
+  // filled by the launcher: y-rows of a band, workgroups per rectangle, Lt / Bt
+  // and the multiply-high magic (0: divide) of division by workgroups per rectangle, Bt, Lz, Lt / Bt, slots,
+  // site blocks, site blocks per XCD
+  int rows, bpp, ntb;
+  uint32_t m_bpp, m_bt, m_lz, m_ntb, m_nslots, m_nblk, m_per;
   int split_mask;          // bit mu: hops across the mu boundary come from halo buffers (skipped here)
   int c1, c2, aux_mode, reduce;
   double coef_y;
@@ -94,6 +99,12 @@ struct DslashArgs {
   char* const* cg_p;
   const CGState* cg_st;
 };
+
+// The quad form of the stencil (dslash_quad.hip): whether it takes a launch,
+// its LDS, and the launch itself (dslash_launch chooses).
+bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag, bool pro);
+size_t dslash_quad_lds_bytes(int prec, int CB, int L5);
+hipError_t dslash_quad_launch(const DslashArgs& A, int prec, bool dag, int threads, int grid, hipStream_t st);
 
 hipError_t dslash_launch(DslashArgs A, int prec, bool hop, bool dag, bool pro, int cb_log2, hipStream_t st);
 // The traversal a launch of CB-site workgroups actually takes (invalid Bt or
@@ -126,10 +137,10 @@ struct DDArgs {
 };
 hipError_t dd_pack(const DDArgs& A, int prec, hipStream_t st);
 hipError_t dd_exterior(const DDArgs& A, int prec, hipStream_t st);
-size_t dslash_lds_bytes(const DslashArgs& A, int prec, int cb_log2, bool hop);
+size_t dslash_lds_bytes(const DslashArgs& A, int prec, int cb_log2, bool hop, bool dag, bool pro);
 int dslash_max_threads(int prec);
 
-// ---- BLAS-1 / reductions (one thread per 4D site, loop over s) ------------
+// ---- BLAS-1 / reductions (one thread per site and slice) -------------------
 struct BlasArgs {
   Geom g;
   char* const* a;   // [nslots]
@@ -166,11 +177,12 @@ hipError_t scalar_cg_alpha(CGState* st_, const double* partials, int n, int nslo
 hipError_t scalar_cg_beta(CGState* st_, const double* partials, int n, int nslots, hipStream_t st);
 
 // ---- layout, precision, sources --------------------------------------------
-// user complex128 full field [s][t][z][y][x][spin][col] -> half-field of parity par (prec p)
-hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* half, int par, int p,
+// user complex128 full field [s][t][z][y][x][spin][col] -> half-fields of
+// precision p (a null table: that parity is not wanted)
+hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int p,
                                int nslots, hipStream_t st);
-// half-field (prec p; nullptr entry in table: zeros) -> user sites of parity par
-hipError_t layout_half_to_user(const Geom& g, const char* const* half, char* const* user, int par, int p,
+// half-fields of precision p (a null entry: zeros) -> user field, both parities
+hipError_t layout_half_to_user(const Geom& g, const char* const* even, const char* const* odd, char* const* user, int p,
                                int nslots, hipStream_t st);
 // user gauge complex128 [t][z][y][x][mu][3][3] (device) -> internal 12-real, prec p
 hipError_t layout_gauge(const Geom& g, const double* user, char* out, int p, hipStream_t st);

@@ -11,45 +11,113 @@ __device__ __forceinline__ int lex_index(const Geom& g, int par, int cb) {
   return ((t * g.Lz + z) * g.Ly + y) * g.Lx + x;
 }
 
-template <int P>
-__global__ __launch_bounds__(256) void k_user_to_half(Geom g, const char* const* user, char* const* half, int par) {
+// ---------------------------------------------------------------------------
+// User fields <-> half-fields.  The 16 sites of a tile of both parities are 32
+// consecutive user sites (cb = lexicographic index / 2), 6 KB per slice, so a
+// workgroup streams whole runs of the user field, 16 bytes per lane, and hands
+// them over in LDS to the lanes that own a (site, slice).  Reading a spinor per
+// lane instead (192 bytes apart) fetched every line several times.  Bound by
+// memory: at 32^3 x 64, L5 = 12, FP32 one parity in takes 814 us (890 with a
+// spinor per lane), both parities out, in one launch, 1107 us (2 x 1097).
+// ---------------------------------------------------------------------------
+constexpr int kRowU = 13;        // 16-byte words per site in LDS: 12 and one of padding
+constexpr int kConvThreads = 128;
+
+// parity bit of x of the site with index cb: its lexicographic index is
+// 2 cb + (bit ^ parity)
+__device__ __forceinline__ int row_bit(const Geom& g, int cb) {
+  int x, y, z, t;
+  site_coords(g, 0, cb, x, y, z, t);
+  return (y + z + t) & 1;
+}
+
+// site and slice of a lane in a wavefront of 16 sites x 4 slices, in the order
+// of the stored units
+__device__ __forceinline__ void conv_lane(int L5, int lane, int& in, int& sq) {
+  const bool q = quad_layout(L5);
+  in = q ? lane >> 2 : lane & 15;
+  sq = q ? lane & 3 : lane >> 4;
+}
+
+// BOTH: half-fields of both parities, 4 slices per workgroup, wavefront p
+// converts parity p.  Otherwise parity par only, 8 slices per workgroup.
+template <int P, bool BOTH>
+__global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const char* const* user, char* const* even,
+                                                               char* const* odd, int par) {
   using R = typename PrecTraits<P>::Real;
-  const int cb = blockIdx.x * 256 + threadIdx.x;
-  const int s = blockIdx.y;
-  const int slot = blockIdx.z;
-  if (cb >= g.Vh) return;
+  constexpr int S = BOTH ? 4 : 8, W = BOTH ? 32 : 16;  // slices, user sites per slice
+  __shared__ __align__(16) v2d row[S * W * kRowU];
+  __shared__ int bit[16];
+  const int tid = threadIdx.x, tile = blockIdx.x, s0 = blockIdx.y * S, slot = blockIdx.z;
   const size_t V4 = (size_t)g.Vh * 2;
-  const int i4 = lex_index(g, par, cb);
-  const double2* u = reinterpret_cast<const double2*>(user[slot]) + ((size_t)s * V4 + i4) * 12;
+  const int ns = min(S, g.L5 - s0), nw = min(W, (int)(V4 - (size_t)tile * 32) / (BOTH ? 1 : 2));
+  if (tid < 16) bit[tid] = row_bit(g, tile * 16 + tid);
+  __syncthreads();
+  const v2d* u = reinterpret_cast<const v2d*>(user[slot]);
+#pragma unroll
+  for (int j = 0; j < S * W * 12 / kConvThreads; ++j) {
+    const int e = tid + j * kConvThreads;
+    const int l = e / 12, k = e - l * 12;  // (slice, site), component
+    const int sl = l / W, i = l % W;
+    if (sl < ns && i < nw) {
+      const size_t site = (size_t)tile * 32 + (BOTH ? i : 2 * i + (bit[i] ^ par));
+      row[l * kRowU + k] = ldg<v2d>(u + ((size_t)(s0 + sl) * V4 + site) * 12 + k);
+    }
+  }
+  __syncthreads();
+  const int wave = tid >> 6;
+  int in, sq;
+  conv_lane(g.L5, tid & 63, in, sq);
+  const int sl = BOTH ? sq : 4 * wave + sq, p = BOTH ? wave : par;
+  const int cb = tile * 16 + in;
+  if (sl >= ns || cb >= g.Vh) return;
+  const v2d* r = row + (sl * W + (BOTH ? 2 * in + (bit[in] ^ p) : in)) * kRowU;
   R v[24];
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
-    const double2 d = u[k];
+    const v2d d = r[k];
     v[2 * k] = (R)d.x;
     v[2 * k + 1] = (R)d.y;
   }
-  SpinorIO<P>::store(half[slot], FieldDesc{g.Vh, g.L5}, cb, s, v);
+  SpinorIO<P>::store((p == 0 ? even : odd)[slot], FieldDesc{g.Vh, g.L5}, cb, s0 + sl, v);
 }
 
+// Both parities of 4 slices per workgroup; a null half-field writes zeros.
 template <int P>
-__global__ __launch_bounds__(256) void k_half_to_user(Geom g, const char* const* half, char* const* user, int par) {
+__global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const char* const* even, const char* const* odd,
+                                                               char* const* user, bool nt) {
   using R = typename PrecTraits<P>::Real;
-  const int cb = blockIdx.x * 256 + threadIdx.x;
-  const int s = blockIdx.y;
-  const int slot = blockIdx.z;
-  if (cb >= g.Vh) return;
+  constexpr int S = 4, W = 32;
+  __shared__ __align__(16) v2d row[S * W * kRowU];
+  const int tid = threadIdx.x, tile = blockIdx.x, s0 = blockIdx.y * S, slot = blockIdx.z;
   const size_t V4 = (size_t)g.Vh * 2;
-  const int i4 = lex_index(g, par, cb);
-  double2* u = reinterpret_cast<double2*>(user[slot]) + ((size_t)s * V4 + i4) * 12;
-  R v[24];
-  if (half[slot] != nullptr) {
-    SpinorIO<P>::load(half[slot], FieldDesc{g.Vh, g.L5}, cb, s, v);
-  } else {
+  const int ns = min(S, g.L5 - s0), nw = min(W, (int)(V4 - (size_t)tile * 32));
+  const int p = tid >> 6;
+  int in, sq;
+  conv_lane(g.L5, tid & 63, in, sq);
+  const int cb = tile * 16 + in;
+  if (sq < ns && cb < g.Vh) {
+    const char* half = (p == 0 ? even : odd)[slot];
+    R v[24];
+    if (half != nullptr) {
+      SpinorIO<P>::load(half, FieldDesc{g.Vh, g.L5}, cb, s0 + sq, v);
+    } else {
 #pragma unroll
-    for (int k = 0; k < 24; ++k) v[k] = 0;
+      for (int k = 0; k < 24; ++k) v[k] = 0;
+    }
+    v2d* r = row + (sq * W + 2 * in + (row_bit(g, cb) ^ p)) * kRowU;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) r[k] = v2d{(double)v[2 * k], (double)v[2 * k + 1]};
   }
+  __syncthreads();
+  v2d* u = reinterpret_cast<v2d*>(user[slot]);
 #pragma unroll
-  for (int k = 0; k < 12; ++k) u[k] = make_double2((double)v[2 * k], (double)v[2 * k + 1]);
+  for (int j = 0; j < S * W * 12 / kConvThreads; ++j) {
+    const int e = tid + j * kConvThreads;
+    const int l = e / 12, k = e - l * 12;
+    const int sl = l / W, i = l % W;
+    if (sl < ns && i < nw) stg<v2d>(u + ((size_t)(s0 + sl) * V4 + (size_t)tile * 32 + i) * 12 + k, row[l * kRowU + k], nt);
+  }
 }
 
 template <int P>
@@ -333,29 +401,43 @@ hipError_t source_physical(const Geom& g, int nrhs, int mask, const char* gauge6
   return hipGetLastError();
 }
 
-hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* half, int par, int p,
-                               int nslots, hipStream_t st) {
-  const dim3 grid((g.Vh + 255) / 256, g.L5, nslots), blk(256);
-  switch (p) {
-    case F64: launch_k(k_user_to_half<F64>, grid, blk, 0, st, g, user, half, par); break;
-    case F32: launch_k(k_user_to_half<F32>, grid, blk, 0, st, g, user, half, par); break;
-    case F16: launch_k(k_user_to_half<F16>, grid, blk, 0, st, g, user, half, par); break;
-    case BF16: launch_k(k_user_to_half<BF16>, grid, blk, 0, st, g, user, half, par); break;
-    case I16: launch_k(k_user_to_half<I16>, grid, blk, 0, st, g, user, half, par); break;
-    default: return hipErrorInvalidValue;
-  }
+template <int P>
+static hipError_t user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int nslots,
+                               hipStream_t st) {
+  const unsigned tiles = (g.Vh + 15) / 16;
+  if (even != nullptr && odd != nullptr)
+    launch_k(k_user_to_half<P, true>, dim3(tiles, (g.L5 + 3) / 4, nslots), dim3(kConvThreads), 0, st, g, user, even,
+             odd, 0);
+  else
+    launch_k(k_user_to_half<P, false>, dim3(tiles, (g.L5 + 7) / 8, nslots), dim3(kConvThreads), 0, st, g, user, even,
+             odd, even != nullptr ? 0 : 1);
   return hipGetLastError();
 }
 
-hipError_t layout_half_to_user(const Geom& g, const char* const* half, char* const* user, int par, int p,
+hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int p,
                                int nslots, hipStream_t st) {
-  const dim3 grid((g.Vh + 255) / 256, g.L5, nslots), blk(256);
+  if (even == nullptr && odd == nullptr) return hipErrorInvalidValue;
   switch (p) {
-    case F64: launch_k(k_half_to_user<F64>, grid, blk, 0, st, g, half, user, par); break;
-    case F32: launch_k(k_half_to_user<F32>, grid, blk, 0, st, g, half, user, par); break;
-    case F16: launch_k(k_half_to_user<F16>, grid, blk, 0, st, g, half, user, par); break;
-    case BF16: launch_k(k_half_to_user<BF16>, grid, blk, 0, st, g, half, user, par); break;
-    case I16: launch_k(k_half_to_user<I16>, grid, blk, 0, st, g, half, user, par); break;
+    case F64: return user_to_half<F64>(g, user, even, odd, nslots, st);
+    case F32: return user_to_half<F32>(g, user, even, odd, nslots, st);
+    case F16: return user_to_half<F16>(g, user, even, odd, nslots, st);
+    case BF16: return user_to_half<BF16>(g, user, even, odd, nslots, st);
+    case I16: return user_to_half<I16>(g, user, even, odd, nslots, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t layout_half_to_user(const Geom& g, const char* const* even, const char* const* odd, char* const* user, int p,
+                               int nslots, hipStream_t st) {
+  const dim3 grid((g.Vh + 15) / 16, (g.L5 + 3) / 4, nslots), blk(kConvThreads);
+  // user fields beyond the 256 MB MALL are streamed past the caches
+  const bool nt = (double)nslots * g.Vh * 2 * g.L5 * 192 > 256e6;
+  switch (p) {
+    case F64: launch_k(k_half_to_user<F64>, grid, blk, 0, st, g, even, odd, user, nt); break;
+    case F32: launch_k(k_half_to_user<F32>, grid, blk, 0, st, g, even, odd, user, nt); break;
+    case F16: launch_k(k_half_to_user<F16>, grid, blk, 0, st, g, even, odd, user, nt); break;
+    case BF16: launch_k(k_half_to_user<BF16>, grid, blk, 0, st, g, even, odd, user, nt); break;
+    case I16: launch_k(k_half_to_user<I16>, grid, blk, 0, st, g, even, odd, user, nt); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -130,10 +130,10 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
   const int cls = prec == MDWF_F64 ? MDWF_PROF_DSLASH_F64 : MDWF_PROF_DSLASH_INNER;
   hipError_t e = hipSuccess;
   hipEvent_t ev;
-  auto conv_in = [&](int par, char* const* half) {
+  auto conv_in = [&](char* const* even, char* const* odd) {
     if (e != hipSuccess) return;
     prof_begin(c, &ev);
-    e = layout_user_to_half(geom, UIN, half, par, prec, nrhs, c->stream);
+    e = layout_user_to_half(geom, UIN, even, odd, prec, nrhs, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   };
   auto run = [&](const Prog& p, char* const* i, char* const* a, char* const* o) {
@@ -145,8 +145,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
   switch (op) {
     case MDWF_OP_D:
     case MDWF_OP_DDAG: {
-      conv_in(0, IE);
-      conv_in(1, IO);
+      conv_in(IE, IO);
       const bool dg = op == MDWF_OP_DDAG;
       run(dg ? prog_Ddag(0) : prog_D(0), IO, IE, OE);
       run(dg ? prog_Ddag(1) : prog_D(1), IE, IO, OO);
@@ -155,20 +154,20 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       break;
     }
     case MDWF_OP_MHAT:
-      conv_in(0, IE);
+      conv_in(IE, nullptr);
       run(prog_A1(), IE, nullptr, T);
       run(prog_A2(false, false), T, IE, OE);
       res_e = OE;
       break;
     case MDWF_OP_MHATDAG:
-      conv_in(0, IE);
+      conv_in(IE, nullptr);
       run(prog_5D(CH_M5INV_DAG), IE, nullptr, OO);
       run(prog_B1(), OO, nullptr, T);
       run(prog_B2(), T, OO, OE);
       res_e = OE;
       break;
     case MDWF_OP_NORMAL:
-      conv_in(0, IE);
+      conv_in(IE, nullptr);
       run(prog_A1(), IE, nullptr, T);
       run(prog_A2(true, false), T, IE, OO);
       run(prog_B1(), OO, nullptr, T);
@@ -176,19 +175,18 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       res_e = OE;
       break;
     case MDWF_OP_HOP_EO:
-      conv_in(1, IO);
+      conv_in(nullptr, IO);
       run(prog_HOP(0, false), IO, nullptr, OE);
       res_e = OE;
       break;
     case MDWF_OP_HOP_OE:
-      conv_in(0, IE);
+      conv_in(IE, nullptr);
       run(prog_HOP(1, false), IE, nullptr, OO);
       res_o = OO;
       break;
     case MDWF_OP_HOP:
     case MDWF_OP_HOPDAG: {
-      conv_in(0, IE);
-      conv_in(1, IO);
+      conv_in(IE, IO);
       const bool dg = op == MDWF_OP_HOPDAG;
       run(prog_HOP(0, dg), IO, nullptr, OE);
       run(prog_HOP(1, dg), IE, nullptr, OO);
@@ -199,8 +197,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
     case MDWF_OP_M5:
     case MDWF_OP_M5INV:
     case MDWF_OP_MPHI: {
-      conv_in(0, IE);
-      conv_in(1, IO);
+      conv_in(IE, IO);
       const int ch = op == MDWF_OP_M5 ? CH_M5 : op == MDWF_OP_M5INV ? CH_M5INV : CH_MPHI;
       run(prog_5D(ch), IE, nullptr, OE);
       run(prog_5D(ch), IO, nullptr, OO);
@@ -209,8 +206,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       break;
     }
     case MDWF_OP_PREP:
-      conv_in(0, IE);
-      conv_in(1, IO);
+      conv_in(IE, IO);
       run(prog_5D(CH_M5INV), IO, nullptr, T);
       run(prog_PRE(0), T, IE, OE);
       res_e = OE;
@@ -220,8 +216,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
   }
   if (e == hipSuccess) {
     prof_begin(c, &ev);
-    e = layout_half_to_user(geom, res_e, UOUT, 0, prec, nrhs, c->stream);
-    if (e == hipSuccess) e = layout_half_to_user(geom, res_o, UOUT, 1, prec, nrhs, c->stream);
+    e = layout_half_to_user(geom, res_e, res_o, UOUT, prec, nrhs, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
   return hip_err(c, e, "mdwf_dslash");
@@ -418,7 +413,7 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   if (phase_ms != nullptr)
     for (auto& x : ev) (void)hipEventCreate(&x);
-  hipError_t e = layout_user_to_half(geom, UIN, IO, 1, prec, nrhs, c->stream);
+  hipError_t e = layout_user_to_half(geom, UIN, nullptr, IO, prec, nrhs, c->stream);
   if (e == hipSuccess && ev[0]) e = hipEventRecord(ev[0], c->stream);
   if (e == hipSuccess && split_mask != 0) e = dd_pack(D, prec, c->stream);
   if (e == hipSuccess && ev[1]) e = hipEventRecord(ev[1], c->stream);
@@ -430,10 +425,7 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
   if (e == hipSuccess && ev[2]) e = hipEventRecord(ev[2], c->stream);
   if (e == hipSuccess && split_mask != 0) e = dd_exterior(D, prec, c->stream);
   if (e == hipSuccess && ev[3]) e = hipEventRecord(ev[3], c->stream);
-  if (e == hipSuccess) {
-    e = layout_half_to_user(geom, OE, UOUT, 0, prec, nrhs, c->stream);
-    if (e == hipSuccess) e = layout_half_to_user(geom, NUL, UOUT, 1, prec, nrhs, c->stream);
-  }
+  if (e == hipSuccess) e = layout_half_to_user(geom, OE, NUL, UOUT, prec, nrhs, c->stream);
   if (phase_ms != nullptr) {
     if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
     for (int k = 0; k < 3; ++k) {

@@ -166,17 +166,18 @@ struct One {
     if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
-    e = layout_user_to_half(geom, U, H, par, F64, 1, c->stream);
+    e = layout_user_to_half(geom, U, par == 0 ? H : nullptr, par == 0 ? nullptr : H, F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
-  void to_user(const void* half, void* user, int par) {
+  void to_user(const void* even, const void* odd, void* user) {
     if (e != hipSuccess) return;
-    char* const* H = tab(half);
+    char* const* E = tab(even);
+    char* const* O = tab(odd);
     char* const* U = tab(user);
     if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
-    e = layout_half_to_user(geom, H, U, par, F64, 1, c->stream);
+    e = layout_half_to_user(geom, E, O, U, F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
   // out = ca * in + cb * out (precisions pin -> pout)
@@ -261,8 +262,7 @@ static mdwf_status finalize(mdwf_ctx* c, mdwf_job* j, int r) {
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
   o.to_half(eta, T.t1, 1);
   o.prog(prog_PRE(1), xh, T.t1, T.t2);  // psi_o = M5^-1 (eta_o + 1/2 H_oe M_phi psi_e)
-  o.to_user(xh, psi, 0);
-  o.to_user(T.t2, psi, 1);
+  o.to_user(xh, T.t2, psi);
   o.prog(prog_D(0), T.t2, xh, T.t3);    // (D psi)_e
   o.to_half(eta, T.t1, 0);
   if (o.e != hipSuccess) return hip_err(c, o.e, "finalize");
