@@ -43,103 +43,146 @@ __device__ __forceinline__ bool holds_site(const Geom& g, int unit, int at) {
   return ((g.Vh - 1) & ~15) + in < g.Vh;
 }
 
-// p = r + beta p, and pt = M_phi p from the new p: (M_phi p)_s = b5 p_s +
-// c5 (P5 p)_s, P5 taking spins 0,1 from slice s - 1 and spins 2,3 from slice
-// s + 1, the wall hop carrying -mq.  pt is the input of the first stencil
-// launch of the next iteration, which then needs no fifth-dimension prologue
-// on its eight neighbours.  One thread per site and slice, a workgroup holds
-// whole columns, and the neighbouring slices' halves pass through LDS (both
+// A workgroup's threads over whole fifth-dimension columns: `tiles` 16-site
+// tiles, one thread per site and slice in the order of the stored units.
+struct ColumnThread {
+  int s, in, tl;  // slice, site in the tile, tile of the workgroup
+  bool valid;
+  Place at;
+};
+__device__ __forceinline__ ColumnThread column_thread(const Geom& g, int tiles) {
+  const int ul = threadIdx.x >> 4, at = threadIdx.x & 15;
+  ColumnThread t;
+  t.tl = ul / g.L5;
+  const int u = ul - t.tl * g.L5;
+  const int tile = blockIdx.x * tiles + t.tl;
+  place_site(u, at, g.L5, t.in, t.s);
+  t.valid = tile * 16 + t.in < g.Vh;
+  t.at = Place{(size_t)tile * g.L5 + u, at};
+  return t;
+}
+
+// out = M_phi v on the workgroup's columns: (M_phi v)_s = b5 v_s + c5 (P5 v)_s,
+// P5 taking spins 0,1 from slice s - 1 and spins 2,3 from slice s + 1, the wall
+// hop carrying -mq.  The neighbouring slices' halves pass through LDS (both
 // halves at once in FP32; FP64 takes them one after the other).
+template <class R> constexpr bool kPhiBoth = sizeof(R) == 4;
+template <class R> constexpr int kPhiRow = kPhiBoth<R> ? 24 : 12;
+template <class R> constexpr int kPhiSlice = 16 * kPhiRow<R> + 4;  // the 4 spread a quad's rows over the banks
+template <class R>
+__device__ __forceinline__ void column_mphi(void* smem, const ColumnThread& t, int L5, const Coef5& c, const R v[24],
+                                            R out[24]) {
+  const R b5 = (R)c.b5, c5 = (R)c.c5, wall = (R)(-c.c5 * c.mq);
+  const int s = t.s;
+  R* lds = reinterpret_cast<R*>(smem) + (size_t)t.tl * L5 * kPhiSlice<R>;
+  const int up = s == 0 ? L5 - 1 : s - 1, dn = s == L5 - 1 ? 0 : s + 1;
+  const R cu = s == 0 ? wall : c5, cd = s == L5 - 1 ? wall : c5;
+  R* mine = lds + s * kPhiSlice<R> + t.in * kPhiRow<R>;
+  const R* ru = lds + up * kPhiSlice<R> + t.in * kPhiRow<R>;
+  const R* rd = lds + dn * kPhiSlice<R> + t.in * kPhiRow<R> + (kPhiBoth<R> ? 12 : 0);
+#pragma unroll
+  for (int k = 0; k < kPhiRow<R>; ++k) mine[k] = v[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 12; ++k) out[k] = b5 * v[k] + cu * ru[k];
+  if constexpr (!kPhiBoth<R>) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 12; ++k) mine[k] = v[12 + k];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int k = 0; k < 12; ++k) out[12 + k] = b5 * v[12 + k] + cd * rd[k];
+}
+
+// p = r + beta p, and pt = M_phi p from the new p: the input of the first
+// stencil launch of the next iteration, which then needs no fifth-dimension
+// prologue on its eight neighbours.
 template <int PS>
 __global__ __launch_bounds__(512) void k_cg_p(BlasArgs A, int tiles) {
   using RS = typename PrecTraits<PS>::Real;
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr bool kBoth = sizeof(RS) == 4;
-  constexpr int kRow = kBoth ? 24 : 12;
-  const int slot = blockIdx.y;
-  const CGState& S = A.st[slot];
-  if (!S.active) return;
-  const int L5 = A.g.L5;
-  const int ul = threadIdx.x >> 4, at = threadIdx.x & 15;  // unit of the workgroup, place
-  const int tl = ul / L5, u = ul - tl * L5;
-  const int tile = blockIdx.x * tiles + tl;
-  int in, s;
-  place_site(u, at, L5, in, s);
-  const bool valid = tile * 16 + in < A.g.Vh;
-  const FieldDesc f{A.g.Vh, L5};
-  const Place pl{(size_t)tile * L5 + u, at};
-  const RS beta = (RS)S.beta;
-  const Coef5& c = A.coef[slot];
-  const RS b5 = (RS)c.b5, c5 = (RS)c.c5, wall = (RS)(-c.c5 * c.mq);
-  RS cur[24], out[24];
-  if (valid) {
-    RS rv[24];
-    SpinorAt<PS>::load(A.a[slot], f, pl, cur);
-    SpinorAt<PS>::load(A.b[slot], f, pl, rv);
-#pragma unroll
-    for (int k = 0; k < 24; ++k) cur[k] = rv[k] + beta * cur[k];
-    SpinorAt<PS>::store(A.a[slot], f, pl, cur, A.nt_store);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 24; ++k) cur[k] = 0;
-  }
-  constexpr int kSlice = 16 * kRow + 4;  // the 4 spread a quad's rows over the banks
-  RS* lds = reinterpret_cast<RS*>(smem) + (size_t)tl * L5 * kSlice;
-  const int up = s == 0 ? L5 - 1 : s - 1, dn = s == L5 - 1 ? 0 : s + 1;
-  const RS cu = s == 0 ? wall : c5, cd = s == L5 - 1 ? wall : c5;
-  RS* mine = lds + s * kSlice + in * kRow;
-  const RS *ru = lds + up * kSlice + in * kRow, *rd = lds + dn * kSlice + in * kRow + (kBoth ? 12 : 0);
-#pragma unroll
-  for (int k = 0; k < kRow; ++k) mine[k] = cur[k];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 12; ++k) out[k] = b5 * cur[k] + cu * ru[k];
-  if constexpr (!kBoth) {
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 12; ++k) mine[k] = cur[12 + k];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int k = 0; k < 12; ++k) out[12 + k] = b5 * cur[12 + k] + cd * rd[k];
-  if (valid) SpinorAt<PS>::store(A.c[slot], f, pl, out, A.nt_store);
-}
-
-template <int PI, int PO>
-__global__ __launch_bounds__(kBlasThreads) void k_axpby(BlasArgs A) {
-  using RI = typename PrecTraits<PI>::Real;
-  using RO = typename PrecTraits<PO>::Real;
-  using RC = typename PrecTraits<(PI == F64 || PO == F64) ? F64 : F32>::Real;
   const int slot = blockIdx.y;
   if (A.st != nullptr && !A.st[slot].active) return;
+  const RS beta = (RS)(A.st != nullptr ? A.st[slot].beta : A.ca);
+  const bool fresh = A.st == nullptr && A.ca == 0.0;  // p = r
+  const ColumnThread t = column_thread(A.g, tiles);
+  const FieldDesc f{A.g.Vh, A.g.L5};
+  RS cur[24], out[24];
+#pragma unroll
+  for (int k = 0; k < 24; ++k) cur[k] = 0;
+  if (t.valid) {
+    RS rv[24];
+    if (!fresh) SpinorAt<PS>::load(A.a[slot], f, t.at, cur);
+    SpinorAt<PS>::load(A.b[slot], f, t.at, rv);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) cur[k] = rv[k] + beta * cur[k];
+    SpinorAt<PS>::store(A.a[slot], f, t.at, cur, A.nt_store);
+  }
+  column_mphi<RS>(smem, t, A.g.L5, A.coef[slot], cur, out);
+  if (t.valid) SpinorAt<PS>::store(A.c[slot], f, t.at, out, A.nt_store);
+}
+
+// The streaming part of a reliable update in one pass: fold the solution
+// increment into the FP64 solution, and form what the two M^ launches of the
+// residual read (z = eta^ - xh as their xpay term, M_phi xh as their input).
+// Bound by memory: 5 FP64 fields and x read and written.  It replaces a copy,
+// two xpays, a clearing pass and a fifth-dimension pass, and the FP64 M^ of the
+// update needs no M_phi prologue: the FP64 work of a 16^3 x 32 x 12 solve of 12
+// RHS (12 updates each) went from 147 to 97 ms.
+template <int PX, bool HAS_X>
+__global__ __launch_bounds__(512) void k_update(BlasArgs A, int tiles) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int slot = blockIdx.y;
+  const ColumnThread t = column_thread(A.g, tiles);
+  const FieldDesc f{A.g.Vh, A.g.L5};
+  double xh[24], out[24];
+#pragma unroll
+  for (int k = 0; k < 24; ++k) xh[k] = 0;
+  if (t.valid) {
+    SpinorAt<F64>::load(A.b[slot], f, t.at, xh);
+    if constexpr (HAS_X) {
+      typename PrecTraits<PX>::Real x[24];
+      SpinorAt<PX>::load(A.a[slot], f, t.at, x);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) {
+        xh[k] += (double)x[k];
+        x[k] = 0;
+      }
+      SpinorAt<PX>::store(A.a[slot], f, t.at, x, A.nt_store);
+      SpinorAt<F64>::store(A.b[slot], f, t.at, xh, A.nt_store);
+    }
+    SpinorAt<F64>::load(A.c[slot], f, t.at, out);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) out[k] -= xh[k];
+    SpinorAt<F64>::store(A.d[slot], f, t.at, out, A.nt_store);
+  }
+  column_mphi<double>(smem, t, A.g.L5, A.coef[slot], xh, out);
+  if (t.valid) SpinorAt<F64>::store(A.e[slot], f, t.at, out, A.nt_store);
+}
+
+template <int PO>
+__global__ __launch_bounds__(kBlasThreads) void k_round(BlasArgs A) {
+  using RO = typename PrecTraits<PO>::Real;
+  const int slot = blockIdx.y;
   const int idx = blockIdx.x * kBlasThreads + threadIdx.x;
   const int unit = idx >> 4, at = idx & 15;
   const FieldDesc f{A.g.Vh, A.g.L5};
   double loc = 0;
   if (unit < blas_units(A.g) && holds_site(A.g, unit, at)) {
     const Place pl{(size_t)unit, at};
-    const char* in = A.a[slot];
-    char* out = A.b[slot];
-    const RC ca = (RC)A.ca, cbeta = (RC)A.cb;
-    RI iv[24];
+    double iv[24];
     RO ov[24];
-    SpinorAt<PI>::load(in, f, pl, iv);
-    if (A.cb != 0.0) {
-      SpinorAt<PO>::load(out, f, pl, ov);
+    SpinorAt<F64>::load(A.a[slot], f, pl, iv);
 #pragma unroll
-      for (int k = 0; k < 24; ++k) ov[k] = (RO)(ca * (RC)iv[k] + cbeta * (RC)ov[k]);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 24; ++k) ov[k] = (RO)(ca * (RC)iv[k]);
+    for (int k = 0; k < 24; ++k) {
+      ov[k] = (RO)iv[k];
+      loc += iv[k] * iv[k];
     }
-#pragma unroll
-    for (int k = 0; k < 24; ++k) loc += (double)ov[k] * (double)ov[k];
-    SpinorAt<PO>::store(out, f, pl, ov);
+    SpinorAt<PO>::store(A.b[slot], f, pl, ov);
   }
-  if (A.partials != nullptr) {
-    const double t = block_sum_256(loc);
-    if (threadIdx.x == 0) A.partials[(size_t)slot * A.nblk + blockIdx.x] = t;
-  }
+  const double t = block_sum_256(loc);
+  if (threadIdx.x == 0) A.partials[(size_t)slot * A.nblk + blockIdx.x] = t;
 }
 
 template <int P>
@@ -154,7 +197,7 @@ __global__ __launch_bounds__(kBlasThreads) void k_norm_diff(BlasArgs A) {
     const Place pl{(size_t)unit, at};
     R av[24], bv[24];
     SpinorAt<P>::load(A.a[slot], f, pl, av);
-    if (A.b != nullptr) {
+    if (A.b[slot] != nullptr) {
       SpinorAt<P>::load(A.b[slot], f, pl, bv);
 #pragma unroll
       for (int k = 0; k < 24; ++k) av[k] -= bv[k];
@@ -176,13 +219,31 @@ static dim3 blas_grid(BlasArgs& A) {
 }
 
 
+// Workgroups of whole columns: at least 256 threads' worth of 16-site tiles.
+template <class R> struct ColumnLaunch {
+  dim3 grid, block;
+  int tiles;
+  size_t lds;
+  ColumnLaunch(const Geom& g, int nslots) {
+    const int column = 16 * g.L5;
+    tiles = column >= 256 ? 1 : 256 / column;
+    grid = dim3(((g.Vh + 15) / 16 + tiles - 1) / tiles, nslots);
+    block = dim3(tiles * column);
+    lds = (size_t)tiles * g.L5 * kPhiSlice<R> * sizeof(R);
+  }
+};
+
 template <int PS> static hipError_t cg_p_launch(const BlasArgs& A, hipStream_t st) {
-  using RS = typename PrecTraits<PS>::Real;
-  const int column = 16 * A.g.L5;  // threads of one 16-site tile
-  const int tiles = column >= 256 ? 1 : 256 / column;
-  const int ntile = (A.g.Vh + 15) / 16;
-  const size_t lds = (size_t)tiles * A.g.L5 * (16 * (sizeof(RS) == 4 ? 24 : 12) + 4) * sizeof(RS);
-  launch_k(k_cg_p<PS>, dim3((ntile + tiles - 1) / tiles, A.nslots), dim3(tiles * column), lds, st, A, tiles);
+  const ColumnLaunch<typename PrecTraits<PS>::Real> L(A.g, A.nslots);
+  launch_k(k_cg_p<PS>, L.grid, L.block, L.lds, st, A, L.tiles);
+  return hipGetLastError();
+}
+
+hipError_t blas_update(BlasArgs A, int px, hipStream_t st) {
+  const ColumnLaunch<double> L(A.g, A.nslots);
+  if (px < 0) launch_k((k_update<F64, false>), L.grid, L.block, L.lds, st, A, L.tiles);
+  else if (px == F32) launch_k((k_update<F32, true>), L.grid, L.block, L.lds, st, A, L.tiles);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -197,30 +258,18 @@ hipError_t blas_cg_p(BlasArgs A, int ps, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-template <int PI>
-static hipError_t axpby_out(BlasArgs A, int pout, dim3 grid, hipStream_t st) {
+hipError_t blas_round(BlasArgs A, int pout, hipStream_t st) {
+  const dim3 grid = blas_grid(A);
   const dim3 blk(kBlasThreads);
   switch (pout) {
-    case F64: launch_k((k_axpby<PI, F64>), grid, blk, 0, st, A); break;
-    case F32: launch_k((k_axpby<PI, F32>), grid, blk, 0, st, A); break;
-    case F16: launch_k((k_axpby<PI, F16>), grid, blk, 0, st, A); break;
-    case BF16: launch_k((k_axpby<PI, BF16>), grid, blk, 0, st, A); break;
-    case I16: launch_k((k_axpby<PI, I16>), grid, blk, 0, st, A); break;
+    case F64: launch_k(k_round<F64>, grid, blk, 0, st, A); break;
+    case F32: launch_k(k_round<F32>, grid, blk, 0, st, A); break;
+    case F16: launch_k(k_round<F16>, grid, blk, 0, st, A); break;
+    case BF16: launch_k(k_round<BF16>, grid, blk, 0, st, A); break;
+    case I16: launch_k(k_round<I16>, grid, blk, 0, st, A); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-hipError_t blas_axpby(BlasArgs A, int pin, int pout, hipStream_t st) {
-  const dim3 grid = blas_grid(A);
-  switch (pin) {
-    case F64: return axpby_out<F64>(A, pout, grid, st);
-    case F32: return axpby_out<F32>(A, pout, grid, st);
-    case F16: return axpby_out<F16>(A, pout, grid, st);
-    case BF16: return axpby_out<BF16>(A, pout, grid, st);
-    case I16: return axpby_out<I16>(A, pout, grid, st);
-  }
-  return hipErrorInvalidValue;
 }
 
 hipError_t blas_norm_diff(BlasArgs A, int p, hipStream_t st) {

@@ -363,8 +363,8 @@ int streaming_stores(const Geom& g, int prec, int nslots) {
 
 static std::string tune_key(const Geom& g, int prec, const Prog& p, int nslots, int cg) {
   char buf[256];
-  snprintf(buf, sizeof(buf), "dslash5 p%d h%d d%d pr%d c%d.%d a%d r%d u%d s%d L%dx%dx%dx%d L5=%d n%d gfx950",
-           prec, (int)p.hop, (int)p.dag, (int)p.pro, p.c1, p.c2, p.aux, p.reduce, (int)cg,
+  snprintf(buf, sizeof(buf), "dslash5 p%d h%d d%d pr0 c%d.%d a%d r%d u%d s%d L%dx%dx%dx%d L5=%d n%d gfx950",
+           prec, (int)p.hop, (int)p.dag, p.c1, p.c2, p.aux, p.reduce, (int)cg,
            p.hop ? default_stage() : 0, g.Lx, g.Ly, g.Lz, g.Lt, g.L5, nslots);
   std::string k = buf;
   if (p.split != 0) k += " x" + std::to_string(p.split);
@@ -388,8 +388,7 @@ static int default_stage() {
 // candidate gives the same result.
 constexpr int kTravBtShift = 12, kTravYbShift = 16, kRhsOrderShift = 24;
 
-static void candidates(const Geom& g, int prec, DslashArgs A, bool hop, bool dag, bool pro, std::vector<int>& out,
-                       int& dflt) {
+static void candidates(const Geom& g, int prec, DslashArgs A, bool hop, bool dag, std::vector<int>& out, int& dflt) {
   out.clear();
   dflt = -1;
   const int stage = hop ? default_stage() : 0;
@@ -412,7 +411,7 @@ static void candidates(const Geom& g, int prec, DslashArgs A, bool hop, bool dag
     const int CB = 1 << lg;
     if (CB * g.L5 > dslash_max_threads(prec)) break;
     if (CB > 2 * g.Vh && lg > 4) break;
-    const size_t lds = dslash_lds_bytes(A, prec, lg, hop, dag, pro);
+    const size_t lds = dslash_lds_bytes(A, prec, lg, hop, dag);
     if (lds > 160 * 1024) break;
     for (int t : trav) out.push_back(lg | (stage << 8) | t);
   }
@@ -491,7 +490,7 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   }
   std::vector<int> cand;
   int dflt = 4;
-  candidates(geom, prec, A, pr.hop, pr.dag, pr.pro, cand, dflt);
+  candidates(geom, prec, A, pr.hop, pr.dag, cand, dflt);
   if (cand.empty()) return hipErrorInvalidValue;
   int lg = dflt;
   const std::string key = tune_key(geom, prec, pr, nslots, fuse != nullptr ? fuse->mode : 0);
@@ -510,13 +509,13 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
     for (int cl : cand) {
       DslashArgs B = A0;
       apply_candidate(B, cl);
-      hipError_t e = dslash_launch(B, prec, pr.hop, pr.dag, pr.pro, cl & 0xff, c->stream);  // warm-up
+      hipError_t e = dslash_launch(B, prec, pr.hop, pr.dag, cl & 0xff, c->stream);  // warm-up
       if (e != hipSuccess) {
         (void)hipGetLastError();
         continue;
       }
       (void)hipEventRecord(e0, c->stream);
-      for (int r = 0; r < 3; ++r) (void)dslash_launch(B, prec, pr.hop, pr.dag, pr.pro, cl & 0xff, c->stream);
+      for (int r = 0; r < 3; ++r) (void)dslash_launch(B, prec, pr.hop, pr.dag, cl & 0xff, c->stream);
       (void)hipEventRecord(e1, c->stream);
       (void)hipEventSynchronize(e1);
       float ms = 0;
@@ -535,7 +534,7 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   hipEvent_t ev;
   prof_begin(c, &ev);
   apply_candidate(A, lg);
-  hipError_t e = dslash_launch(A, prec, pr.hop, pr.dag, pr.pro, lg & 0xff, c->stream);
+  hipError_t e = dslash_launch(A, prec, pr.hop, pr.dag, lg & 0xff, c->stream);
   prof_end(c, cls, prog_bytes(geom, prec, pr, nslots, fuse != nullptr ? fuse->mode : 0), ev);
   return e;
 }

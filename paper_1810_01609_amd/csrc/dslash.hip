@@ -160,38 +160,9 @@ __device__ __forceinline__ void stage_fill(const DslashArgs& A, Stage<typename P
   }
 }
 
-// load_bidiag (dag = 0) for 16-bit storage, with the three sites' scales
-// divided by their maximum m, which is returned: the combination stays O(1)
-// whatever the field's magnitude, so it can be rounded back to 16 bits.
-template <int P>
-__device__ __forceinline__ float load_bidiag_norm(const char* base, const FieldDesc& f, int cb, int s, int L5, float a,
-                                                  float b, float mq, float v[24]) {
-  int s_up = s - 1, s_dn = s + 1;
-  float b_up = b, b_dn = b;
-  if (s_up < 0) { s_up = L5 - 1; b_up = -b * mq; }
-  if (s_dn >= L5) { s_dn = 0; b_dn = -b * mq; }
-  using IO = SpinorIO<P>;
-  const float c0 = IO::scale(base, f, cb, s), cu = IO::scale(base, f, cb, s_up), cd = IO::scale(base, f, cb, s_dn);
-  const float m = fmaxf(c0, fmaxf(cu, cd));
-  const float im = m >= kMinNormalF32 ? 1.0f / m : 0.f;  // stored scales are 0 or normal
-#pragma unroll
-  for (int g = 0; g < 3; ++g) IO::group(base, f, cb, s, g, a * c0 * im, v + 8 * g);
-  float t[16];
-  IO::group(base, f, cb, s_up, 0, b_up * cu * im, t);
-  IO::group(base, f, cb, s_up, 1, b_up * cu * im, t + 8);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) v[k] += t[k];
-  IO::group(base, f, cb, s_dn, 1, b_dn * cd * im, t);
-  IO::group(base, f, cb, s_dn, 2, b_dn * cd * im, t + 8);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) v[12 + k] += t[4 + k];
-  return m;
-}
-
-template <int P, bool DAG, bool PRO, int MU, bool SPLIT>
-__device__ __forceinline__ void hop_dir_packed(const DslashArgs& A, const FieldDesc& f, const char* in, int s,
-                                               const Coef5& c, Cplx<float> acc[4][3], Stage<float> st, int CB,
-                                               int cbl) {
+template <int P, bool DAG, int MU, bool SPLIT>
+__device__ __forceinline__ void hop_dir_packed(const FieldDesc& f, const char* in, int s, Cplx<float> acc[4][3],
+                                               Stage<float> st, int CB, int cbl) {
   using K = Packed<P>;
   using T2 = typename K::T2;
   constexpr int SF = DAG ? +1 : -1;
@@ -205,27 +176,13 @@ __device__ __forceinline__ void hop_dir_packed(const DslashArgs& A, const FieldD
     }
     T2 h[2][3];
     float sc;
-    if constexpr (PRO) {
-      float v[24];
-      sc = load_bidiag_norm<P>(in, f, nb, s, A.g.L5, (float)c.b5, (float)c.c5, (float)c.mq, v);
-      Cplx<float> pf[4][3], hf[2][3];
+    uint32_t q[12];
+    SpinorIO<P>::load_packed(in, f, nb, s, q, sc);
+    T2 psi[4][3];
 #pragma unroll
-      for (int k = 0; k < 12; ++k) pf[k / 3][k % 3] = {v[2 * k], v[2 * k + 1]};
-      if (fb == 0) project<MU, SF>(pf, hf);
-      else project<MU, SB>(pf, hf);
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) h[k][a] = K::make(hf[k][a].re, hf[k][a].im);
-    } else {
-      uint32_t q[12];
-      SpinorIO<P>::load_packed(in, f, nb, s, q, sc);
-      T2 psi[4][3];
-#pragma unroll
-      for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = __builtin_bit_cast(T2, q[k]);
-      if (fb == 0) project<MU, SF>(psi, h);
-      else project<MU, SB>(psi, h);
-    }
+    for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = __builtin_bit_cast(T2, q[k]);
+    if (fb == 0) project<MU, SF>(psi, h);
+    else project<MU, SB>(psi, h);
     Cplx<float> w[2][3];
     colour_mul_packed<P>(lnk, MU + 4 * fb, CB, cbl, h, w);
     if (fb == 0) accumulate_scaled<MU, SF>(acc, w, sc);
@@ -234,9 +191,9 @@ __device__ __forceinline__ void hop_dir_packed(const DslashArgs& A, const FieldD
   }
 }
 
-template <int P, bool DAG, bool PRO, bool STAGE, int MU, bool SPLIT>
+template <int P, bool DAG, bool STAGE, int MU, bool SPLIT>
 __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldDesc& f, const char* in, int cb, int s,
-                                        const int X[4], const Coef5& c, Cplx<typename PrecTraits<P>::Real> acc[4][3],
+                                        const int X[4], Cplx<typename PrecTraits<P>::Real> acc[4][3],
                                         Stage<typename PrecTraits<P>::Real> st, int CB, int cbl) {
   using R = typename PrecTraits<P>::Real;
   const Geom& g = A.g;
@@ -274,7 +231,7 @@ __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldD
     // product unscaled; the site's scale (and 1/32767) joins in the
     // accumulation, one multiply-add per result instead of one multiply per
     // loaded value
-    constexpr bool kI16Raw = P == I16 && STAGE && !PRO;
+    constexpr bool kI16Raw = P == I16 && STAGE;
     float sc16 = 1.f;
     if constexpr (kI16Raw) {
       uint32_t q[12];
@@ -284,8 +241,7 @@ __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldD
       for (int k = 0; k < 12; ++k)
         psi[k / 3][k % 3] = {(R)(int16_t)(uint16_t)(q[k] & 0xffffu), (R)(int16_t)(uint16_t)(q[k] >> 16)};
     } else {
-      if constexpr (PRO) load_bidiag<P>(in, f, nb, s, g.L5, (R)c.b5, (R)c.c5, (R)c.mq, false, v);
-      else SpinorIO<P>::load(in, f, nb, s, v);
+      SpinorIO<P>::load(in, f, nb, s, v);
 #pragma unroll
       for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = {v[2 * k], v[2 * k + 1]};
     }
@@ -424,15 +380,15 @@ __device__ __forceinline__ void hop_batches(const FieldDesc& f, const char* in, 
 #ifndef MDWF_HOP_BATCH_CGU
 #define MDWF_HOP_BATCH_CGU 0
 #endif
-template <int P, bool PRO, bool CGU> constexpr int kHopBatch =
-    (P == F64 || PRO) ? 0 : CGU ? MDWF_HOP_BATCH_CGU : MDWF_HOP_BATCH;
+template <int P, bool CGU> constexpr int kHopBatch =
+    P == F64 ? 0 : CGU ? MDWF_HOP_BATCH_CGU : MDWF_HOP_BATCH;
 
-template <int P, bool DAG, bool PRO, bool STAGE, int MU, bool SPLIT>
+template <int P, bool DAG, bool STAGE, int MU, bool SPLIT>
 __device__ __forceinline__ void hop_dir(const DslashArgs& A, const FieldDesc& f, const char* in, int cb, int s,
-                                        const int X[4], const Coef5& c, Cplx<typename PrecTraits<P>::Real> acc[4][3],
+                                        const int X[4], Cplx<typename PrecTraits<P>::Real> acc[4][3],
                                         Stage<typename PrecTraits<P>::Real> st, int CB, int cbl) {
-  if constexpr (STAGE && Packed<P>::enabled) hop_dir_packed<P, DAG, PRO, MU, SPLIT>(A, f, in, s, c, acc, st, CB, cbl);
-  else hop_dir_single<P, DAG, PRO, STAGE, MU, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
+  if constexpr (STAGE && Packed<P>::enabled) hop_dir_packed<P, DAG, MU, SPLIT>(f, in, s, acc, st, CB, cbl);
+  else hop_dir_single<P, DAG, STAGE, MU, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
 }
 
 // ---------------------------------------------------------------------------
@@ -593,7 +549,7 @@ template <int P> constexpr int kMaxThreads = P == F64 ? 512 : 1024;
 template <int P> constexpr int kWavesPerEU =
     (P == F16 || P == BF16 || P == I16) ? (MDWF_WAVES_PER_EU > 0 ? MDWF_WAVES_PER_EU : 6) : kMaxThreads<P> / 256;
 
-template <int P, bool HOP, bool DAG, bool PRO, bool STAGE, bool CGU, bool SPLIT>
+template <int P, bool HOP, bool DAG, bool STAGE, bool CGU, bool SPLIT>
 __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<P>))) void dslash5_kernel(
     DslashArgs A) {
   using R = typename PrecTraits<P>::Real;
@@ -644,13 +600,13 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int b = 0; b < 3; ++b) acc[a][b] = {0, 0};
       const char* in = A.in[slot];
-      if constexpr (STAGE && kHopBatch<P, PRO, CGU> > 0) {
-        hop_batches<P, DAG, SPLIT, kHopBatch<P, PRO, CGU>, 0>(f, in, s, acc, st, CB, cbl);
+      if constexpr (STAGE && kHopBatch<P, CGU> > 0) {
+        hop_batches<P, DAG, SPLIT, kHopBatch<P, CGU>, 0>(f, in, s, acc, st, CB, cbl);
       } else {
-        hop_dir<P, DAG, PRO, STAGE, 0, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
-        hop_dir<P, DAG, PRO, STAGE, 1, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
-        hop_dir<P, DAG, PRO, STAGE, 2, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
-        hop_dir<P, DAG, PRO, STAGE, 3, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
+        hop_dir<P, DAG, STAGE, 0, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
+        hop_dir<P, DAG, STAGE, 1, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
+        hop_dir<P, DAG, STAGE, 2, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
+        hop_dir<P, DAG, STAGE, 3, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
       }
 #pragma unroll
       for (int k = 0; k < 12; ++k) {
@@ -743,9 +699,9 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 // launcher
 // ---------------------------------------------------------------------------
-template <int P, bool HOP, bool DAG, bool PRO, bool STAGE, bool CGU = false, bool SPLIT = false>
+template <int P, bool HOP, bool DAG, bool STAGE, bool CGU = false, bool SPLIT = false>
 static hipError_t launch_t(const DslashArgs& A, int threads, size_t smem, int grid, hipStream_t st) {
-  auto k = dslash5_kernel<P, HOP, DAG, PRO, STAGE, CGU, SPLIT>;
+  auto k = dslash5_kernel<P, HOP, DAG, STAGE, CGU, SPLIT>;
   if (smem > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -756,29 +712,28 @@ static hipError_t launch_t(const DslashArgs& A, int threads, size_t smem, int gr
 }
 
 template <int P, bool STAGE>
-static hipError_t launch_s(const DslashArgs& A, bool dag, bool pro, int threads, size_t smem, int grid,
+static hipError_t launch_s(const DslashArgs& A, bool dag, int threads, size_t smem, int grid,
                            hipStream_t st) {
   // the CG update is fused into M^+ only: r (and x) into its second launch
   // (B2), x alone possibly into its first (B1)
   if (dag && (A.cg_update == 1 || A.cg_update == 2))
-    return launch_t<P, true, true, false, STAGE, true>(A, threads, smem, grid, st);
+    return launch_t<P, true, true, STAGE, true>(A, threads, smem, grid, st);
   if (A.cg_update != 0 && !(dag && A.cg_update == 3)) return hipErrorInvalidValue;
-  if (dag) return launch_t<P, true, true, false, STAGE>(A, threads, smem, grid, st);
-  if (pro) return launch_t<P, true, false, true, STAGE>(A, threads, smem, grid, st);
-  return launch_t<P, true, false, false, STAGE>(A, threads, smem, grid, st);
+  if (dag) return launch_t<P, true, true, STAGE>(A, threads, smem, grid, st);
+  return launch_t<P, true, false, STAGE>(A, threads, smem, grid, st);
 }
 
 template <int P>
-static hipError_t launch_p(const DslashArgs& A, bool hop, bool dag, bool pro, int threads, size_t smem, int grid,
+static hipError_t launch_p(const DslashArgs& A, bool hop, bool dag, int threads, size_t smem, int grid,
                            hipStream_t st) {
   if (A.split_mask != 0) {
     // the split interior exists for the plain staged hop only
-    if (!hop || dag || pro || !A.stage || A.cg_update) return hipErrorInvalidValue;
-    return launch_t<P, true, false, false, true, false, true>(A, threads, smem, grid, st);
+    if (!hop || dag || !A.stage || A.cg_update) return hipErrorInvalidValue;
+    return launch_t<P, true, false, true, false, true>(A, threads, smem, grid, st);
   }
-  if (!hop) return A.cg_update ? hipErrorInvalidValue : launch_t<P, false, false, false, false>(A, threads, smem, grid, st);
-  if (A.stage) return launch_s<P, true>(A, dag, pro, threads, smem, grid, st);
-  return launch_s<P, false>(A, dag, pro, threads, smem, grid, st);
+  if (!hop) return A.cg_update ? hipErrorInvalidValue : launch_t<P, false, false, false>(A, threads, smem, grid, st);
+  if (A.stage) return launch_s<P, true>(A, dag, threads, smem, grid, st);
+  return launch_s<P, false>(A, dag, threads, smem, grid, st);
 }
 
 int dslash_max_threads(int prec) { return prec == F64 ? kMaxThreads<F64> : kMaxThreads<F32>; }
@@ -807,8 +762,8 @@ static bool red_overlays(size_t chain, size_t red, size_t stage) {
   return MDWF_RED_OVERLAY && red > 0 && red <= std::max(chain, stage);
 }
 
-size_t dslash_lds_bytes(const DslashArgs& A, int prec, int cb_log2, bool hop, bool dag, bool pro) {
-  if (dslash_quad_ok(A, prec, hop, dag, pro)) return dslash_quad_lds_bytes(prec, 1 << cb_log2, A.g.L5);
+size_t dslash_lds_bytes(const DslashArgs& A, int prec, int cb_log2, bool hop, bool dag) {
+  if (dslash_quad_ok(A, prec, hop, dag)) return dslash_quad_lds_bytes(prec, 1 << cb_log2, A.g.L5);
   size_t chain, red, stage;
   lds_layout(A, prec, cb_log2, hop, chain, red, stage);
   return std::max(chain, stage) + (red_overlays(chain, red, stage) ? 0 : red);
@@ -823,7 +778,7 @@ void clamp_traversal(const Geom& g, int CB, int& bt, int& yb) {
   if (bt < 0 || (bt > 0 && ((g.Lxh * g.Ly) % CB != 0 || g.Lt % bt != 0))) bt = 0;
 }
 
-hipError_t dslash_launch(DslashArgs A, int prec, bool hop, bool dag, bool pro, int cb_log2, hipStream_t st) {
+hipError_t dslash_launch(DslashArgs A, int prec, bool hop, bool dag, int cb_log2, hipStream_t st) {
   const int CB = 1 << cb_log2;
   A.cb_log2 = cb_log2;
   A.nblk = (A.g.Vh + CB - 1) / CB;
@@ -852,13 +807,13 @@ hipError_t dslash_launch(DslashArgs A, int prec, bool hop, bool dag, bool pro, i
   A.m_nslots = div_magic(A.nslots, grid);
   A.m_nblk = div_magic(A.nblk, grid);
   A.m_per = div_magic(A.nblk >> 3, grid);
-  if (dslash_quad_ok(A, prec, hop, dag, pro)) return dslash_quad_launch(A, prec, dag, threads, grid, st);
+  if (dslash_quad_ok(A, prec, hop, dag)) return dslash_quad_launch(A, prec, dag, threads, grid, st);
   switch (prec) {
-    case F64: return launch_p<F64>(A, hop, dag, pro, threads, smem, grid, st);
-    case F32: return launch_p<F32>(A, hop, dag, pro, threads, smem, grid, st);
-    case F16: return launch_p<F16>(A, hop, dag, pro, threads, smem, grid, st);
-    case BF16: return launch_p<BF16>(A, hop, dag, pro, threads, smem, grid, st);
-    case I16: return launch_p<I16>(A, hop, dag, pro, threads, smem, grid, st);
+    case F64: return launch_p<F64>(A, hop, dag, threads, smem, grid, st);
+    case F32: return launch_p<F32>(A, hop, dag, threads, smem, grid, st);
+    case F16: return launch_p<F16>(A, hop, dag, threads, smem, grid, st);
+    case BF16: return launch_p<BF16>(A, hop, dag, threads, smem, grid, st);
+    case I16: return launch_p<I16>(A, hop, dag, threads, smem, grid, st);
   }
   return hipErrorInvalidValue;
 }

@@ -1,6 +1,6 @@
 // The fused stencil for fifth dimensions of a multiple of four slices, 32- and
-// 16-bit storage: the same launches as dslash5_kernel without the M_phi
-// prologue, with the work of a site laid over quads of lanes.
+// 16-bit storage: the hop launches of dslash5_kernel with the work of a site
+// laid over quads of lanes.
 //
 // A wavefront owns 16 consecutive sites x 4 consecutive slices, lane
 // 4 * site + (slice & 3); a site's L5 / 4 wavefronts form one workgroup (times
@@ -531,6 +531,8 @@ enum QuadProg : int {
   QP_B1 = 4,    // M_phi^T M5^-T h
   QP_B2 = 5,    // M5^T aux + coef_y M_phi^T h
   QP_B2C = 6,   // the same into r -= alpha (.) instead of out
+  QP_D = 7,     // M5 aux + coef_y h
+  QP_PRE = 8,   // M5^-1 (aux + coef_y h)
 };
 constexpr bool prog_dag(int p) { return p == QP_B1 || p == QP_B2 || p == QP_B2C; }
 
@@ -619,6 +621,19 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
       v[k] = fmaf(be, aux[k], c5y * v[k]);
     }
     quad_chain<false, true, true>(v, add, Q, 0.f, mq, 1.f, 0.f, 1.f);
+  } else if constexpr (PROG == QP_D || PROG == QP_PRE) {
+    Raw<P> ar{};
+    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(A.aux, slot, A.g, w), tile, L5), oo, os, ar);
+    float aux[24], add[24];
+    unpack<P>(ar, aux);
+    const float al = (float)cf.alpha, be = (float)cf.beta, cy = (float)A.coef_y;
+#pragma unroll
+    for (int k = 0; k < 24; ++k) {
+      add[k] = fmaf(PROG == QP_D ? al : 1.f, aux[k], cy * v[k]);
+      v[k] = PROG == QP_D ? be * aux[k] : add[k];
+    }
+    if constexpr (PROG == QP_D) quad_chain<false, true, false>(v, add, Q, 0.f, mq, 1.f, 0.f, 1.f);
+    else quad_chain<true, false, false>(v, nullptr, Q, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
 
   if constexpr (PROG == QP_B2C) {
@@ -700,6 +715,8 @@ int quad_prog(const DslashArgs& A, bool dag) {
     if (A.c1 == CH_MPHI_M5INV && A.c2 == CH_NONE && A.aux_mode == AUX_NONE && A.coef_y == 1.0) return QP_A1;
     if (A.c1 == CH_M5INV && A.aux_mode == AUX_PLAIN && (A.c2 == CH_NONE || A.c2 == CH_M5INV_DAG))
       return A.c2 == CH_NONE ? QP_A2 : QP_A2C;
+    if (A.c1 == CH_NONE && A.c2 == CH_NONE && A.aux_mode == AUX_M5) return QP_D;
+    if (A.c1 == CH_NONE && A.c2 == CH_M5INV && A.aux_mode == AUX_PLAIN) return QP_PRE;
     return -1;
   }
   if (A.c2 != CH_NONE) return -1;
@@ -719,18 +736,19 @@ template <int P> hipError_t launch_qp(const DslashArgs& A, bool dag, int threads
     case QP_B1: return launch_q<P, QP_B1, true>(A, threads, grid, st);
     case QP_B2: return launch_q<P, QP_B2, true>(A, threads, grid, st);
     case QP_B2C: return launch_q<P, QP_B2C, true>(A, threads, grid, st);
+    case QP_D: return launch_q<P, QP_D, false>(A, threads, grid, st);
+    case QP_PRE: return launch_q<P, QP_PRE, false>(A, threads, grid, st);
   }
   return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// The launches this kernel takes: the staged hop without the M_phi prologue
-// or the split, 32- and 16-bit storage, L5 a multiple of 4, neighbour offsets
+// The launches this kernel takes: the staged hop without the split, 32- and 16-bit storage, L5 a multiple of 4, neighbour offsets
 // that fit 32 bits (fields under 4 GB), and a second chain's totals that fit
 // the stage they overlay (all but L5 = 32 of FP32 and int16).
-bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag, bool pro) {
-  if (!hop || pro || !A.stage || A.split_mask != 0 || prec == F64 || A.g.L5 % 4 != 0 || kSiteTile != 16) return false;
+bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag) {
+  if (!hop || !A.stage || A.split_mask != 0 || prec == F64 || A.g.L5 % 4 != 0 || kSiteTile != 16) return false;
   if (spinor_field_bytes(prec, A.g.L5, A.g.Vh) >= ((size_t)1 << 32)) return false;
   const size_t stage = prec == F32 || prec == I16 ? stage_bytes<F32>(16) : stage_bytes<F16>(16);
   if (totals_bytes(16, A.g.L5) > stage) return false;

@@ -30,7 +30,7 @@ struct ProfRec {
 
 // one fused-operator program (see DslashArgs)
 struct Prog {
-  bool hop, dag, pro;
+  bool hop, dag;
   int c1, c2, aux, reduce;
   double coef;
   int out_par;

@@ -51,7 +51,7 @@ enum AuxMode : int {
   AUX_M5DAG = 3,  // + M5^T aux
 };
 
-// out = c2( coef_y * c1( H (or H^dag) ( M_phi in if PRO ) ) + auxterm )
+// out = c2( coef_y * c1( H (or H^dag) in ) + auxterm )
 // with an optional |.|^2 reduction of the value before c2.
 struct DslashArgs {
   Geom g;
@@ -102,11 +102,11 @@ struct DslashArgs {
 
 // The quad form of the stencil (dslash_quad.hip): whether it takes a launch,
 // its LDS, and the launch itself (dslash_launch chooses).
-bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag, bool pro);
+bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag);
 size_t dslash_quad_lds_bytes(int prec, int CB, int L5);
 hipError_t dslash_quad_launch(const DslashArgs& A, int prec, bool dag, int threads, int grid, hipStream_t st);
 
-hipError_t dslash_launch(DslashArgs A, int prec, bool hop, bool dag, bool pro, int cb_log2, hipStream_t st);
+hipError_t dslash_launch(DslashArgs A, int prec, bool hop, bool dag, int cb_log2, hipStream_t st);
 // The traversal a launch of CB-site workgroups actually takes (invalid Bt or
 // band counts fall back to the linear order / one band).
 void clamp_traversal(const Geom& g, int CB, int& bt, int& yb);
@@ -137,7 +137,7 @@ struct DDArgs {
 };
 hipError_t dd_pack(const DDArgs& A, int prec, hipStream_t st);
 hipError_t dd_exterior(const DDArgs& A, int prec, hipStream_t st);
-size_t dslash_lds_bytes(const DslashArgs& A, int prec, int cb_log2, bool hop, bool dag, bool pro);
+size_t dslash_lds_bytes(const DslashArgs& A, int prec, int cb_log2, bool hop, bool dag);
 int dslash_max_threads(int prec);
 
 // ---- BLAS-1 / reductions (one thread per site and slice) -------------------
@@ -147,22 +147,28 @@ struct BlasArgs {
   char* const* b;
   char* const* c;
   char* const* d;
+  char* const* e;
   CGState* st;      // [nslots] (CG kernels)
   double* partials; // [nslots][nblk]
   int nblk;         // filled by launcher
   int nslots;
-  double ca, cb;    // coefficients for axpby
-  const Coef5* coef; // [nslots] (k_cg_p)
-  int nt_store;      // k_cg_p: streaming stores of p and pt
+  double ca;        // beta of blas_cg_p without a CG state
+  const Coef5* coef; // [nslots] (k_cg_p, k_update)
+  int nt_store;      // streaming stores
 };
 constexpr int kBlasThreads = 256;
 
-// CG: p = r + beta p and pt = M_phi p.   a=p b=r c=pt, coef
+// CG: p = r + beta p and pt = M_phi p.   a=p b=r c=pt, coef.  beta and the
+// active flag come from the CG state; without one (st null) beta is A.ca, and
+// p is not read where that is zero.
 hipError_t blas_cg_p(BlasArgs A, int ps, hipStream_t st);
-// out = ca * in + cb * out  (cb == 0: out is not read).  a=in(pin) b=out(pout);
-// partials of |out|^2 if A.partials.
-hipError_t blas_axpby(BlasArgs A, int pin, int pout, hipStream_t st);
-// partials of |a - b|^2 (b may be nullptr table: |a|^2).  both precision p
+// Start of a reliable update, FP64 xh, eta^, z and pt, x of precision px:
+//   xh += x, x = 0 (without x, px < 0: xh stays), z = eta^ - xh, pt = M_phi xh.
+// a=x b=xh c=eta^ d=z e=pt, coef
+hipError_t blas_update(BlasArgs A, int px, hipStream_t st);
+// b = a rounded from FP64 to precision pout; partials of |a|^2
+hipError_t blas_round(BlasArgs A, int pout, hipStream_t st);
+// partials of |a - b|^2 (|a|^2 where b's entry is null).  both precision p
 hipError_t blas_norm_diff(BlasArgs A, int p, hipStream_t st);
 int blas_nblk(const Geom& g);
 // STREAM-style copy of n16 16-byte vectors (achievable-bandwidth reference)
@@ -181,6 +187,10 @@ hipError_t scalar_cg_beta(CGState* st_, const double* partials, int n, int nslot
 // precision p (a null table: that parity is not wanted)
 hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int p,
                                int nslots, hipStream_t st);
+// one parity of it, as half and phi = M_phi of it (formed from the FP64 user
+// values); half may be a null table
+hipError_t layout_user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
+                                   const Coef5* coef, int par, int p, int nslots, hipStream_t st);
 // half-fields of precision p (a null entry: zeros) -> user field, both parities
 hipError_t layout_half_to_user(const Geom& g, const char* const* even, const char* const* odd, char* const* user, int p,
                                int nslots, hipStream_t st);

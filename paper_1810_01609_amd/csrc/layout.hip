@@ -82,6 +82,65 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const cha
   SpinorIO<P>::store((p == 0 ? even : odd)[slot], FieldDesc{g.Vh, g.L5}, cb, s0 + sl, v);
 }
 
+// One parity with M_phi applied: whole columns of a 16-site tile per
+// workgroup, so that slices s - 1 and s + 1 are in LDS beside s; M_phi is
+// formed in FP64 and rounded once.  The hop then reads a field that already
+// holds M_phi psi; forming it on each of its eight neighbours took a 32^3 x 64
+// x 12 hop from 700 to 1310 us in FP32 and a 24^3 x 64 x 16 one of two RHS from
+// 504 to 1102 us in FP16, against one more half-field written here.
+template <int P>
+__global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* const* user, char* const* half,
+                                                          char* const* phi, const Coef5* coef, int par) {
+  using R = typename PrecTraits<P>::Real;
+  extern __shared__ __align__(16) unsigned char smem[];
+  v2d* row = reinterpret_cast<v2d*>(smem);
+  __shared__ int bit[16];
+  const int tid = threadIdx.x, tile = blockIdx.x, slot = blockIdx.y;
+  const int L5 = g.L5, nthr = 16 * L5;  // = blockDim.x: one thread per site and slice
+  const size_t V4 = (size_t)g.Vh * 2;
+  const int nw = min(16, g.Vh - tile * 16);
+  if (tid < 16) bit[tid] = row_bit(g, tile * 16 + tid);
+  __syncthreads();
+  const v2d* u = reinterpret_cast<const v2d*>(user[slot]);
+#pragma unroll
+  for (int j = 0; j < 12; ++j) {
+    const int e = tid + j * nthr;
+    const int l = e / 12, k = e - l * 12;
+    const int s = l >> 4, i = l & 15;
+    if (i < nw) row[l * kRowU + k] = ldg<v2d>(u + ((size_t)s * V4 + (size_t)tile * 32 + 2 * i + (bit[i] ^ par)) * 12 + k);
+  }
+  __syncthreads();
+  int in, s;
+  place_site(tid >> 4, tid & 15, L5, in, s);
+  if (in >= nw) return;
+  const Place at{(size_t)tile * L5 + (tid >> 4), tid & 15};
+  const FieldDesc f{g.Vh, L5};
+  const v2d* r = row + (s * 16 + in) * kRowU;
+  R v[24];
+  if (half != nullptr) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const v2d d = r[k];
+      v[2 * k] = (R)d.x;
+      v[2 * k + 1] = (R)d.y;
+    }
+    SpinorAt<P>::store(half[slot], f, at, v);
+  }
+  const Coef5& c = coef[slot];
+  const double b5 = c.b5, wall = -c.c5 * c.mq;
+  const double cu = s == 0 ? wall : c.c5, cd = s == L5 - 1 ? wall : c.c5;
+  const v2d* ru = row + ((s == 0 ? L5 - 1 : s - 1) * 16 + in) * kRowU;
+  const v2d* rd = row + ((s == L5 - 1 ? 0 : s + 1) * 16 + in) * kRowU;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const v2d d = r[k], o = k < 6 ? ru[k] : rd[k];
+    const double w = k < 6 ? cu : cd;
+    v[2 * k] = (R)(b5 * d.x + w * o.x);
+    v[2 * k + 1] = (R)(b5 * d.y + w * o.y);
+  }
+  SpinorAt<P>::store(phi[slot], f, at, v);
+}
+
 // Both parities of 4 slices per workgroup; a null half-field writes zeros.
 template <int P>
 __global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const char* const* even, const char* const* odd,
@@ -423,6 +482,32 @@ hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* con
     case F16: return user_to_half<F16>(g, user, even, odd, nslots, st);
     case BF16: return user_to_half<BF16>(g, user, even, odd, nslots, st);
     case I16: return user_to_half<I16>(g, user, even, odd, nslots, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int P>
+static hipError_t user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
+                                   const Coef5* coef, int par, int nslots, hipStream_t st) {
+  const size_t lds = (size_t)16 * g.L5 * kRowU * 16;
+  auto k = k_user_to_half_phi<P>;
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  launch_k(k, dim3((g.Vh + 15) / 16, nslots), dim3(16 * g.L5), lds, st, g, user, half, phi, coef, par);
+  return hipGetLastError();
+}
+
+hipError_t layout_user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
+                                   const Coef5* coef, int par, int p, int nslots, hipStream_t st) {
+  switch (p) {
+    case F64: return user_to_half_phi<F64>(g, user, half, phi, coef, par, nslots, st);
+    case F32: return user_to_half_phi<F32>(g, user, half, phi, coef, par, nslots, st);
+    case F16: return user_to_half_phi<F16>(g, user, half, phi, coef, par, nslots, st);
+    case BF16: return user_to_half_phi<BF16>(g, user, half, phi, coef, par, nslots, st);
+    case I16: return user_to_half_phi<I16>(g, user, half, phi, coef, par, nslots, st);
   }
   return hipErrorInvalidValue;
 }

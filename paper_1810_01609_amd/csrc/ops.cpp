@@ -9,28 +9,28 @@ using namespace mdwf;
 
 namespace mdwf {
 
-// The programs that compose the operators (see DslashArgs):
-//   D_e  = M5 in_e - 1/2 H_eo M_phi in_o            (PRO, aux M5, coef -1/2)
-//   D^+_e = M5^T in_e - 1/2 M_phi^T H^+_eo in_o       (DAG, c1 M_phi^T, aux M5^T)
-//   A1   : t_o = M_phi M5^-1 H_oe M_phi p_e          (PRO, c1 M_phi M5^-1)
-//   A2   : u = p - 1/4 M5^-1 H_eo t_o, out M5^-T u   (c1 M5^-1, aux p, c2 M5^-T)
-//   B1   : w_o = M_phi^T M5^-T H^+_oe v_e            (DAG, c1 M_phi^T M5^-T)
-//   B2   : q = M5^T v - 1/4 M_phi^T H^+_eo w_o       (DAG, c1 M_phi^T, aux M5^T)
-//   PRE  : out = M5^-1 (aux + 1/2 H M_phi in)         (PRO, aux, c2 M5^-1)
+// The programs that compose the operators (see DslashArgs); the inputs of the
+// first three hold M_phi of the field already (the conversion from the user
+// layout, the CG's p-update and the reliable update write it):
+//   D    : M5 aux - 1/2 H in                          (aux M5, coef -1/2)
+//   A1   : t_o = M_phi M5^-1 H_oe in_e                (c1 M_phi M5^-1)
+//   PRE  : out = M5^-1 (aux + 1/2 H in)               (aux, c2 M5^-1)
+//   D^+  : M5^T aux - 1/2 M_phi^T H^+ in              (DAG, c1 M_phi^T, aux M5^T)
+//   A2   : u = aux - 1/4 M5^-1 H_eo t_o, out M5^-T u  (c1 M5^-1, aux, c2 M5^-T)
+//   B1   : w_o = M_phi^T M5^-T H^+_oe v_e             (DAG, c1 M_phi^T M5^-T)
+//   B2   : q = M5^T v - 1/4 M_phi^T H^+_eo w_o        (DAG, c1 M_phi^T, aux M5^T)
 // so that M^ p = A2 without c2, and M^+ y = B2(B1(M5^-T y)).
-Prog prog_D(int par) { return Prog{true, false, true, CH_NONE, CH_NONE, AUX_M5, 0, -0.5, par}; }
-Prog prog_Ddag(int par) { return Prog{true, true, false, CH_MPHI_DAG, CH_NONE, AUX_M5DAG, 0, -0.5, par}; }
-Prog prog_A1() { return Prog{true, false, true, CH_MPHI_M5INV, CH_NONE, AUX_NONE, 0, 1.0, 1}; }
-// A1 on an input that already holds M_phi p (the CG loop's p-update writes it)
-Prog prog_A1_pt() { return Prog{true, false, false, CH_MPHI_M5INV, CH_NONE, AUX_NONE, 0, 1.0, 1}; }
+Prog prog_D(int par) { return Prog{true, false, CH_NONE, CH_NONE, AUX_M5, 0, -0.5, par}; }
+Prog prog_Ddag(int par) { return Prog{true, true, CH_MPHI_DAG, CH_NONE, AUX_M5DAG, 0, -0.5, par}; }
+Prog prog_A1() { return Prog{true, false, CH_MPHI_M5INV, CH_NONE, AUX_NONE, 0, 1.0, 1}; }
 Prog prog_A2(bool with_c2, bool reduce) {
-  return Prog{true, false, false, CH_M5INV, with_c2 ? CH_M5INV_DAG : CH_NONE, AUX_PLAIN, reduce ? 1 : 0, -0.25, 0};
+  return Prog{true, false, CH_M5INV, with_c2 ? CH_M5INV_DAG : CH_NONE, AUX_PLAIN, reduce ? 1 : 0, -0.25, 0};
 }
-Prog prog_B1() { return Prog{true, true, false, CH_MPHIDAG_M5INVDAG, CH_NONE, AUX_NONE, 0, 1.0, 1}; }
-Prog prog_B2() { return Prog{true, true, false, CH_MPHI_DAG, CH_NONE, AUX_M5DAG, 0, -0.25, 0}; }
-Prog prog_PRE(int par) { return Prog{true, false, true, CH_NONE, CH_M5INV, AUX_PLAIN, 0, 0.5, par}; }
-Prog prog_HOP(int par, bool dag) { return Prog{true, dag, false, CH_NONE, CH_NONE, AUX_NONE, 0, 1.0, par}; }
-Prog prog_5D(int chain) { return Prog{false, false, false, chain, CH_NONE, AUX_NONE, 0, 1.0, 0}; }
+Prog prog_B1() { return Prog{true, true, CH_MPHIDAG_M5INVDAG, CH_NONE, AUX_NONE, 0, 1.0, 1}; }
+Prog prog_B2() { return Prog{true, true, CH_MPHI_DAG, CH_NONE, AUX_M5DAG, 0, -0.25, 0}; }
+Prog prog_PRE(int par) { return Prog{true, false, CH_NONE, CH_M5INV, AUX_PLAIN, 0, 0.5, par}; }
+Prog prog_HOP(int par, bool dag) { return Prog{true, dag, CH_NONE, CH_NONE, AUX_NONE, 0, 1.0, par}; }
+Prog prog_5D(int chain) { return Prog{false, false, chain, CH_NONE, AUX_NONE, 0, 1.0, 0}; }
 
 }  // namespace mdwf
 
@@ -136,6 +136,13 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
     e = layout_user_to_half(geom, UIN, even, odd, prec, nrhs, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   };
+  // one parity, and M_phi of it
+  auto conv_phi = [&](int par, char* const* half, char* const* phi) {
+    if (e != hipSuccess) return;
+    prof_begin(c, &ev);
+    e = layout_user_to_half_phi(geom, UIN, half, phi, coef_d, par, prec, nrhs, c->stream);
+    prof_end(c, MDWF_PROF_OTHER, 0, ev);
+  };
   auto run = [&](const Prog& p, char* const* i, char* const* a, char* const* o) {
     if (e != hipSuccess) return;
     e = run_prog(c, g, geom, prec, p, i, a, o, coef_d, nrhs, nullptr, 0, nullptr, 0, cls, i != o && a != o);
@@ -144,18 +151,23 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
   char* const* res_o = NUL;
   switch (op) {
     case MDWF_OP_D:
-    case MDWF_OP_DDAG: {
+      conv_phi(1, IO, T);
+      conv_phi(0, IE, OO);
+      run(prog_D(0), T, IE, OE);
+      run(prog_D(1), OO, IO, T);
+      res_e = OE;
+      res_o = T;
+      break;
+    case MDWF_OP_DDAG:
       conv_in(IE, IO);
-      const bool dg = op == MDWF_OP_DDAG;
-      run(dg ? prog_Ddag(0) : prog_D(0), IO, IE, OE);
-      run(dg ? prog_Ddag(1) : prog_D(1), IE, IO, OO);
+      run(prog_Ddag(0), IO, IE, OE);
+      run(prog_Ddag(1), IE, IO, OO);
       res_e = OE;
       res_o = OO;
       break;
-    }
     case MDWF_OP_MHAT:
-      conv_in(IE, nullptr);
-      run(prog_A1(), IE, nullptr, T);
+      conv_phi(0, IE, IO);
+      run(prog_A1(), IO, nullptr, T);
       run(prog_A2(false, false), T, IE, OE);
       res_e = OE;
       break;
@@ -167,8 +179,8 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       res_e = OE;
       break;
     case MDWF_OP_NORMAL:
-      conv_in(IE, nullptr);
-      run(prog_A1(), IE, nullptr, T);
+      conv_phi(0, IE, IO);
+      run(prog_A1(), IO, nullptr, T);
       run(prog_A2(true, false), T, IE, OO);
       run(prog_B1(), OO, nullptr, T);
       run(prog_B2(), T, OO, OE);
@@ -207,7 +219,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
     }
     case MDWF_OP_PREP:
       conv_in(IE, IO);
-      run(prog_5D(CH_M5INV), IO, nullptr, T);
+      run(prog_5D(CH_MPHI_M5INV), IO, nullptr, T);
       run(prog_PRE(0), T, IE, OE);
       res_e = OE;
       break;

@@ -32,7 +32,6 @@ using namespace mdwf;
 namespace mdwf {
 Prog prog_D(int par);
 Prog prog_A1();
-Prog prog_A1_pt();
 Prog prog_A2(bool with_c2, bool reduce);
 Prog prog_B1();
 Prog prog_B2();
@@ -101,9 +100,18 @@ static mdwf_status get_temps(mdwf_ctx* c, const Geom& g, FP64Temps& T) {
   return MDWF_OK;
 }
 
-// |a - b|^2 (or |a|^2) of single half-fields in FP64, to the host
+// the n sums in red_out, to the host
+static mdwf_status read_sums(mdwf_ctx* c, int n, std::vector<double>& out) {
+  hipError_t e = hipMemcpyAsync(c->red_host, c->red_out.p, n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) return hip_err(c, e, "FP64 norm");
+  out.assign(c->red_host, c->red_host + n);
+  return MDWF_OK;
+}
+
+// |a - b|^2 (|a|^2 where b is null) of half-fields in FP64, to the host
 static mdwf_status norms_f64(mdwf_ctx* c, const Geom& g, const std::vector<const void*>& a,
-                             const std::vector<const void*>* b, std::vector<double>& out) {
+                             const std::vector<const void*>& b, std::vector<double>& out) {
   const int n = (int)a.size();
   BlasArgs B{};
   B.g = g;
@@ -114,19 +122,17 @@ static mdwf_status norms_f64(mdwf_ctx* c, const Geom& g, const std::vector<const
   s = ensure(c, c->red_out, (size_t)n * sizeof(double));
   if (s != MDWF_OK) return s;
   B.a = upload_table(c, a);
-  B.b = b != nullptr ? upload_table(c, *b) : nullptr;
+  B.b = upload_table(c, b);
   B.partials = static_cast<double*>(c->partials_b.p);
   hipEvent_t ev;
   prof_begin(c, &ev);
   hipError_t e = blas_norm_diff(B, F64, c->stream);
   if (e == hipSuccess) e = scalar_reduce(B.partials, nblk, n, static_cast<double*>(c->red_out.p), c->stream);
-  prof_end(c, MDWF_PROF_BLAS, (double)g.Vh * g.L5 * 192.0 * (b ? 2 : 1) * n, ev);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->red_host, c->red_out.p, n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  int fields = n;
+  for (const void* q : b) fields += q != nullptr;
+  prof_end(c, MDWF_PROF_BLAS, (double)g.Vh * g.L5 * 192.0 * fields, ev);
   if (e != hipSuccess) return hip_err(c, e, "FP64 norm");
-  out.assign(c->red_host, c->red_host + n);
-  return MDWF_OK;
+  return read_sums(c, n, out);
 }
 
 // single-slot helpers (tables of one entry)
@@ -143,21 +149,16 @@ struct One {
     if (t == nullptr && e == hipSuccess) e = hipErrorOutOfMemory;
     return t;
   }
+  // an FP64 program on fields of one job
   void prog(const Prog& p, const void* in, const void* aux, void* out) {
-    prog_in(p, F64, in, aux, out, MDWF_PROF_DSLASH_F64);
-  }
-  // a program in precision prec on fields of one job
-  void prog_in(const Prog& p, int prec, const void* in, void* out) {
-    prog_in(p, prec, in, nullptr, out, MDWF_PROF_DSLASH_INNER);
-  }
-  void prog_in(const Prog& p, int prec, const void* in, const void* aux, void* out, int cls) {
     if (e != hipSuccess) return;
     if (coef_d == nullptr) { e = hipErrorInvalidValue; return; }
     char* const* I = tab(in);
     char* const* A = aux ? tab(aux) : nullptr;
     char* const* O = tab(out);
     if (e != hipSuccess) return;
-    e = run_prog(c, g, geom, prec, p, I, A, O, coef_d, 1, nullptr, 0, nullptr, 0, cls, in != out && aux != out);
+    e = run_prog(c, g, geom, F64, p, I, A, O, coef_d, 1, nullptr, 0, nullptr, 0, MDWF_PROF_DSLASH_F64,
+                 in != out && aux != out);
   }
   void to_half(const void* user, void* half, int par) {
     if (e != hipSuccess) return;
@@ -167,6 +168,17 @@ struct One {
     hipEvent_t ev;
     prof_begin(c, &ev);
     e = layout_user_to_half(geom, U, par == 0 ? H : nullptr, par == 0 ? nullptr : H, F64, 1, c->stream);
+    prof_end(c, MDWF_PROF_OTHER, 0, ev);
+  }
+  void to_halves(const void* user, void* even, void* odd) {
+    if (e != hipSuccess) return;
+    char* const* U = tab(user);
+    char* const* E = tab(even);
+    char* const* O = tab(odd);
+    if (e != hipSuccess) return;
+    hipEvent_t ev;
+    prof_begin(c, &ev);
+    e = layout_user_to_half(geom, U, E, O, F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
   void to_user(const void* even, const void* odd, void* user) {
@@ -180,22 +192,66 @@ struct One {
     e = layout_half_to_user(geom, E, O, U, F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
-  // out = ca * in + cb * out (precisions pin -> pout)
-  void axpby(const void* in, int pin, void* out, int pout, double ca, double cb) {
+  // r (precision ps) = lo(rh), and |rh|^2 to the host
+  mdwf_status round_norm(const void* rh, void* r, int ps, double& rr) {
+    const int nblk = blas_nblk(geom);
+    mdwf_status s = ensure(c, c->partials_b, (size_t)nblk * sizeof(double));
+    if (s == MDWF_OK) s = ensure(c, c->red_out, sizeof(double));
+    if (s != MDWF_OK) return s;
+    BlasArgs B = args();
+    B.a = tab(rh);
+    B.b = tab(r);
+    B.partials = static_cast<double*>(c->partials_b.p);
+    if (e != hipSuccess) return hip_err(c, e, "residual");
+    hipEvent_t ev;
+    prof_begin(c, &ev);
+    e = blas_round(B, ps, c->stream);
+    if (e == hipSuccess) e = scalar_reduce(B.partials, nblk, 1, static_cast<double*>(c->red_out.p), c->stream);
+    prof_end(c, MDWF_PROF_BLAS, ne() * (192 + spinor_site_bytes(ps)), ev);
+    if (e != hipSuccess) return hip_err(c, e, "residual");
+    std::vector<double> n;
+    s = read_sums(c, 1, n);
+    rr = n.empty() ? 0.0 : n[0];
+    return s;
+  }
+  // p = r + beta p, pt = M_phi p in precision ps (beta = 0: p = r)
+  void direction(void* p, const void* r, void* pt, int ps, double beta) {
     if (e != hipSuccess) return;
+    BlasArgs B = args();
+    B.a = tab(p);
+    B.b = tab(r);
+    B.c = tab(pt);
+    B.ca = beta;
+    if (e != hipSuccess) return;
+    hipEvent_t ev;
+    prof_begin(c, &ev);
+    e = blas_cg_p(B, ps, c->stream);
+    // with the inner operator's launches, where M_phi p outside the loop is counted
+    prof_end(c, MDWF_PROF_DSLASH_INNER, ne() * spinor_site_bytes(ps) * (beta != 0 ? 4 : 3), ev);
+  }
+  // xh += x, x = 0 (x null: neither), z = eta_hat - xh, pt = M_phi xh
+  void update(void* x, int px, void* xh, const void* eta_hat, void* z, void* pt) {
+    if (e != hipSuccess) return;
+    BlasArgs B = args();
+    if (x != nullptr) B.a = tab(x);
+    B.b = tab(xh);
+    B.c = tab(eta_hat);
+    B.d = tab(z);
+    B.e = tab(pt);
+    if (e != hipSuccess) return;
+    hipEvent_t ev;
+    prof_begin(c, &ev);
+    e = blas_update(B, x != nullptr ? px : -1, c->stream);
+    prof_end(c, MDWF_PROF_BLAS, ne() * (192 * 4 + (x != nullptr ? 192 + 2 * spinor_site_bytes(px) : 0)), ev);
+  }
+  double ne() const { return (double)geom.Vh * geom.L5; }
+  BlasArgs args() const {
     BlasArgs B{};
     B.g = geom;
     B.nslots = 1;
-    B.a = tab(in);
-    B.b = tab(out);
-    if (e != hipSuccess) return;
-    B.ca = ca;
-    B.cb = cb;
-    hipEvent_t ev;
-    prof_begin(c, &ev);
-    e = blas_axpby(B, pin, pout, c->stream);
-    const double ne = (double)geom.Vh * geom.L5;
-    prof_end(c, MDWF_PROF_BLAS, ne * (spinor_site_bytes(pin) + spinor_site_bytes(pout) * (cb != 0 ? 2 : 1)), ev);
+    B.coef = coef_d;
+    B.nt_store = streaming_stores(geom, F64, 1);
+    return B;
   }
   void zero(void* p, size_t bytes) {
     if (e != hipSuccess) return;
@@ -203,15 +259,18 @@ struct One {
   }
 };
 
-// rh (in T.t1) = M^+ (eta^ - M^ xh), with eta^_e kept by the job
-static void true_residual(One& o, const FP64Temps& T, const char* eta_hat, const char* xh) {
-  o.axpby(eta_hat, F64, T.t1, F64, 1.0, 0.0);               // eta^_e
-  o.prog(prog_A1(), xh, nullptr, T.t2);                      // M_phi M5^-1 H_oe M_phi xh
-  o.prog(prog_A2(false, false), T.t2, xh, T.t3);             // M^ xh
-  o.axpby(T.t3, F64, T.t1, F64, -1.0, 1.0);                  // y = eta^ - M^ xh
-  o.prog(prog_5D(CH_M5INV_DAG), T.t1, nullptr, T.t3);        // v = M5^-T y
-  o.prog(prog_B1(), T.t3, nullptr, T.t2);
-  o.prog(prog_B2(), T.t2, T.t3, T.t1);                       // rh = M^+ y
+// rh (in T.t1) = M^+ (eta^ - M^ xh), with eta^_e kept by the job; xh += x and
+// x = 0 first where x is not null.  One streaming pass prepares z = eta^ - xh
+// and M_phi xh; then eta^ - M^ xh = z + 1/4 M5^-1 H t needs no pass of its own,
+// nor does v = M5^-T of it.
+static void true_residual(One& o, const FP64Temps& T, char* x, int px, char* xh, const char* eta_hat) {
+  o.update(x, px, xh, eta_hat, T.t1, T.t2);
+  o.prog(prog_A1(), T.t2, nullptr, T.t3);                    // t = M_phi M5^-1 H_oe M_phi xh
+  Prog a2 = prog_A2(true, false);
+  a2.coef = 0.25;
+  o.prog(a2, T.t3, T.t1, T.t2);                              // v = M5^-T (z + 1/4 M5^-1 H_eo t)
+  o.prog(prog_B1(), T.t2, nullptr, T.t3);
+  o.prog(prog_B2(), T.t3, T.t2, T.t1);                       // rh = M^+ (eta^ - M^ xh)
 }
 
 }  // namespace mdwf
@@ -260,28 +319,31 @@ static mdwf_status finalize(mdwf_ctx* c, mdwf_job* j, int r) {
   const char* eta = j->eta + j->user_bytes * r;
   char* psi = j->psi + j->user_bytes * r;
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
+  char* t4 = j->feh[r];  // eta^_e is not needed any more
+  double res = 0, nrm = 0;
+  // parity by parity: |eta - D psi|^2 and |eta|^2, with D psi in t4
+  auto norms = [&]() -> mdwf_status {
+    if (o.e != hipSuccess) return hip_err(c, o.e, "finalize");
+    std::vector<double> n;
+    const mdwf_status s = norms_f64(c, j->geom, {T.t1, T.t1}, {t4, nullptr}, n);
+    if (s == MDWF_OK) {
+      res += n[0];
+      nrm += n[1];
+    }
+    return s;
+  };
+  o.prog(prog_5D(CH_MPHI), xh, nullptr, T.t3);
   o.to_half(eta, T.t1, 1);
-  o.prog(prog_PRE(1), xh, T.t1, T.t2);  // psi_o = M5^-1 (eta_o + 1/2 H_oe M_phi psi_e)
+  o.prog(prog_PRE(1), T.t3, T.t1, T.t2);  // psi_o = M5^-1 (eta_o + 1/2 H_oe M_phi psi_e)
   o.to_user(xh, T.t2, psi);
-  o.prog(prog_D(0), T.t2, xh, T.t3);    // (D psi)_e
+  o.prog(prog_D(1), T.t3, T.t2, t4);      // (D psi)_o
+  st = norms();
+  if (st != MDWF_OK) return st;
+  o.prog(prog_5D(CH_MPHI), T.t2, nullptr, T.t3);
+  o.prog(prog_D(0), T.t3, xh, t4);        // (D psi)_e
   o.to_half(eta, T.t1, 0);
-  if (o.e != hipSuccess) return hip_err(c, o.e, "finalize");
-  std::vector<double> n1, n2;
-  std::vector<const void*> a{T.t1}, b{T.t3};
-  st = norms_f64(c, j->geom, a, &b, n1);
+  st = norms();
   if (st != MDWF_OK) return st;
-  st = norms_f64(c, j->geom, a, nullptr, n2);
-  if (st != MDWF_OK) return st;
-  double res = n1[0], nrm = n2[0];
-  o.prog(prog_D(1), xh, T.t2, T.t3);    // (D psi)_o
-  o.to_half(eta, T.t1, 1);
-  if (o.e != hipSuccess) return hip_err(c, o.e, "finalize");
-  st = norms_f64(c, j->geom, a, &b, n1);
-  if (st != MDWF_OK) return st;
-  st = norms_f64(c, j->geom, a, nullptr, n2);
-  if (st != MDWF_OK) return st;
-  res += n1[0];
-  nrm += n2[0];
   j->stats[r].rel_res_full = nrm > 0 ? std::sqrt(res / nrm) : 0.0;
   return MDWF_OK;
 }
@@ -296,17 +358,9 @@ static mdwf_status reliable_update(mdwf_ctx* c, mdwf_job* j, int r, double& rr) 
   std::vector<Coef5> cf(1, j->coef);
   o.coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), sizeof(Coef5)));
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
-  if (j->ps != F64) {
-    o.axpby(j->fx[r], j->px, xh, F64, 1.0, 1.0);
-    o.zero(j->fx[r], spinor_field_bytes(j->px, j->geom.L5, j->geom.Vh));
-  }
-  true_residual(o, T, j->feh[r], xh);
-  o.axpby(T.t1, F64, j->fr[r], j->ps, 1.0, 0.0);
+  true_residual(o, T, j->ps != F64 ? j->fx[r] : nullptr, j->px, xh, j->feh[r]);
   if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
-  std::vector<double> n;
-  std::vector<const void*> a{T.t1};
-  st = norms_f64(c, j->geom, a, nullptr, n);
-  rr = n.empty() ? 0.0 : n[0];
+  st = o.round_norm(T.t1, j->fr[r], j->ps, rr);
   j->stats[r].reliable_updates += 1;
   return st;
 }
@@ -408,36 +462,29 @@ extern "C" mdwf_status mdwf_job_begin(mdwf_ctx* c, const mdwf_gauge* g, const md
   for (int r = 0; r < nrhs && st == MDWF_OK; ++r) {
     const char* er = j->eta + ub * r;
     char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
-    // b = M^+ eta^, eta^_e = M5^-1 (eta_e + 1/2 H_eo M_phi M5^-1 eta_o)
-    o.to_half(er, T.t1, 0);
-    o.to_half(er, T.t2, 1);
-    o.prog(prog_5D(CH_M5INV), T.t2, nullptr, T.t2);
-    o.prog(prog_PRE(0), T.t2, T.t1, T.t1);
-    o.axpby(T.t1, F64, j->feh[r], F64, 1.0, 0.0);  // keep eta^_e
-    o.prog(prog_5D(CH_M5INV_DAG), T.t1, nullptr, T.t3);
+    // b = M^+ eta^, eta^_e = M5^-1 (eta_e + 1/2 H_eo M_phi M5^-1 eta_o), kept for the updates
+    o.to_halves(er, T.t1, T.t2);
+    o.prog(prog_5D(CH_MPHI_M5INV), T.t2, nullptr, T.t3);
+    o.prog(prog_PRE(0), T.t3, T.t1, j->feh[r]);
+    o.prog(prog_5D(CH_M5INV_DAG), j->feh[r], nullptr, T.t3);
     o.prog(prog_B1(), T.t3, nullptr, T.t2);
     o.prog(prog_B2(), T.t2, T.t3, T.t1);
     if (o.e != hipSuccess) { st = hip_err(c, o.e, "job setup"); break; }
-    std::vector<double> n;
-    std::vector<const void*> a{T.t1};
-    st = norms_f64(c, geom, a, nullptr, n);
+    double bb = 0, rr = 0;  // r = lo(rh), with rh = b or the guess's residual
+    st = o.round_norm(T.t1, j->fr[r], j->ps, bb);
     if (st != MDWF_OK) break;
-    const double bb = n[0];
-    double rr = bb;
+    rr = bb;
     if (opts->use_initial_guess) {
       o.to_half(j->psi + ub * r, xh, 0);
-      true_residual(o, T, j->feh[r], xh);
+      true_residual(o, T, nullptr, -1, xh, j->feh[r]);
       if (o.e != hipSuccess) { st = hip_err(c, o.e, "job setup"); break; }
-      st = norms_f64(c, geom, a, nullptr, n);
+      st = o.round_norm(T.t1, j->fr[r], j->ps, rr);
       if (st != MDWF_OK) break;
-      rr = n[0];
     } else {
       o.zero(xh, spinor_field_bytes(F64, geom.L5, geom.Vh));
     }
     if (j->ps != F64) o.zero(j->fx[r], spinor_field_bytes(j->px, geom.L5, geom.Vh));
-    o.axpby(T.t1, F64, j->fr[r], j->ps, 1.0, 0.0);      // r = lo(rh)
-    o.axpby(j->fr[r], j->ps, j->fp[r], j->ps, 1.0, 0.0);  // p = r
-    o.prog_in(prog_5D(CH_MPHI), j->ps, j->fp[r], j->fpt[r]);
+    o.direction(j->fp[r], j->fr[r], j->fpt[r], j->ps, 0.0);  // p = r
     if (o.e != hipSuccess) { st = hip_err(c, o.e, "job setup"); break; }
     CGState& s = j->st[r];
     s.active = 1;
@@ -597,7 +644,7 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
     for (int i = 0; i < n; ++i) it0[i] = slots[i].job->st[slots[i].r].iters;
     prof_chunk_begin(c, chunk);
     auto iteration = [&]() -> hipError_t {
-      hipError_t e = run_prog(c, j0->g, geom, ps, prog_A1_pt(), PT, nullptr, T, coef_d, n, act, stride, nullptr, 0,
+      hipError_t e = run_prog(c, j0->g, geom, ps, prog_A1(), PT, nullptr, T, coef_d, n, act, stride, nullptr, 0,
                               MDWF_PROF_DSLASH_INNER, true);
       if (e == hipSuccess)
         e = run_prog(c, j0->g, geom, ps, prog_A2(true, true), T, P, V, coef_d, n, act, stride, pd, ntiles,
@@ -719,8 +766,7 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
           std::vector<Coef5> cf(1, j->coef);
           o.coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), sizeof(Coef5)));
           if (o.coef_d == nullptr) return set_err(c, MDWF_EHIP, "reliable update: coefficient upload");
-          o.axpby(j->fr[r], ps, j->fp[r], ps, 1.0, beta);
-          o.prog_in(prog_5D(CH_MPHI), ps, j->fp[r], j->fpt[r]);
+          o.direction(j->fp[r], j->fr[r], j->fpt[r], ps, beta);
           if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
           s.rho = rr;
           s.rho_new = rr;
