@@ -129,7 +129,7 @@ __global__ __launch_bounds__(512) void k_cg_p(BlasArgs A, int tiles) {
 // Bound by memory: 5 FP64 fields and x read and written.  It replaces a copy,
 // two xpays, a clearing pass and a fifth-dimension pass, and the FP64 M^ of the
 // update needs no M_phi prologue: the FP64 work of a 16^3 x 32 x 12 solve of 12
-// RHS (12 updates each) went from 147 to 97 ms.
+// RHS (12 updates each) went from 151 to 124 ms.
 template <int PX, bool HAS_X>
 __global__ __launch_bounds__(512) void k_update(BlasArgs A, int tiles) {
   extern __shared__ __align__(16) unsigned char smem[];

@@ -187,8 +187,8 @@ hipError_t scalar_cg_beta(CGState* st_, const double* partials, int n, int nslot
 // precision p (a null table: that parity is not wanted)
 hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int p,
                                int nslots, hipStream_t st);
-// one parity of it, as half and phi = M_phi of it (formed from the FP64 user
-// values); half may be a null table
+// one parity of it, as half and phi = M_phi of it (formed before any rounding
+// to 16-bit storage); half may be a null table
 hipError_t layout_user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
                                    const Coef5* coef, int par, int p, int nslots, hipStream_t st);
 // half-fields of precision p (a null entry: zeros) -> user field, both parities

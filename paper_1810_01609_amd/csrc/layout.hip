@@ -1,6 +1,7 @@
 // Layout, precision and source kernels: user complex128 fields <-> internal
 // half-fields, gauge compression to 12 reals, point and Z2 sources.
 #include "dev_common.h"
+#include "hop.h"
 #include "kernels.h"
 
 namespace mdwf {
@@ -17,10 +18,14 @@ __device__ __forceinline__ int lex_index(const Geom& g, int par, int cb) {
 // workgroup streams whole runs of the user field, 16 bytes per lane, and hands
 // them over in LDS to the lanes that own a (site, slice).  Reading a spinor per
 // lane instead (192 bytes apart) fetched every line several times.  Bound by
-// memory: at 32^3 x 64, L5 = 12, FP32 one parity in takes 814 us (890 with a
-// spinor per lane), both parities out, in one launch, 1107 us (2 x 1097).
+// memory latency more than by bandwidth (one burst of loads per wavefront), so
+// the rows in LDS have the field's arithmetic type, not the user's FP64: that
+// holds 24 wavefronts per CU instead of 12.  At 32^3 x 64, L5 = 12, one parity in and
+// both out: FP16 787 + 1029 us (806 + 1739 with FP64 rows; a lane per spinor
+// took 2 x 1220 out on 24^3 x 64 x 16 of two RHS, now 1135), FP32 874 + 1107.
 // ---------------------------------------------------------------------------
-constexpr int kRowU = 13;        // 16-byte words per site in LDS: 12 and one of padding
+constexpr int kRowU = 13;        // complex numbers per site in LDS: 12 and one of padding
+template <class R> using Vec2 = R __attribute__((ext_vector_type(2)));
 constexpr int kConvThreads = 128;
 
 // parity bit of x of the site with index cb: its lexicographic index is
@@ -46,7 +51,7 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const cha
                                                                char* const* odd, int par) {
   using R = typename PrecTraits<P>::Real;
   constexpr int S = BOTH ? 4 : 8, W = BOTH ? 32 : 16;  // slices, user sites per slice
-  __shared__ __align__(16) v2d row[S * W * kRowU];
+  __shared__ __align__(16) Vec2<R> row[S * W * kRowU];
   __shared__ int bit[16];
   const int tid = threadIdx.x, tile = blockIdx.x, s0 = blockIdx.y * S, slot = blockIdx.z;
   const size_t V4 = (size_t)g.Vh * 2;
@@ -61,7 +66,8 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const cha
     const int sl = l / W, i = l % W;
     if (sl < ns && i < nw) {
       const size_t site = (size_t)tile * 32 + (BOTH ? i : 2 * i + (bit[i] ^ par));
-      row[l * kRowU + k] = ldg<v2d>(u + ((size_t)(s0 + sl) * V4 + site) * 12 + k);
+      const v2d d = ldg<v2d>(u + ((size_t)(s0 + sl) * V4 + site) * 12 + k);
+      row[l * kRowU + k] = Vec2<R>{(R)d.x, (R)d.y};
     }
   }
   __syncthreads();
@@ -71,20 +77,20 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const cha
   const int sl = BOTH ? sq : 4 * wave + sq, p = BOTH ? wave : par;
   const int cb = tile * 16 + in;
   if (sl >= ns || cb >= g.Vh) return;
-  const v2d* r = row + (sl * W + (BOTH ? 2 * in + (bit[in] ^ p) : in)) * kRowU;
+  const Vec2<R>* r = row + (sl * W + (BOTH ? 2 * in + (bit[in] ^ p) : in)) * kRowU;
   R v[24];
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
-    const v2d d = r[k];
-    v[2 * k] = (R)d.x;
-    v[2 * k + 1] = (R)d.y;
+    v[2 * k] = r[k].x;
+    v[2 * k + 1] = r[k].y;
   }
   SpinorIO<P>::store((p == 0 ? even : odd)[slot], FieldDesc{g.Vh, g.L5}, cb, s0 + sl, v);
 }
 
 // One parity with M_phi applied: whole columns of a 16-site tile per
 // workgroup, so that slices s - 1 and s + 1 are in LDS beside s; M_phi is
-// formed in FP64 and rounded once.  The hop then reads a field that already
+// formed in the field's arithmetic from values rounded to that arithmetic (not
+// to 16-bit storage).  The hop then reads a field that already
 // holds M_phi psi; forming it on each of its eight neighbours took a 32^3 x 64
 // x 12 hop from 700 to 1310 us in FP32 and a 24^3 x 64 x 16 one of two RHS from
 // 504 to 1102 us in FP16, against one more half-field written here.
@@ -93,7 +99,7 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* co
                                                           char* const* phi, const Coef5* coef, int par) {
   using R = typename PrecTraits<P>::Real;
   extern __shared__ __align__(16) unsigned char smem[];
-  v2d* row = reinterpret_cast<v2d*>(smem);
+  Vec2<R>* row = reinterpret_cast<Vec2<R>*>(smem);
   __shared__ int bit[16];
   const int tid = threadIdx.x, tile = blockIdx.x, slot = blockIdx.y;
   const int L5 = g.L5, nthr = 16 * L5;  // = blockDim.x: one thread per site and slice
@@ -107,7 +113,10 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* co
     const int e = tid + j * nthr;
     const int l = e / 12, k = e - l * 12;
     const int s = l >> 4, i = l & 15;
-    if (i < nw) row[l * kRowU + k] = ldg<v2d>(u + ((size_t)s * V4 + (size_t)tile * 32 + 2 * i + (bit[i] ^ par)) * 12 + k);
+    if (i < nw) {
+      const v2d d = ldg<v2d>(u + ((size_t)s * V4 + (size_t)tile * 32 + 2 * i + (bit[i] ^ par)) * 12 + k);
+      row[l * kRowU + k] = Vec2<R>{(R)d.x, (R)d.y};
+    }
   }
   __syncthreads();
   int in, s;
@@ -115,28 +124,27 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* co
   if (in >= nw) return;
   const Place at{(size_t)tile * L5 + (tid >> 4), tid & 15};
   const FieldDesc f{g.Vh, L5};
-  const v2d* r = row + (s * 16 + in) * kRowU;
+  const Vec2<R>* r = row + (s * 16 + in) * kRowU;
   R v[24];
   if (half != nullptr) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      const v2d d = r[k];
-      v[2 * k] = (R)d.x;
-      v[2 * k + 1] = (R)d.y;
+      v[2 * k] = r[k].x;
+      v[2 * k + 1] = r[k].y;
     }
     SpinorAt<P>::store(half[slot], f, at, v);
   }
   const Coef5& c = coef[slot];
-  const double b5 = c.b5, wall = -c.c5 * c.mq;
-  const double cu = s == 0 ? wall : c.c5, cd = s == L5 - 1 ? wall : c.c5;
-  const v2d* ru = row + ((s == 0 ? L5 - 1 : s - 1) * 16 + in) * kRowU;
-  const v2d* rd = row + ((s == L5 - 1 ? 0 : s + 1) * 16 + in) * kRowU;
+  const R b5 = (R)c.b5, c5 = (R)c.c5, wall = (R)(-c.c5 * c.mq);
+  const R cu = s == 0 ? wall : c5, cd = s == L5 - 1 ? wall : c5;
+  const Vec2<R>* ru = row + ((s == 0 ? L5 - 1 : s - 1) * 16 + in) * kRowU;
+  const Vec2<R>* rd = row + ((s == L5 - 1 ? 0 : s + 1) * 16 + in) * kRowU;
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
-    const v2d d = r[k], o = k < 6 ? ru[k] : rd[k];
-    const double w = k < 6 ? cu : cd;
-    v[2 * k] = (R)(b5 * d.x + w * o.x);
-    v[2 * k + 1] = (R)(b5 * d.y + w * o.y);
+    const Vec2<R> d = r[k], o = k < 6 ? ru[k] : rd[k];
+    const R w = k < 6 ? cu : cd;
+    v[2 * k] = b5 * d.x + w * o.x;
+    v[2 * k + 1] = b5 * d.y + w * o.y;
   }
   SpinorAt<P>::store(phi[slot], f, at, v);
 }
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const cha
                                                                char* const* user, bool nt) {
   using R = typename PrecTraits<P>::Real;
   constexpr int S = 4, W = 32;
-  __shared__ __align__(16) v2d row[S * W * kRowU];
+  __shared__ __align__(16) Vec2<R> row[S * W * kRowU];
   const int tid = threadIdx.x, tile = blockIdx.x, s0 = blockIdx.y * S, slot = blockIdx.z;
   const size_t V4 = (size_t)g.Vh * 2;
   const int ns = min(S, g.L5 - s0), nw = min(W, (int)(V4 - (size_t)tile * 32));
@@ -164,9 +172,9 @@ __global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const cha
 #pragma unroll
       for (int k = 0; k < 24; ++k) v[k] = 0;
     }
-    v2d* r = row + (sq * W + 2 * in + (row_bit(g, cb) ^ p)) * kRowU;
+    Vec2<R>* r = row + (sq * W + 2 * in + (row_bit(g, cb) ^ p)) * kRowU;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) r[k] = v2d{(double)v[2 * k], (double)v[2 * k + 1]};
+    for (int k = 0; k < 12; ++k) r[k] = Vec2<R>{v[2 * k], v[2 * k + 1]};
   }
   __syncthreads();
   v2d* u = reinterpret_cast<v2d*>(user[slot]);
@@ -175,7 +183,10 @@ __global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const cha
     const int e = tid + j * kConvThreads;
     const int l = e / 12, k = e - l * 12;
     const int sl = l / W, i = l % W;
-    if (sl < ns && i < nw) stg<v2d>(u + ((size_t)(s0 + sl) * V4 + (size_t)tile * 32 + i) * 12 + k, row[l * kRowU + k], nt);
+    if (sl < ns && i < nw) {
+      const Vec2<R> d = row[l * kRowU + k];
+      stg<v2d>(u + ((size_t)(s0 + sl) * V4 + (size_t)tile * 32 + i) * 12 + k, v2d{(double)d.x, (double)d.y}, nt);
+    }
   }
 }
 
@@ -328,105 +339,133 @@ static SpinPerm gamma_perm(int mask) {
 // Gamma xi enters on the walls of the opposite chirality to the read-out
 // (P+ on slice 0, P- on slice L5-1) and is multiplied by the 4D factor
 // (1 - c5 D_W) = beta + (c5/2) H, beta = 1 - c5 (4 - M5), that turns the
-// Moebius operator into its Shamir-like form.  One thread per 4D site and
-// right-hand side, FP64, user layouts; every other slice is written zero.
+// Moebius operator into its Shamir-like form.  FP64, user layouts.
+//
+// The zeros of the inner slices are a plain clearing pass at the memory's rate;
+// a workgroup hops 64 sites, wavefront w on wall w (one chirality of Gamma xi,
+// two colour vectors per link), and hands its rows to coalesced stores through
+// LDS.  The hop is bound by L1 accesses (xi is read 192 bytes apart) and by
+// latency at three wavefronts per SIMD.  Twelve sources on 16^3 x 32, L5 = 12:
+// 510 + 647 us (3233 with one thread per site that wrote its 12 slices 192 bytes
+// at a time and kept both walls in scratch memory; the writes alone take 615 us
+// at the copy kernel's rate).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double2 times_i_pow(double2 x, int ph) {
-  switch (ph & 3) {
-    case 0: return x;
-    case 1: return make_double2(-x.y, x.x);
-    case 2: return make_double2(-x.x, -x.y);
-    default: return make_double2(x.y, -x.x);
-  }
+// i^ph x, without branches
+__device__ __forceinline__ Cplx<double> times_i_pow(v2d x, int ph) {
+  const double re = (ph & 1) ? x.y : x.x, im = (ph & 1) ? x.x : x.y;
+  const uint64_t fr = (uint64_t)((ph ^ (ph >> 1)) & 1) << 63, fi = (uint64_t)((ph >> 1) & 1) << 63;
+  return {__builtin_bit_cast(double, __builtin_bit_cast(uint64_t, re) ^ fr),
+          __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, im) ^ fi)};
 }
 
-struct GammaTab {
-  int col[4][4];  // row a of g_mu has its entry i^ph[mu][a] in column col[mu][a]
-  int ph[4][4];
-};
-
-// P_w Gamma xi at site i4 (w = 0: spins 0,1; w = 1: spins 2,3), 12 complex numbers
-__device__ __forceinline__ void chi_at(const double2* x, size_t i4, const SpinPerm& G, int w, double2 v[12]) {
+// P_w Gamma xi at site i4 (w = 0: spins 0,1; w = 1: spins 2,3)
+template <int W>
+__device__ __forceinline__ void chi_at(const double2* x, size_t i4, const SpinPerm& G, Cplx<double> v[4][3]) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const bool keep = (w == 0) == (a < 2);
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-      v[a * 3 + c] = keep ? times_i_pow(x[i4 * 12 + G.perm[a] * 3 + c], G.phase[a]) : make_double2(0.0, 0.0);
-  }
+    for (int c = 0; c < 3; ++c) {
+      if ((a >= 2) == (W == 1)) v[a][c] = times_i_pow(ldg<v2d>(x + i4 * 12 + G.perm[a] * 3 + c), G.phase[a] & 3);
+      else v[a][c] = {0, 0};
+    }
 }
 
-__global__ __launch_bounds__(128) void k_source_physical(Geom g, SpinPerm G, GammaTab T, const char* gauge,
-                                                         const double2* xi, double2* eta, double beta, double hc) {
-  const size_t V4 = (size_t)g.Vh * 2;
-  const size_t i4 = (size_t)blockIdx.x * 128 + threadIdx.x;
-  const size_t r = blockIdx.y;
-  if (i4 >= V4) return;
-  const double2* x = xi + r * V4 * 12;
+template <int W, int D>
+__device__ __forceinline__ void source_hop(const Geom& g, const SpinPerm& G, const char* gauge, const double2* x,
+                                           const int X[4], int par, int cb, double hc, Cplx<double> acc[4][3]) {
+  constexpr int MU = D / 2, FB = D % 2, SG = FB == 0 ? -1 : +1;  // (1 - g_mu) forward, (1 + g_mu) backward
+  const int Lmu = MU == 0 ? g.Lx : MU == 1 ? g.Ly : MU == 2 ? g.Lz : g.Lt;
+  int Y[4] = {X[0], X[1], X[2], X[3]};
+  Y[MU] = FB == 0 ? (X[MU] + 1 == Lmu ? 0 : X[MU] + 1) : (X[MU] == 0 ? Lmu : X[MU]) - 1;
+  const bool flip = MU == 3 && g.tap && X[3] == (FB == 0 ? g.Lt - 1 : 0);
+  const size_t j4 = (((size_t)Y[3] * g.Lz + Y[2]) * g.Ly + Y[1]) * g.Lx + Y[0];
+  Cplx<double> U[3][3], v[4][3], h[2][3], w[2][3];
+  // forward: U_mu(x) on the site's own parity; backward: U_mu(x - mu)^dag
+  LinkIO<F64>::load(gauge, g.Vh, FB == 0 ? par : 1 - par, MU, FB == 0 ? cb : (int)(j4 >> 1), U);
+  chi_at<W>(x, j4, G, v);
+  project<MU, SG>(v, h);
+  colour_mul<FB == 1>(U, h, w);
+  const double c = flip ? -hc : hc;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) w[k / 3][k % 3] = {c * w[k / 3][k % 3].re, c * w[k / 3][k % 3].im};
+  accumulate<MU, SG>(acc, w);
+  pin_acc(acc);  // one neighbour at a time in registers
+}
+
+template <int W>
+__device__ __forceinline__ void source_site(const Geom& g, const SpinPerm& G, const char* gauge, const double2* x,
+                                            size_t i4, double beta, double hc, Cplx<double> out[12]) {
   int X[4];
   size_t rem = i4;
   X[0] = (int)(rem % g.Lx); rem /= g.Lx;
   X[1] = (int)(rem % g.Ly); rem /= g.Ly;
   X[2] = (int)(rem % g.Lz); rem /= g.Lz;
   X[3] = (int)rem;
-  const int par = (X[0] + X[1] + X[2] + X[3]) & 1;
-  const int cb = (int)(i4 >> 1);
-  const int Ls[4] = {g.Lx, g.Ly, g.Lz, g.Lt};
-  double2 out[2][12], v[12];
-  for (int w = 0; w < 2; ++w) {
-    chi_at(x, i4, G, w, v);
-    for (int k = 0; k < 12; ++k) out[w][k] = make_double2(beta * v[k].x, beta * v[k].y);
-  }
-  for (int mu = 0; mu < 4; ++mu) {
-    for (int fb = 0; fb < 2; ++fb) {
-      int Y[4] = {X[0], X[1], X[2], X[3]};
-      double sg = 1.0;
-      if (fb == 0) {
-        Y[mu] = X[mu] + 1 == Ls[mu] ? 0 : X[mu] + 1;
-        if (mu == 3 && g.tap && X[3] == g.Lt - 1) sg = -1.0;
-      } else {
-        Y[mu] = X[mu] == 0 ? Ls[mu] - 1 : X[mu] - 1;
-        if (mu == 3 && g.tap && X[3] == 0) sg = -1.0;
-      }
-      const size_t j4 = (((size_t)Y[3] * g.Lz + Y[2]) * g.Ly + Y[1]) * g.Lx + Y[0];
-      Cplx<double> U[3][3];
-      // forward: U_mu(x) on the site's own parity; backward: U_mu(x - mu)^dag
-      if (fb == 0) LinkIO<F64>::load(gauge, g.Vh, par, mu, cb, U);
-      else LinkIO<F64>::load(gauge, g.Vh, 1 - par, mu, (int)(j4 >> 1), U);
-      const double s1 = fb == 0 ? -1.0 : 1.0;  // (1 - g_mu) forward, (1 + g_mu) backward
-      for (int w = 0; w < 2; ++w) {
-        chi_at(x, j4, G, w, v);
-        double2 y[12];
-        for (int a = 0; a < 4; ++a)
-          for (int c = 0; c < 3; ++c) {
-            double re = 0, im = 0;
-            for (int b = 0; b < 3; ++b) {
-              const Cplx<double> u = fb == 0 ? U[c][b] : Cplx<double>{U[b][c].re, -U[b][c].im};
-              const double2 z = v[a * 3 + b];
-              re += u.re * z.x - u.im * z.y;
-              im += u.re * z.y + u.im * z.x;
-            }
-            y[a * 3 + c] = make_double2(re, im);
-          }
-        for (int a = 0; a < 4; ++a)
-          for (int c = 0; c < 3; ++c) {
-            const double2 gy = times_i_pow(y[T.col[mu][a] * 3 + c], T.ph[mu][a]);
-            const double zr = y[a * 3 + c].x + s1 * gy.x, zi = y[a * 3 + c].y + s1 * gy.y;
-            out[w][a * 3 + c].x += hc * sg * zr;
-            out[w][a * 3 + c].y += hc * sg * zi;
-          }
-      }
-    }
-  }
+  const int par = (X[0] + X[1] + X[2] + X[3]) & 1, cb = (int)(i4 >> 1);
+  Cplx<double> acc[4][3];
+  chi_at<W>(x, i4, G, acc);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[k / 3][k % 3] = {beta * acc[k / 3][k % 3].re, beta * acc[k / 3][k % 3].im};
+  pin_acc(acc);
+  source_hop<W, 0>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 1>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 2>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 3>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 4>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 5>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 6>(g, G, gauge, x, X, par, cb, hc, acc);
+  source_hop<W, 7>(g, G, gauge, x, X, par, cb, hc, acc);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) out[k] = acc[k / 3][k % 3];
+}
+
+constexpr int kSitesBlock = 64;      // sites of a workgroup
+constexpr int kSourceThreads = 128;  // two wavefronts: its sites on each wall
+
+__global__ __launch_bounds__(kSourceThreads) void k_source_physical(Geom g, SpinPerm G, const char* gauge,
+                                                                    const double2* xi, double2* eta, double beta,
+                                                                    double hc) {
+  __shared__ __align__(16) v2d row[2 * kSitesBlock * kRowU];
+  const size_t V4 = (size_t)g.Vh * 2, r = blockIdx.y;
+  const int tid = threadIdx.x;
   double2* e = eta + r * g.L5 * V4 * 12;
-  for (int s = 0; s < g.L5; ++s) {
-    for (int k = 0; k < 12; ++k) {
-      double2 val = make_double2(0.0, 0.0);
-      if (s == 0) val = out[0][k];
-      if (s == g.L5 - 1) val = make_double2(val.x + out[1][k].x, val.y + out[1][k].y);
-      e[((size_t)s * V4 + i4) * 12 + k] = val;
-    }
+  const size_t site0 = (size_t)blockIdx.x * kSitesBlock;
+  const size_t i4 = site0 + (tid & 63);
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Cplx<double> out[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) out[k] = {0, 0};
+  if (i4 < V4) {
+    const double2* x = xi + r * V4 * 12;
+    if (w == 0) source_site<0>(g, G, gauge, x, i4, beta, hc, out);
+    else source_site<1>(g, G, gauge, x, i4, beta, hc, out);
   }
+  // wall 0 goes to slice 0, wall 1 to slice L5 - 1: one row of LDS per site and
+  // wall, the walls added where they share the slice
+  v2d* mine = row + tid * kRowU;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) mine[k] = v2d{out[k].re, out[k].im};
+  __syncthreads();
+  const int walls = g.L5 == 1 ? 1 : 2;
+#pragma unroll
+  for (int j = 0; j < 2 * kSitesBlock * 12 / kSourceThreads; ++j) {
+    const int el = tid + j * kSourceThreads;
+    const int l = el / 12, k = el - l * 12;  // (wall, site), component
+    const int wl = l >> 6, i = l & 63;
+    if (wl >= walls || site0 + i >= V4) continue;
+    v2d v = row[l * kRowU + k];
+    if (walls == 1) v += row[(kSitesBlock + i) * kRowU + k];
+    stg<v2d>(e + ((size_t)(wl == 0 ? 0 : g.L5 - 1) * V4 + site0 + i) * 12 + k, v);
+  }
+}
+
+// Clears n 16-byte vectors at the same place of every right-hand side.
+__global__ __launch_bounds__(256) void k_clear(uint4* p, size_t n, size_t stride, bool nt) {
+  const size_t first = (size_t)blockIdx.x * 2048 + threadIdx.x;
+  uint4* q = p + blockIdx.y * stride;
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (first + 256 * j < n) stg<v4u>(q + first + 256 * j, v4u{0, 0, 0, 0}, nt);
 }
 
 hipError_t propagator_4d(const Geom& g, int nrhs, const double* psi, double* q, hipStream_t st) {
@@ -447,15 +486,15 @@ hipError_t current_source(const Geom& g, int nrhs, int mask, const double* q, do
 
 hipError_t source_physical(const Geom& g, int nrhs, int mask, const char* gauge64, const double* xi, double* eta,
                            double beta, double hc, hipStream_t st) {
-  GammaTab T;
-  for (int mu = 0; mu < 4; ++mu)
-    for (int a = 0; a < 4; ++a) {
-      T.col[mu][a] = kGammaCol[mu][a];
-      T.ph[mu][a] = kGammaPh[mu][a];
-    }
   const size_t V4 = (size_t)g.Vh * 2;
-  const dim3 grid((unsigned)((V4 + 127) / 128), (unsigned)nrhs), blk(128);
-  launch_k(k_source_physical, grid, blk, 0, st, g, gamma_perm(mask), T, gauge64, reinterpret_cast<const double2*>(xi),
+  if (g.L5 > 2) {  // the inner slices
+    const size_t n = (size_t)(g.L5 - 2) * V4 * 12;
+    const bool nt = (double)nrhs * V4 * g.L5 * 192 > 256e6;  // beyond the MALL: streamed
+    launch_k(k_clear, dim3((unsigned)((n + 2047) / 2048), (unsigned)nrhs), dim3(256), 0, st,
+             reinterpret_cast<uint4*>(eta) + V4 * 12, n, (size_t)g.L5 * V4 * 12, nt);
+  }
+  launch_k(k_source_physical, dim3((unsigned)((V4 + kSitesBlock - 1) / kSitesBlock), (unsigned)nrhs),
+           dim3(kSourceThreads), 0, st, g, gamma_perm(mask), gauge64, reinterpret_cast<const double2*>(xi),
            reinterpret_cast<double2*>(eta), beta, hc);
   return hipGetLastError();
 }
@@ -489,7 +528,7 @@ hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* con
 template <int P>
 static hipError_t user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
                                    const Coef5* coef, int par, int nslots, hipStream_t st) {
-  const size_t lds = (size_t)16 * g.L5 * kRowU * 16;
+  const size_t lds = (size_t)16 * g.L5 * kRowU * 2 * sizeof(typename PrecTraits<P>::Real);
   auto k = k_user_to_half_phi<P>;
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
