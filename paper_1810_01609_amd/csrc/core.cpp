@@ -191,6 +191,27 @@ char* const* upload_table(mdwf_ctx* c, const std::vector<const void*>& ptrs) {
   return static_cast<char* const*>(upload_bytes(c, ptrs.data(), ptrs.size() * sizeof(void*)));
 }
 
+bool make_tables(mdwf_ctx* c, const std::vector<std::vector<const void*>>& ptrs, const std::vector<Coef5>& coefs,
+                 LaunchTables& out) {
+  const size_t n = coefs.size(), tb = n * sizeof(void*);
+  out.tab.clear();
+  if (n == 1) {
+    for (const auto& p : ptrs) out.tab.push_back(PtrTab::single(p[0]));
+    out.coef = CoefTab::single(coefs[0]);
+    return true;
+  }
+  std::vector<char> buf(n * sizeof(Coef5) + ptrs.size() * tb);
+  memcpy(buf.data(), coefs.data(), n * sizeof(Coef5));
+  char* w = buf.data() + n * sizeof(Coef5);
+  for (size_t k = 0; k < ptrs.size(); ++k) memcpy(w + k * tb, ptrs[k].data(), tb);
+  const char* d = static_cast<const char*>(upload_bytes(c, buf.data(), buf.size()));
+  if (d == nullptr) return false;
+  out.coef = CoefTab(reinterpret_cast<const Coef5*>(d));
+  for (size_t k = 0; k < ptrs.size(); ++k)
+    out.tab.push_back(PtrTab(reinterpret_cast<char* const*>(d + n * sizeof(Coef5) + k * tb)));
+  return true;
+}
+
 static hipEvent_t get_event(mdwf_ctx* c) {
   if (!c->events.empty()) {
     hipEvent_t e = c->events.back();
@@ -457,7 +478,7 @@ static double prog_bytes(const Geom& g, int prec, const Prog& p, int nslots, int
 }
 
 hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int prec, const Prog& pr,
-                    char* const* in, char* const* aux, char* const* out, const Coef5* coef_d, int nslots,
+                    const PtrTab& in, const PtrTab& aux, const PtrTab& out, const CoefTab& coef, int nslots,
                     const int* active, int active_stride, double* partials, int ntiles, int cls, bool tunable,
                     const CgFuse* fuse) {
   DslashArgs A{};
@@ -467,7 +488,7 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   A.in = in;
   A.aux = aux;
   A.out = out;
-  A.coef = coef_d;
+  A.coef = coef;
   A.active = active;
   A.active_stride = active_stride;
   A.partials = partials;

@@ -130,6 +130,25 @@ __device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
 }
 __device__ __forceinline__ int fastdiv(int n, uint32_t m) { return m == 0 ? n : (int)__umulhi((uint32_t)n, m); }
 
+// One pointer per right-hand side of a launch: a table in device memory, or
+// the pointer itself where there is only one right-hand side.  That spares a
+// single-RHS launch the upload of its tables (a copy of some 3 us on the
+// stream each) and the kernel a dependent load.
+struct PtrTab {
+  char* const* t = nullptr;
+  char* one = nullptr;
+  PtrTab() = default;
+  __host__ __device__ PtrTab(char* const* table) : t(table) {}
+  static PtrTab single(const void* p) {
+    PtrTab r;
+    r.one = const_cast<char*>(static_cast<const char*>(p));
+    return r;
+  }
+  __device__ __forceinline__ char* operator[](int slot) const { return t != nullptr ? t[slot] : one; }
+  __host__ __device__ bool empty() const { return t == nullptr && one == nullptr; }
+  bool operator!=(const PtrTab& o) const { return t != o.t || one != o.one; }
+};
+
 // 4D coordinates of the site with checkerboard index cb and parity par.
 __device__ __forceinline__ void site_coords(const Geom& g, int par, int cb, int& x, int& y, int& z, int& t) {
   int r = fastdiv(cb, g.mLxh);
@@ -548,6 +567,20 @@ template <> struct LinkIO<I16> : LinkIO16<I16> {};
 // ---------------------------------------------------------------------------
 struct Coef5 {
   double b5, c5, mq, alpha, beta, kappa, inv_alpha, inv_c;
+};
+
+// the coefficients of a launch's right-hand sides, likewise
+struct CoefTab {
+  const Coef5* t = nullptr;
+  Coef5 one{};
+  CoefTab() = default;
+  CoefTab(const Coef5* table) : t(table) {}
+  static CoefTab single(const Coef5& c) {
+    CoefTab r;
+    r.one = c;
+    return r;
+  }
+  __device__ __forceinline__ Coef5 operator[](int slot) const { return t != nullptr ? t[slot] : one; }
 };
 
 // CG scalars of one right-hand side, resident on the device.

@@ -73,7 +73,7 @@ struct Base {
   char* d;
   char* s;
 };
-template <int P> __device__ __forceinline__ Base field_base(char* const* table, int slot, const Geom& g, int w) {
+template <int P> __device__ __forceinline__ Base field_base(const PtrTab& table, int slot, const Geom& g, int w) {
   char* p = uniform_ptr(table[slot]);
   Base b;
   b.d = p + (size_t)w * 4 * kSliceBytes<P>;
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   const bool valid = cb0 + cbl < A.g.Vh;
   const uint32_t lo = q * 16, ls = q * 4;  // the lane's slice
   const uint32_t oo = (lane >> 4) * kSliceBytes<P> + (lane & 15) * 16, os = lane * 4;  // its own site and slice
-  const Coef5& cf = A.coef[slot];
+  const Coef5 cf = A.coef[slot];
   const float mq = (float)cf.mq;
 
   uint32_t* nbr = reinterpret_cast<uint32_t*>(smem + CB * kLinkRow<P> * 4);

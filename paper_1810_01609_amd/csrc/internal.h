@@ -136,21 +136,27 @@ mdwf_status ensure(mdwf_ctx* c, DevBuf& b, size_t n);
 void release(DevBuf& b);
 // upload a pointer table / small array (stream-ordered); returns device address
 char* const* upload_table(mdwf_ctx* c, const std::vector<const void*>& ptrs);
+// `count` pointer tables of n entries each, and n coefficients, in one upload
+// (none for n = 1, where they travel in the launches); false on failure
+struct LaunchTables {
+  std::vector<PtrTab> tab;
+  CoefTab coef;
+};
+bool make_tables(mdwf_ctx* c, const std::vector<std::vector<const void*>>& ptrs, const std::vector<Coef5>& coefs,
+                 LaunchTables& out);
 void* upload_bytes(mdwf_ctx* c, const void* data, size_t n);
 void reset_tables(mdwf_ctx* c);
 
 // CG update fused into a stencil launch (see DslashArgs::cg_update)
 struct CgFuse {
-  char* const* x;
-  char* const* r;
-  char* const* p;
+  PtrTab x, r, p;
   const CGState* st;
   int mode;  // DslashArgs::cg_update
 };
 
 // launches with profiling
 hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geom, int prec, const Prog& pr,
-                    char* const* in, char* const* aux, char* const* out, const Coef5* coef_d, int nslots,
+                    const PtrTab& in, const PtrTab& aux, const PtrTab& out, const CoefTab& coef, int nslots,
                     const int* active, int active_stride, double* partials, int ntiles, int cls, bool tunable,
                     const CgFuse* fuse = nullptr);
 // 1 when a launch over nslots fields of this size should store with

@@ -57,10 +57,10 @@ struct DslashArgs {
   Geom g;
   int out_par;
   const char* gauge;       // gauge field of this precision
-  char* const* in;         // [nslots] input half-fields (parity 1-out_par; out_par if no hop)
-  char* const* aux;        // [nslots] or nullptr
-  char* const* out;        // [nslots]
-  const Coef5* coef;       // [nslots]
+  PtrTab in;               // [nslots] input half-fields (parity 1-out_par; out_par if no hop)
+  PtrTab aux;              // [nslots] or empty
+  PtrTab out;              // [nslots]
+  CoefTab coef;             // [nslots]
   const int* active;       // nullptr or active flag of slot i at active[i*active_stride]
   int active_stride;
   double* partials;        // [nslots][ntiles] (16-site tiles) when reduce
@@ -94,9 +94,9 @@ struct DslashArgs {
   // (checkerboard index, slice) pairs of x and p (fields of the other parity).
   // x is FP64 for an FP64 kernel, FP32 otherwise.
   int cg_update;
-  char* const* cg_x;
-  char* const* cg_r;
-  char* const* cg_p;
+  PtrTab cg_x;
+  PtrTab cg_r;
+  PtrTab cg_p;
   const CGState* cg_st;
 };
 
@@ -143,17 +143,17 @@ int dslash_max_threads(int prec);
 // ---- BLAS-1 / reductions (one thread per site and slice) -------------------
 struct BlasArgs {
   Geom g;
-  char* const* a;   // [nslots]
-  char* const* b;
-  char* const* c;
-  char* const* d;
-  char* const* e;
+  PtrTab a;   // [nslots]
+  PtrTab b;
+  PtrTab c;
+  PtrTab d;
+  PtrTab e;
   CGState* st;      // [nslots] (CG kernels)
   double* partials; // [nslots][nblk]
   int nblk;         // filled by launcher
   int nslots;
   double ca;        // beta of blas_cg_p without a CG state
-  const Coef5* coef; // [nslots] (k_cg_p, k_update)
+  CoefTab coef;    // [nslots] (k_cg_p, k_update)
   int nt_store;      // streaming stores
 };
 constexpr int kBlasThreads = 256;
@@ -184,15 +184,15 @@ hipError_t scalar_cg_beta(CGState* st_, const double* partials, int n, int nslot
 
 // ---- layout, precision, sources --------------------------------------------
 // user complex128 full field [s][t][z][y][x][spin][col] -> half-fields of
-// precision p (a null table: that parity is not wanted)
-hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int p,
+// precision p (an empty table: that parity is not wanted)
+hipError_t layout_user_to_half(const Geom& g, const PtrTab& user, const PtrTab& even, const PtrTab& odd, int p,
                                int nslots, hipStream_t st);
 // one parity of it, as half and phi = M_phi of it (formed before any rounding
-// to 16-bit storage); half may be a null table
-hipError_t layout_user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
-                                   const Coef5* coef, int par, int p, int nslots, hipStream_t st);
+// to 16-bit storage); half may be empty
+hipError_t layout_user_to_half_phi(const Geom& g, const PtrTab& user, const PtrTab& half, const PtrTab& phi,
+                                   const CoefTab& coef, int par, int p, int nslots, hipStream_t st);
 // half-fields of precision p (a null entry: zeros) -> user field, both parities
-hipError_t layout_half_to_user(const Geom& g, const char* const* even, const char* const* odd, char* const* user, int p,
+hipError_t layout_half_to_user(const Geom& g, const PtrTab& even, const PtrTab& odd, const PtrTab& user, int p,
                                int nslots, hipStream_t st);
 // user gauge complex128 [t][z][y][x][mu][3][3] (device) -> internal 12-real, prec p
 hipError_t layout_gauge(const Geom& g, const double* user, char* out, int p, hipStream_t st);

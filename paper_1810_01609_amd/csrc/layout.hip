@@ -47,8 +47,8 @@ __device__ __forceinline__ void conv_lane(int L5, int lane, int& in, int& sq) {
 // BOTH: half-fields of both parities, 4 slices per workgroup, wavefront p
 // converts parity p.  Otherwise parity par only, 8 slices per workgroup.
 template <int P, bool BOTH>
-__global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const char* const* user, char* const* even,
-                                                               char* const* odd, int par) {
+__global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, PtrTab user, PtrTab even, PtrTab odd,
+                                                               int par) {
   using R = typename PrecTraits<P>::Real;
   constexpr int S = BOTH ? 4 : 8, W = BOTH ? 32 : 16;  // slices, user sites per slice
   __shared__ __align__(16) Vec2<R> row[S * W * kRowU];
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const cha
     v[2 * k] = r[k].x;
     v[2 * k + 1] = r[k].y;
   }
-  SpinorIO<P>::store((p == 0 ? even : odd)[slot], FieldDesc{g.Vh, g.L5}, cb, s0 + sl, v);
+  SpinorIO<P>::store(p == 0 ? even[slot] : odd[slot], FieldDesc{g.Vh, g.L5}, cb, s0 + sl, v);
 }
 
 // One parity with M_phi applied: whole columns of a 16-site tile per
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, const cha
 // x 12 hop from 700 to 1310 us in FP32 and a 24^3 x 64 x 16 one of two RHS from
 // 504 to 1102 us in FP16, against one more half-field written here.
 template <int P>
-__global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* const* user, char* const* half,
-                                                          char* const* phi, const Coef5* coef, int par) {
+__global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, PtrTab user, PtrTab half, PtrTab phi,
+                                                          CoefTab coef, int par) {
   using R = typename PrecTraits<P>::Real;
   extern __shared__ __align__(16) unsigned char smem[];
   Vec2<R>* row = reinterpret_cast<Vec2<R>*>(smem);
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* co
   const FieldDesc f{g.Vh, L5};
   const Vec2<R>* r = row + (s * 16 + in) * kRowU;
   R v[24];
-  if (half != nullptr) {
+  if (!half.empty()) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
       v[2 * k] = r[k].x;
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* co
     }
     SpinorAt<P>::store(half[slot], f, at, v);
   }
-  const Coef5& c = coef[slot];
+  const Coef5 c = coef[slot];
   const R b5 = (R)c.b5, c5 = (R)c.c5, wall = (R)(-c.c5 * c.mq);
   const R cu = s == 0 ? wall : c5, cd = s == L5 - 1 ? wall : c5;
   const Vec2<R>* ru = row + ((s == 0 ? L5 - 1 : s - 1) * 16 + in) * kRowU;
@@ -151,8 +151,8 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, const char* co
 
 // Both parities of 4 slices per workgroup; a null half-field writes zeros.
 template <int P>
-__global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const char* const* even, const char* const* odd,
-                                                               char* const* user, bool nt) {
+__global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, PtrTab even, PtrTab odd, PtrTab user,
+                                                               bool nt) {
   using R = typename PrecTraits<P>::Real;
   constexpr int S = 4, W = 32;
   __shared__ __align__(16) Vec2<R> row[S * W * kRowU];
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kConvThreads) void k_half_to_user(Geom g, const cha
   conv_lane(g.L5, tid & 63, in, sq);
   const int cb = tile * 16 + in;
   if (sq < ns && cb < g.Vh) {
-    const char* half = (p == 0 ? even : odd)[slot];
+    const char* half = p == 0 ? even[slot] : odd[slot];
     R v[24];
     if (half != nullptr) {
       SpinorIO<P>::load(half, FieldDesc{g.Vh, g.L5}, cb, s0 + sq, v);
@@ -500,21 +500,21 @@ hipError_t source_physical(const Geom& g, int nrhs, int mask, const char* gauge6
 }
 
 template <int P>
-static hipError_t user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int nslots,
+static hipError_t user_to_half(const Geom& g, const PtrTab& user, const PtrTab& even, const PtrTab& odd, int nslots,
                                hipStream_t st) {
   const unsigned tiles = (g.Vh + 15) / 16;
-  if (even != nullptr && odd != nullptr)
+  if (!even.empty() && !odd.empty())
     launch_k(k_user_to_half<P, true>, dim3(tiles, (g.L5 + 3) / 4, nslots), dim3(kConvThreads), 0, st, g, user, even,
              odd, 0);
   else
     launch_k(k_user_to_half<P, false>, dim3(tiles, (g.L5 + 7) / 8, nslots), dim3(kConvThreads), 0, st, g, user, even,
-             odd, even != nullptr ? 0 : 1);
+             odd, !even.empty() ? 0 : 1);
   return hipGetLastError();
 }
 
-hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* const* even, char* const* odd, int p,
+hipError_t layout_user_to_half(const Geom& g, const PtrTab& user, const PtrTab& even, const PtrTab& odd, int p,
                                int nslots, hipStream_t st) {
-  if (even == nullptr && odd == nullptr) return hipErrorInvalidValue;
+  if (even.empty() && odd.empty()) return hipErrorInvalidValue;
   switch (p) {
     case F64: return user_to_half<F64>(g, user, even, odd, nslots, st);
     case F32: return user_to_half<F32>(g, user, even, odd, nslots, st);
@@ -526,8 +526,8 @@ hipError_t layout_user_to_half(const Geom& g, const char* const* user, char* con
 }
 
 template <int P>
-static hipError_t user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
-                                   const Coef5* coef, int par, int nslots, hipStream_t st) {
+static hipError_t user_to_half_phi(const Geom& g, const PtrTab& user, const PtrTab& half, const PtrTab& phi,
+                                   const CoefTab& coef, int par, int nslots, hipStream_t st) {
   const size_t lds = (size_t)16 * g.L5 * kRowU * 2 * sizeof(typename PrecTraits<P>::Real);
   auto k = k_user_to_half_phi<P>;
   if (lds > 65536) {
@@ -539,8 +539,8 @@ static hipError_t user_to_half_phi(const Geom& g, const char* const* user, char*
   return hipGetLastError();
 }
 
-hipError_t layout_user_to_half_phi(const Geom& g, const char* const* user, char* const* half, char* const* phi,
-                                   const Coef5* coef, int par, int p, int nslots, hipStream_t st) {
+hipError_t layout_user_to_half_phi(const Geom& g, const PtrTab& user, const PtrTab& half, const PtrTab& phi,
+                                   const CoefTab& coef, int par, int p, int nslots, hipStream_t st) {
   switch (p) {
     case F64: return user_to_half_phi<F64>(g, user, half, phi, coef, par, nslots, st);
     case F32: return user_to_half_phi<F32>(g, user, half, phi, coef, par, nslots, st);
@@ -551,7 +551,7 @@ hipError_t layout_user_to_half_phi(const Geom& g, const char* const* user, char*
   return hipErrorInvalidValue;
 }
 
-hipError_t layout_half_to_user(const Geom& g, const char* const* even, const char* const* odd, char* const* user, int p,
+hipError_t layout_half_to_user(const Geom& g, const PtrTab& even, const PtrTab& odd, const PtrTab& user, int p,
                                int nslots, hipStream_t st) {
   const dim3 grid((g.Vh + 15) / 16, (g.L5 + 3) / 4, nslots), blk(kConvThreads);
   // user fields beyond the 256 MB MALL are streamed past the caches

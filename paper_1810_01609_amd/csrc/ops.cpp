@@ -59,15 +59,8 @@ static mdwf_status dslash_check(mdwf_ctx* c, const char* who, const mdwf_gauge* 
 // internal half-fields per RHS (in_e, in_o, out_e, out_o, temporary), a table
 // of null pointers (a zero parity) and the per-RHS coefficients.
 struct DslashTables {
-  char* const* UIN;
-  char* const* UOUT;
-  char* const* IE;
-  char* const* IO;
-  char* const* OE;
-  char* const* OO;
-  char* const* T;
-  char* const* NUL;
-  const Coef5* coef;
+  PtrTab UIN, UOUT, IE, IO, OE, OO, T, NUL;
+  CoefTab coef;
 };
 
 static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geom, int32_t op, int32_t prec,
@@ -88,67 +81,52 @@ extern "C" mdwf_status mdwf_dslash(mdwf_ctx* c, const mdwf_gauge* g, const mdwf_
   st = ensure(c, c->dws, fb * 5 * nrhs);
   if (st != MDWF_OK) return st;
   const Coef5 coef = make_coef(act);
-  std::vector<Coef5> coefs(nrhs, coef);
-  const Coef5* coef_d = static_cast<const Coef5*>(upload_bytes(c, coefs.data(), coefs.size() * sizeof(Coef5)));
-  std::vector<const void*> uin(nrhs), uout(nrhs), ie(nrhs), io(nrhs), oe(nrhs), oo(nrhs), tt(nrhs), nul(nrhs, nullptr);
+  std::vector<std::vector<const void*>> p(8, std::vector<const void*>(nrhs, nullptr));
   char* w = static_cast<char*>(c->dws.p);
   for (int r = 0; r < nrhs; ++r) {
-    uin[r] = ib + ub * r;
-    uout[r] = ob + ub * r;
-    ie[r] = w + fb * (5 * r + 0);
-    io[r] = w + fb * (5 * r + 1);
-    oe[r] = w + fb * (5 * r + 2);
-    oo[r] = w + fb * (5 * r + 3);
-    tt[r] = w + fb * (5 * r + 4);
+    p[0][r] = ib + ub * r;
+    p[1][r] = ob + ub * r;
+    for (int k = 0; k < 5; ++k) p[2 + k][r] = w + fb * (5 * r + k);
   }
-  DslashTables t;
-  t.UIN = upload_table(c, uin);
-  t.UOUT = upload_table(c, uout);
-  t.IE = upload_table(c, ie);
-  t.IO = upload_table(c, io);
-  t.OE = upload_table(c, oe);
-  t.OO = upload_table(c, oo);
-  t.T = upload_table(c, tt);
-  t.NUL = upload_table(c, nul);
-  t.coef = coef_d;
-  if (!t.coef || !t.UIN || !t.UOUT || !t.IE || !t.IO || !t.OE || !t.OO || !t.T || !t.NUL)
+  LaunchTables lt;
+  if (!make_tables(c, p, std::vector<Coef5>(nrhs, coef), lt))
     return set_err(c, MDWF_EHIP, "mdwf_dslash: table upload failed");
+  const DslashTables t{lt.tab[0], lt.tab[1], lt.tab[2], lt.tab[3], lt.tab[4], lt.tab[5], lt.tab[6], lt.tab[7], lt.coef};
   return dslash_body(c, g, geom, op, prec, nrhs, t);
 }
 
 static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geom, int32_t op, int32_t prec,
                                int32_t nrhs, const DslashTables& t) {
-  char* const* UIN = t.UIN;
-  char* const* UOUT = t.UOUT;
-  char* const* IE = t.IE;
-  char* const* IO = t.IO;
-  char* const* OE = t.OE;
-  char* const* OO = t.OO;
-  char* const* T = t.T;
-  char* const* NUL = t.NUL;
-  const Coef5* coef_d = t.coef;
+  const PtrTab& UIN = t.UIN;
+  const PtrTab& UOUT = t.UOUT;
+  const PtrTab& IE = t.IE;
+  const PtrTab& IO = t.IO;
+  const PtrTab& OE = t.OE;
+  const PtrTab& OO = t.OO;
+  const PtrTab& T = t.T;
+  const PtrTab& NUL = t.NUL;
+  const CoefTab& coef = t.coef;
   const int cls = prec == MDWF_F64 ? MDWF_PROF_DSLASH_F64 : MDWF_PROF_DSLASH_INNER;
   hipError_t e = hipSuccess;
   hipEvent_t ev;
-  auto conv_in = [&](char* const* even, char* const* odd) {
+  auto conv_in = [&](const PtrTab& even, const PtrTab& odd) {
     if (e != hipSuccess) return;
     prof_begin(c, &ev);
     e = layout_user_to_half(geom, UIN, even, odd, prec, nrhs, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   };
   // one parity, and M_phi of it
-  auto conv_phi = [&](int par, char* const* half, char* const* phi) {
+  auto conv_phi = [&](int par, const PtrTab& half, const PtrTab& phi) {
     if (e != hipSuccess) return;
     prof_begin(c, &ev);
-    e = layout_user_to_half_phi(geom, UIN, half, phi, coef_d, par, prec, nrhs, c->stream);
+    e = layout_user_to_half_phi(geom, UIN, half, phi, coef, par, prec, nrhs, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   };
-  auto run = [&](const Prog& p, char* const* i, char* const* a, char* const* o) {
+  auto run = [&](const Prog& p, const PtrTab& i, const PtrTab& a, const PtrTab& o) {
     if (e != hipSuccess) return;
-    e = run_prog(c, g, geom, prec, p, i, a, o, coef_d, nrhs, nullptr, 0, nullptr, 0, cls, i != o && a != o);
+    e = run_prog(c, g, geom, prec, p, i, a, o, coef, nrhs, nullptr, 0, nullptr, 0, cls, i != o && a != o);
   };
-  char* const* res_e = NUL;
-  char* const* res_o = NUL;
+  PtrTab res_e = NUL, res_o = NUL;
   switch (op) {
     case MDWF_OP_D:
       conv_phi(1, IO, T);
@@ -167,41 +145,41 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       break;
     case MDWF_OP_MHAT:
       conv_phi(0, IE, IO);
-      run(prog_A1(), IO, nullptr, T);
+      run(prog_A1(), IO, PtrTab(), T);
       run(prog_A2(false, false), T, IE, OE);
       res_e = OE;
       break;
     case MDWF_OP_MHATDAG:
-      conv_in(IE, nullptr);
-      run(prog_5D(CH_M5INV_DAG), IE, nullptr, OO);
-      run(prog_B1(), OO, nullptr, T);
+      conv_in(IE, PtrTab());
+      run(prog_5D(CH_M5INV_DAG), IE, PtrTab(), OO);
+      run(prog_B1(), OO, PtrTab(), T);
       run(prog_B2(), T, OO, OE);
       res_e = OE;
       break;
     case MDWF_OP_NORMAL:
       conv_phi(0, IE, IO);
-      run(prog_A1(), IO, nullptr, T);
+      run(prog_A1(), IO, PtrTab(), T);
       run(prog_A2(true, false), T, IE, OO);
-      run(prog_B1(), OO, nullptr, T);
+      run(prog_B1(), OO, PtrTab(), T);
       run(prog_B2(), T, OO, OE);
       res_e = OE;
       break;
     case MDWF_OP_HOP_EO:
-      conv_in(nullptr, IO);
-      run(prog_HOP(0, false), IO, nullptr, OE);
+      conv_in(PtrTab(), IO);
+      run(prog_HOP(0, false), IO, PtrTab(), OE);
       res_e = OE;
       break;
     case MDWF_OP_HOP_OE:
-      conv_in(IE, nullptr);
-      run(prog_HOP(1, false), IE, nullptr, OO);
+      conv_in(IE, PtrTab());
+      run(prog_HOP(1, false), IE, PtrTab(), OO);
       res_o = OO;
       break;
     case MDWF_OP_HOP:
     case MDWF_OP_HOPDAG: {
       conv_in(IE, IO);
       const bool dg = op == MDWF_OP_HOPDAG;
-      run(prog_HOP(0, dg), IO, nullptr, OE);
-      run(prog_HOP(1, dg), IE, nullptr, OO);
+      run(prog_HOP(0, dg), IO, PtrTab(), OE);
+      run(prog_HOP(1, dg), IE, PtrTab(), OO);
       res_e = OE;
       res_o = OO;
       break;
@@ -211,15 +189,15 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
     case MDWF_OP_MPHI: {
       conv_in(IE, IO);
       const int ch = op == MDWF_OP_M5 ? CH_M5 : op == MDWF_OP_M5INV ? CH_M5INV : CH_MPHI;
-      run(prog_5D(ch), IE, nullptr, OE);
-      run(prog_5D(ch), IO, nullptr, OO);
+      run(prog_5D(ch), IE, PtrTab(), OE);
+      run(prog_5D(ch), IO, PtrTab(), OO);
       res_e = OE;
       res_o = OO;
       break;
     }
     case MDWF_OP_PREP:
       conv_in(IE, IO);
-      run(prog_5D(CH_MPHI_M5INV), IO, nullptr, T);
+      run(prog_5D(CH_MPHI_M5INV), IO, PtrTab(), T);
       run(prog_PRE(0), T, IE, OE);
       res_e = OE;
       break;
@@ -307,32 +285,33 @@ extern "C" mdwf_status mdwf_dslash_noalloc(mdwf_ctx* c, const mdwf_gauge* g, con
   hipError_t e = hipSuccess;
   char* base = static_cast<char*>(scratch_ptr(c->device, e));
   if (base == nullptr) return hip_err(c, e, "mdwf_dslash_noalloc: scratch address");
-  ScratchTables t{};
   const char* ib = static_cast<const char*>(in);
   const char* ob = static_cast<const char*>(out);
   char* w = base + kScratchTableBytes;
   const Coef5 coef = make_coef(act);
-  for (int r = 0; r < nrhs; ++r) {
-    t.ptr[0][r] = ib + ub * r;
-    t.ptr[1][r] = ob + ub * r;
-    for (int k = 0; k < 5; ++k) t.ptr[2 + k][r] = w + fb * (5 * r + k);
-    t.ptr[7][r] = nullptr;
-    t.coef[r] = coef;
-  }
-  launch_k(k_put_tables, dim3(1), dim3(256), 0, c->stream, t, base);
-  e = hipGetLastError();
-  if (e != hipSuccess) return hip_err(c, e, "mdwf_dslash_noalloc: table kernel");
-  char* const* tab = reinterpret_cast<char* const*>(base);
   DslashTables d;
-  d.UIN = tab + 0 * kScratchMaxRhs;
-  d.UOUT = tab + 1 * kScratchMaxRhs;
-  d.IE = tab + 2 * kScratchMaxRhs;
-  d.IO = tab + 3 * kScratchMaxRhs;
-  d.OE = tab + 4 * kScratchMaxRhs;
-  d.OO = tab + 5 * kScratchMaxRhs;
-  d.T = tab + 6 * kScratchMaxRhs;
-  d.NUL = tab + 7 * kScratchMaxRhs;
-  d.coef = reinterpret_cast<const Coef5*>(base + 8 * kScratchMaxRhs * sizeof(void*));
+  if (nrhs == 1) {  // the pointers travel in the launches
+    d = DslashTables{PtrTab::single(ib), PtrTab::single(ob), PtrTab::single(w), PtrTab::single(w + fb),
+                     PtrTab::single(w + fb * 2), PtrTab::single(w + fb * 3), PtrTab::single(w + fb * 4), PtrTab(),
+                     CoefTab::single(coef)};
+  } else {
+    ScratchTables t{};
+    for (int r = 0; r < nrhs; ++r) {
+      t.ptr[0][r] = ib + ub * r;
+      t.ptr[1][r] = ob + ub * r;
+      for (int k = 0; k < 5; ++k) t.ptr[2 + k][r] = w + fb * (5 * r + k);
+      t.ptr[7][r] = nullptr;
+      t.coef[r] = coef;
+    }
+    launch_k(k_put_tables, dim3(1), dim3(256), 0, c->stream, t, base);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_err(c, e, "mdwf_dslash_noalloc: table kernel");
+    char* const* tab = reinterpret_cast<char* const*>(base);
+    PtrTab p[8];
+    for (int k = 0; k < 8; ++k) p[k] = PtrTab(tab + k * kScratchMaxRhs);
+    d = DslashTables{p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7],
+                     CoefTab(reinterpret_cast<const Coef5*>(base + 8 * kScratchMaxRhs * sizeof(void*)))};
+  }
   // kernel timing would create HIP events: it is left off for this call
   const int prof = c->prof;
   c->prof = 0;
@@ -425,19 +404,19 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   if (phase_ms != nullptr)
     for (auto& x : ev) (void)hipEventCreate(&x);
-  hipError_t e = layout_user_to_half(geom, UIN, nullptr, IO, prec, nrhs, c->stream);
+  hipError_t e = layout_user_to_half(geom, PtrTab(UIN), PtrTab(), PtrTab(IO), prec, nrhs, c->stream);
   if (e == hipSuccess && ev[0]) e = hipEventRecord(ev[0], c->stream);
   if (e == hipSuccess && split_mask != 0) e = dd_pack(D, prec, c->stream);
   if (e == hipSuccess && ev[1]) e = hipEventRecord(ev[1], c->stream);
   if (e == hipSuccess) {
     Prog p = prog_HOP(0, false);
     p.split = split_mask;
-    e = run_prog(c, g, geom, prec, p, IO, nullptr, OE, coef_d, nrhs, nullptr, 0, nullptr, 0, cls, false);
+    e = run_prog(c, g, geom, prec, p, PtrTab(IO), PtrTab(), PtrTab(OE), CoefTab(coef_d), nrhs, nullptr, 0, nullptr, 0, cls, false);
   }
   if (e == hipSuccess && ev[2]) e = hipEventRecord(ev[2], c->stream);
   if (e == hipSuccess && split_mask != 0) e = dd_exterior(D, prec, c->stream);
   if (e == hipSuccess && ev[3]) e = hipEventRecord(ev[3], c->stream);
-  if (e == hipSuccess) e = layout_half_to_user(geom, OE, NUL, UOUT, prec, nrhs, c->stream);
+  if (e == hipSuccess) e = layout_half_to_user(geom, PtrTab(OE), PtrTab(NUL), PtrTab(UOUT), prec, nrhs, c->stream);
   if (phase_ms != nullptr) {
     if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
     for (int k = 0; k < 3; ++k) {

@@ -121,8 +121,8 @@ static mdwf_status norms_f64(mdwf_ctx* c, const Geom& g, const std::vector<const
   if (s != MDWF_OK) return s;
   s = ensure(c, c->red_out, (size_t)n * sizeof(double));
   if (s != MDWF_OK) return s;
-  B.a = upload_table(c, a);
-  B.b = upload_table(c, b);
+  B.a = PtrTab(upload_table(c, a));
+  B.b = PtrTab(upload_table(c, b));
   B.partials = static_cast<double*>(c->partials_b.p);
   hipEvent_t ev;
   prof_begin(c, &ev);
@@ -135,61 +135,39 @@ static mdwf_status norms_f64(mdwf_ctx* c, const Geom& g, const std::vector<const
   return read_sums(c, n, out);
 }
 
-// single-slot helpers (tables of one entry)
+// single-slot helpers (the pointers travel in the launches)
 struct One {
   mdwf_ctx* c;
   const mdwf_gauge* g;
   Geom geom;
-  const Coef5* coef_d;
+  CoefTab coef;
   hipError_t e = hipSuccess;
-  // a one-entry device pointer table; a failed upload turns into an error
-  // here instead of a null table reaching a kernel
-  char* const* tab(const void* p) {
-    char* const* t = upload_table(c, std::vector<const void*>{p});
-    if (t == nullptr && e == hipSuccess) e = hipErrorOutOfMemory;
-    return t;
-  }
+  static PtrTab tab(const void* p) { return PtrTab::single(p); }
   // an FP64 program on fields of one job
   void prog(const Prog& p, const void* in, const void* aux, void* out) {
     if (e != hipSuccess) return;
-    if (coef_d == nullptr) { e = hipErrorInvalidValue; return; }
-    char* const* I = tab(in);
-    char* const* A = aux ? tab(aux) : nullptr;
-    char* const* O = tab(out);
-    if (e != hipSuccess) return;
-    e = run_prog(c, g, geom, F64, p, I, A, O, coef_d, 1, nullptr, 0, nullptr, 0, MDWF_PROF_DSLASH_F64,
+    e = run_prog(c, g, geom, F64, p, tab(in), tab(aux), tab(out), coef, 1, nullptr, 0, nullptr, 0, MDWF_PROF_DSLASH_F64,
                  in != out && aux != out);
   }
   void to_half(const void* user, void* half, int par) {
     if (e != hipSuccess) return;
-    char* const* U = tab(user);
-    char* const* H = tab(half);
-    if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
-    e = layout_user_to_half(geom, U, par == 0 ? H : nullptr, par == 0 ? nullptr : H, F64, 1, c->stream);
+    e = layout_user_to_half(geom, tab(user), tab(par == 0 ? half : nullptr), tab(par == 0 ? nullptr : half), F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
   void to_halves(const void* user, void* even, void* odd) {
     if (e != hipSuccess) return;
-    char* const* U = tab(user);
-    char* const* E = tab(even);
-    char* const* O = tab(odd);
-    if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
-    e = layout_user_to_half(geom, U, E, O, F64, 1, c->stream);
+    e = layout_user_to_half(geom, tab(user), tab(even), tab(odd), F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
   void to_user(const void* even, const void* odd, void* user) {
     if (e != hipSuccess) return;
-    char* const* E = tab(even);
-    char* const* O = tab(odd);
-    char* const* U = tab(user);
-    if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
-    e = layout_half_to_user(geom, E, O, U, F64, 1, c->stream);
+    e = layout_half_to_user(geom, tab(even), tab(odd), tab(user), F64, 1, c->stream);
     prof_end(c, MDWF_PROF_OTHER, 0, ev);
   }
   // r (precision ps) = lo(rh), and |rh|^2 to the host
@@ -202,7 +180,6 @@ struct One {
     B.a = tab(rh);
     B.b = tab(r);
     B.partials = static_cast<double*>(c->partials_b.p);
-    if (e != hipSuccess) return hip_err(c, e, "residual");
     hipEvent_t ev;
     prof_begin(c, &ev);
     e = blas_round(B, ps, c->stream);
@@ -222,7 +199,6 @@ struct One {
     B.b = tab(r);
     B.c = tab(pt);
     B.ca = beta;
-    if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
     e = blas_cg_p(B, ps, c->stream);
@@ -233,12 +209,11 @@ struct One {
   void update(void* x, int px, void* xh, const void* eta_hat, void* z, void* pt) {
     if (e != hipSuccess) return;
     BlasArgs B = args();
-    if (x != nullptr) B.a = tab(x);
+    B.a = tab(x);
     B.b = tab(xh);
     B.c = tab(eta_hat);
     B.d = tab(z);
     B.e = tab(pt);
-    if (e != hipSuccess) return;
     hipEvent_t ev;
     prof_begin(c, &ev);
     e = blas_update(B, x != nullptr ? px : -1, c->stream);
@@ -249,7 +224,7 @@ struct One {
     BlasArgs B{};
     B.g = geom;
     B.nslots = 1;
-    B.coef = coef_d;
+    B.coef = coef;
     B.nt_store = streaming_stores(geom, F64, 1);
     return B;
   }
@@ -313,9 +288,7 @@ static mdwf_status finalize(mdwf_ctx* c, mdwf_job* j, int r) {
   FP64Temps T;
   mdwf_status st = get_temps(c, j->geom, T);
   if (st != MDWF_OK) return st;
-  One o{c, j->g, j->geom, nullptr};
-  std::vector<Coef5> cf(1, j->coef);
-  o.coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), sizeof(Coef5)));
+  One o{c, j->g, j->geom, CoefTab::single(j->coef)};
   const char* eta = j->eta + j->user_bytes * r;
   char* psi = j->psi + j->user_bytes * r;
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
@@ -354,9 +327,7 @@ static mdwf_status reliable_update(mdwf_ctx* c, mdwf_job* j, int r, double& rr) 
   FP64Temps T;
   mdwf_status st = get_temps(c, j->geom, T);
   if (st != MDWF_OK) return st;
-  One o{c, j->g, j->geom, nullptr};
-  std::vector<Coef5> cf(1, j->coef);
-  o.coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), sizeof(Coef5)));
+  One o{c, j->g, j->geom, CoefTab::single(j->coef)};
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
   true_residual(o, T, j->ps != F64 ? j->fx[r] : nullptr, j->px, xh, j->feh[r]);
   if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
@@ -456,9 +427,7 @@ extern "C" mdwf_status mdwf_job_begin(mdwf_ctx* c, const mdwf_gauge* g, const md
     mdwf_job_end(j);
     return st;
   }
-  One o{c, g, geom, nullptr};
-  std::vector<Coef5> cf(1, j->coef);
-  o.coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), sizeof(Coef5)));
+  One o{c, g, geom, CoefTab::single(j->coef)};
   for (int r = 0; r < nrhs && st == MDWF_OK; ++r) {
     const char* er = j->eta + ub * r;
     char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
@@ -547,9 +516,8 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
   gather();
   if (slots.empty() || iters == 0) return MDWF_OK;
 
-  using Tab = char* const*;
-  Tab X = nullptr, R = nullptr, P = nullptr, PT = nullptr, T = nullptr, V = nullptr;
-  const Coef5* coef_d = nullptr;
+  PtrTab X, R, P, PT, T, V;
+  CoefTab coef;
   CGState* S_d = nullptr;
   double* pd = nullptr;
   double* pb = nullptr;
@@ -564,10 +532,10 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
       t[i] = j->ft[k]; v[i] = j->fv[k];
       cf[i] = j->coef;
     }
-    X = upload_table(c, x); R = upload_table(c, r); P = upload_table(c, p); PT = upload_table(c, pt);
-    T = upload_table(c, t); V = upload_table(c, v);
-    coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), n * sizeof(Coef5)));
-    if (!X || !R || !P || !PT || !T || !V || !coef_d) return set_err(c, MDWF_EHIP, "mdwf_job_step: table upload");
+    LaunchTables lt;
+    if (!make_tables(c, {x, r, p, pt, t, v}, cf, lt)) return set_err(c, MDWF_EHIP, "mdwf_job_step: table upload");
+    X = lt.tab[0]; R = lt.tab[1]; P = lt.tab[2]; PT = lt.tab[3]; T = lt.tab[4]; V = lt.tab[5];
+    coef = lt.coef;
     mdwf_status s2 = ensure(c, c->states, n * sizeof(CGState));
     if (s2 == MDWF_OK) s2 = ensure(c, c->partials_d, (size_t)n * ntiles * sizeof(double));
     if (s2 == MDWF_OK) s2 = ensure(c, c->partials_b, (size_t)n * nblk * sizeof(double));
@@ -644,10 +612,10 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
     for (int i = 0; i < n; ++i) it0[i] = slots[i].job->st[slots[i].r].iters;
     prof_chunk_begin(c, chunk);
     auto iteration = [&]() -> hipError_t {
-      hipError_t e = run_prog(c, j0->g, geom, ps, prog_A1(), PT, nullptr, T, coef_d, n, act, stride, nullptr, 0,
+      hipError_t e = run_prog(c, j0->g, geom, ps, prog_A1(), PT, PtrTab(), T, coef, n, act, stride, nullptr, 0,
                               MDWF_PROF_DSLASH_INNER, true);
       if (e == hipSuccess)
-        e = run_prog(c, j0->g, geom, ps, prog_A2(true, true), T, P, V, coef_d, n, act, stride, pd, ntiles,
+        e = run_prog(c, j0->g, geom, ps, prog_A2(true, true), T, P, V, coef, n, act, stride, pd, ntiles,
                      MDWF_PROF_DSLASH_INNER, true);
       hipEvent_t ev;
       if (e == hipSuccess) {  // alpha = rho / <p, A p>, <p, A p> = |M^ p|^2 from A2
@@ -656,15 +624,15 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
         prof_end(c, MDWF_PROF_SCALAR, 0, ev);
       }
       if (e == hipSuccess) {  // w_o = M_phi^T M5^-T H^+_oe v (and x += alpha p)
-        const CgFuse fx{X, nullptr, P, S_d, 3};
-        e = run_prog(c, j0->g, geom, ps, prog_B1(), V, nullptr, T, coef_d, n, act, stride, nullptr, 0,
+        const CgFuse fx{X, PtrTab(), P, S_d, 3};
+        e = run_prog(c, j0->g, geom, ps, prog_B1(), V, PtrTab(), T, coef, n, act, stride, nullptr, 0,
                      MDWF_PROF_DSLASH_INNER, true, x_in_b1 ? &fx : nullptr);
       }
       if (e == hipSuccess) {  // q = M^+ M^ p, fused with r -= alpha q, |r|^2 (and x += alpha p)
         const CgFuse fz{X, R, P, S_d, x_in_b1 ? 2 : 1};
         Prog b2 = prog_B2();
         b2.reduce = 1;
-        e = run_prog(c, j0->g, geom, ps, b2, T, V, T, coef_d, n, act, stride, pd, ntiles, MDWF_PROF_DSLASH_INNER,
+        e = run_prog(c, j0->g, geom, ps, b2, T, V, T, coef, n, act, stride, pd, ntiles, MDWF_PROF_DSLASH_INNER,
                      false, &fz);
       }
       if (e == hipSuccess) {
@@ -678,7 +646,7 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
         B.nslots = n;
         B.a = P; B.b = R; B.c = PT;
         B.st = S_d;
-        B.coef = coef_d;
+        B.coef = coef;
         B.nt_store = streaming_stores(geom, ps, n);
         prof_begin(c, &ev);
         e = blas_cg_p(B, ps, c->stream);
@@ -762,10 +730,7 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
         } else {
           // continue: beta from the true residual, p = r + beta p
           const double beta = rr / s.rho;
-          One o{c, j->g, geom, nullptr};
-          std::vector<Coef5> cf(1, j->coef);
-          o.coef_d = static_cast<const Coef5*>(upload_bytes(c, cf.data(), sizeof(Coef5)));
-          if (o.coef_d == nullptr) return set_err(c, MDWF_EHIP, "reliable update: coefficient upload");
+          One o{c, j->g, geom, CoefTab::single(j->coef)};
           o.direction(j->fp[r], j->fr[r], j->fpt[r], ps, beta);
           if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
           s.rho = rr;
