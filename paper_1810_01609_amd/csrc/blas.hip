@@ -95,17 +95,30 @@ __device__ __forceinline__ void column_mphi(void* smem, const ColumnThread& t, i
   for (int k = 0; k < 12; ++k) out[12 + k] = b5 * v[12 + k] + cd * rd[k];
 }
 
-// p = r + beta p, and pt = M_phi p from the new p: the input of the first
-// stencil launch of the next iteration, which then needs no fifth-dimension
-// prologue on its eight neighbours.
+// p' = r + beta p, and pt = M_phi p': the input of the first stencil launch of
+// the next iteration, which then needs no fifth-dimension prologue on its eight
+// neighbours.  The direction alternates between two fields, so that x can be
+// updated with two of them at once.
 template <int PS>
 __global__ __launch_bounds__(512) void k_cg_p(BlasArgs A, int tiles) {
   using RS = typename PrecTraits<PS>::Real;
   extern __shared__ __align__(16) unsigned char smem[];
   const int slot = blockIdx.y;
-  if (A.st != nullptr && !A.st[slot].active) return;
-  const RS beta = (RS)(A.st != nullptr ? A.st[slot].beta : A.ca);
-  const bool fresh = A.st == nullptr && A.ca == 0.0;  // p = r
+  // everything of the slot in one burst of scalar loads
+  char *pa = A.a[slot], *pb = A.b[slot], *pc = A.c[slot], *pd = A.d[slot];
+  const Coef5 coef = A.coef[slot];
+  int active = 1, phase = 1;
+  double b = A.ca;
+  if (A.st != nullptr) {
+    active = A.st[slot].active;
+    phase = A.st[slot].phase;
+    b = A.st[slot].beta;
+  }
+  if (!active) return;
+  const RS beta = (RS)b;
+  const bool fresh = A.st == nullptr && A.ca == 0.0;  // p' = r
+  const char* from = phase != 0 ? pa : pd;
+  char* to = phase != 0 ? pd : pa;
   const ColumnThread t = column_thread(A.g, tiles);
   const FieldDesc f{A.g.Vh, A.g.L5};
   RS cur[24], out[24];
@@ -113,14 +126,14 @@ __global__ __launch_bounds__(512) void k_cg_p(BlasArgs A, int tiles) {
   for (int k = 0; k < 24; ++k) cur[k] = 0;
   if (t.valid) {
     RS rv[24];
-    if (!fresh) SpinorAt<PS>::load(A.a[slot], f, t.at, cur);
-    SpinorAt<PS>::load(A.b[slot], f, t.at, rv);
+    if (!fresh) SpinorAt<PS>::load(from, f, t.at, cur);
+    SpinorAt<PS>::load(pb, f, t.at, rv);
 #pragma unroll
     for (int k = 0; k < 24; ++k) cur[k] = rv[k] + beta * cur[k];
-    SpinorAt<PS>::store(A.a[slot], f, t.at, cur, A.nt_store);
+    SpinorAt<PS>::store(to, f, t.at, cur, A.nt_store);
   }
-  column_mphi<RS>(smem, t, A.g.L5, A.coef[slot], cur, out);
-  if (t.valid) SpinorAt<PS>::store(A.c[slot], f, t.at, out, A.nt_store);
+  column_mphi<RS>(smem, t, A.g.L5, coef, cur, out);
+  if (t.valid) SpinorAt<PS>::store(pc, f, t.at, out, A.nt_store);
 }
 
 // The streaming part of a reliable update in one pass: fold the solution
@@ -130,26 +143,48 @@ __global__ __launch_bounds__(512) void k_cg_p(BlasArgs A, int tiles) {
 // two xpays, a clearing pass and a fifth-dimension pass, and the FP64 M^ of the
 // update needs no M_phi prologue: the FP64 work of a 16^3 x 32 x 12 solve of 12
 // RHS (12 updates each) went from 151 to 124 ms.
-template <int PX, bool HAS_X>
+template <int PS>
 __global__ __launch_bounds__(512) void k_update(BlasArgs A, int tiles) {
+  using RS = typename PrecTraits<PS>::Real;
   extern __shared__ __align__(16) unsigned char smem[];
   const int slot = blockIdx.y;
   const ColumnThread t = column_thread(A.g, tiles);
   const FieldDesc f{A.g.Vh, A.g.L5};
+  const bool has_x = !A.a.empty(), has_p = !A.f.empty();
   double xh[24], out[24];
 #pragma unroll
   for (int k = 0; k < 24; ++k) xh[k] = 0;
   if (t.valid) {
     SpinorAt<F64>::load(A.b[slot], f, t.at, xh);
-    if constexpr (HAS_X) {
-      typename PrecTraits<PX>::Real x[24];
-      SpinorAt<PX>::load(A.a[slot], f, t.at, x);
+    if (has_x || has_p) {
+      constexpr int PX = PS == F64 ? F64 : F32;
+      RS x[24];  // the arithmetic type of the inner iteration is the type of x
 #pragma unroll
-      for (int k = 0; k < 24; ++k) {
-        xh[k] += (double)x[k];
-        x[k] = 0;
+      for (int k = 0; k < 24; ++k) x[k] = 0;
+      if constexpr (PS == F64) {
+#pragma unroll
+        for (int k = 0; k < 24; ++k) x[k] = xh[k];
+      } else {
+        if (has_x) SpinorAt<PX>::load(A.a[slot], f, t.at, x);
       }
-      SpinorAt<PX>::store(A.a[slot], f, t.at, x, A.nt_store);
+      if (has_p) {
+        RS p[24];
+        SpinorAt<PS>::load(A.f[slot], f, t.at, p);
+        const RS alpha = (RS)A.ca;
+#pragma unroll
+        for (int k = 0; k < 24; ++k) x[k] += alpha * p[k];
+      }
+      if constexpr (PS == F64) {
+#pragma unroll
+        for (int k = 0; k < 24; ++k) xh[k] = x[k];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 24; ++k) {
+          xh[k] += (double)x[k];
+          x[k] = 0;
+        }
+        SpinorAt<PX>::store(A.a[slot], f, t.at, x, A.nt_store);
+      }
       SpinorAt<F64>::store(A.b[slot], f, t.at, xh, A.nt_store);
     }
     SpinorAt<F64>::load(A.c[slot], f, t.at, out);
@@ -239,11 +274,18 @@ template <int PS> static hipError_t cg_p_launch(const BlasArgs& A, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t blas_update(BlasArgs A, int px, hipStream_t st) {
+hipError_t blas_update(BlasArgs A, int ps, hipStream_t st) {
   const ColumnLaunch<double> L(A.g, A.nslots);
-  if (px < 0) launch_k((k_update<F64, false>), L.grid, L.block, L.lds, st, A, L.tiles);
-  else if (px == F32) launch_k((k_update<F32, true>), L.grid, L.block, L.lds, st, A, L.tiles);
-  else return hipErrorInvalidValue;
+  // an increment needs a field to go to
+  if (ps == F64 ? !A.a.empty() : A.a.empty() && !A.f.empty()) return hipErrorInvalidValue;
+  switch (ps) {
+    case F64: launch_k(k_update<F64>, L.grid, L.block, L.lds, st, A, L.tiles); break;
+    case F32: launch_k(k_update<F32>, L.grid, L.block, L.lds, st, A, L.tiles); break;
+    case F16: launch_k(k_update<F16>, L.grid, L.block, L.lds, st, A, L.tiles); break;
+    case BF16: launch_k(k_update<BF16>, L.grid, L.block, L.lds, st, A, L.tiles); break;
+    case I16: launch_k(k_update<I16>, L.grid, L.block, L.lds, st, A, L.tiles); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -370,6 +412,7 @@ __global__ __launch_bounds__(kScalarThreads) void k_cg_alpha(CGState* S, const d
       s.flags |= CG_FLAG_BREAKDOWN;
       s.active = 0;
     } else {
+      s.alpha_prev = s.alpha;
       s.alpha = s.rho / pq;
     }
   }
@@ -398,6 +441,7 @@ __global__ __launch_bounds__(kScalarThreads) void k_cg_beta(CGState* S, const do
     } else {
       s.beta = rr / s.rho;
       s.rho = rr;
+      s.phase ^= 1;  // the next direction goes to the other field; a frozen RHS keeps its phase
       if (rn > s.rmax) s.rmax = rn;
     }
   }

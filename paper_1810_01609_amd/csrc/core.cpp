@@ -467,11 +467,12 @@ static double prog_bytes(const Geom& g, int prec, const Prog& p, int nslots, int
   const double sb = spinor_site_bytes(prec);
   const double xs = spinor_site_bytes(prec == F64 ? F64 : F32) / sb;
   // in + out (+ aux); the fused CG update reads r and writes r instead of
-  // out (+ reads p, reads and writes x), or adds p and x to a plain launch
+  // out (+ p and x), or adds p and x to a plain launch
   double per = 2.0 + (p.aux != AUX_NONE ? 1.0 : 0.0);
-  if (cg == 1) per += 2.0 + 2.0 * xs;
+  // the update of x comes every second iteration: two p and x read, x written
+  if (cg == 1) per += 2.0 + xs;
   if (cg == 2) per += 1.0;
-  if (cg == 3) per += 1.0 + 2.0 * xs;
+  if (cg == 3) per += 1.0 + xs;
   double b = nslots * ne * sb * per;
   if (p.hop) b += 8.0 * g.Vh * 12.0 * link_real_bytes(prec);
   return b;
@@ -507,6 +508,7 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
     A.cg_x = fuse->x;
     A.cg_r = fuse->r;
     A.cg_p = fuse->p;
+    A.cg_p2 = fuse->p2;
     A.cg_st = fuse->st;
   }
   std::vector<int> cand;
@@ -514,9 +516,10 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   candidates(geom, prec, A, pr.hop, pr.dag, cand, dflt);
   if (cand.empty()) return hipErrorInvalidValue;
   int lg = dflt;
-  const std::string key = tune_key(geom, prec, pr, nslots, fuse != nullptr ? fuse->mode : 0);
   // the fused CG update is destructive (x, r in place): never tuned on live data
-  if (fuse != nullptr) tunable = false;
+  const bool destructive = fuse != nullptr && fuse->mode != 4;
+  const std::string key = tune_key(geom, prec, pr, nslots, destructive ? fuse->mode : 0);
+  if (destructive) tunable = false;
   auto it = c->tune.find(key);
   if (it != c->tune.end()) {
     lg = it->second;

@@ -291,8 +291,23 @@ struct FieldDesc {
 
 template <int P> struct SpinorAt;
 
+// load8 / store8: the third k of a site's 24 reals (store8 for FP64 and FP32)
 template <> struct SpinorAt<F64> {
   using R = double;
+  static __device__ __forceinline__ void load8(const char* base, const FieldDesc&, const Place& at, int k, R v[8]) {
+    const double2* p = reinterpret_cast<const double2*>(base) + group_index(at, 4 * k, 12);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const v2d d = ldg<v2d>(p + (size_t)g * kSiteTile);
+      v[2 * g] = d.x;
+      v[2 * g + 1] = d.y;
+    }
+  }
+  static __device__ __forceinline__ void store8(char* base, const FieldDesc&, const Place& at, int k, const R v[8], bool nt) {
+    double2* p = reinterpret_cast<double2*>(base) + group_index(at, 4 * k, 12);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) stg<v2d>(p + (size_t)g * kSiteTile, v2d{v[2 * g], v[2 * g + 1]}, nt);
+  }
   static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, const Place& at, R v[24]) {
     const double2* p = reinterpret_cast<const double2*>(base) + group_index(at, 0, 12);
 #pragma unroll
@@ -322,6 +337,22 @@ template <> struct SpinorAt<F64> {
 
 template <> struct SpinorAt<F32> {
   using R = float;
+  static __device__ __forceinline__ void load8(const char* base, const FieldDesc&, const Place& at, int k, R v[8]) {
+    const float4* p = reinterpret_cast<const float4*>(base) + group_index(at, 2 * k, 6);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const v4f d = ldg<v4f>(p + (size_t)g * kSiteTile);
+      v[4 * g] = d.x;
+      v[4 * g + 1] = d.y;
+      v[4 * g + 2] = d.z;
+      v[4 * g + 3] = d.w;
+    }
+  }
+  static __device__ __forceinline__ void store8(char* base, const FieldDesc&, const Place& at, int k, const R v[8], bool nt) {
+    float4* p = reinterpret_cast<float4*>(base) + group_index(at, 2 * k, 6);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) stg<v4f>(p + (size_t)g * kSiteTile, v4f{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]}, nt);
+  }
   static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, const Place& at, R v[24]) {
     const float4* p = reinterpret_cast<const float4*>(base) + group_index(at, 0, 6);
 #pragma unroll
@@ -376,6 +407,9 @@ template <int P> struct SpinorAt16 {
 #pragma unroll
       for (int k = 0; k < 8; ++k) v[k] *= sc;
     }
+  }
+  static __device__ __forceinline__ void load8(const char* base, const FieldDesc& f, const Place& at, int k, R v[8]) {
+    group(base, f, at, k, scale(base, f, at), v);
   }
   static __device__ __forceinline__ void load(const char* base, const FieldDesc& f, const Place& at, R v[24]) {
     const float sc = scale(base, f, at);
@@ -589,6 +623,12 @@ struct CGState {
   int flags;    // CG_FLAG_*
   int iters;
   int max_iter;
+  // x is updated every second iteration: the current direction is in the first
+  // (0) or second (1) of the two p fields, and in phase 1 the update of x by
+  // the first, with alpha_prev, is still due
+  int phase;
+  int pad_;
+  double alpha_prev;
   double rho;       // |r|^2 of the current residual
   double rho_new;   // |r|^2 after the latest update
   double pq;        // <p, A p>

@@ -519,18 +519,25 @@ template <class R> __device__ __forceinline__ void lds_get(const R* lds, int CB,
 // The kernel.  HOP = false turns it into a pure fifth-dimension operator
 // (input and output of the same parity).
 // ---------------------------------------------------------------------------
-// x += alpha p on one (checkerboard index, slice) of the CG's x and p
+// x += alpha_prev p + alpha p2 on one (checkerboard index, slice) of the CG's
+// x and p, in phase 1
 template <int P>
-__device__ __forceinline__ void x_update(const DslashArgs& A, const FieldDesc& f, int slot, int cb, int s,
-                                         typename PrecTraits<P>::Real alpha) {
+__device__ __forceinline__ void x_update(const DslashArgs& A, const SlotIO& io, const FieldDesc& f, int cb, int s) {
   constexpr int PX = P == F64 ? F64 : F32;
-  typename PrecTraits<P>::Real pv[24];
-  typename PrecTraits<PX>::Real xv[24];
-  SpinorIO<P>::load(A.cg_p[slot], f, cb, s, pv);
-  SpinorIO<PX>::load(A.cg_x[slot], f, cb, s, xv);
+  using R = typename PrecTraits<P>::Real;
+  if (io.phase == 0) return;
+  const R a0 = (R)io.alpha_prev, a1 = (R)io.alpha;
+  const Place at = place_of(cb, s, f.L5);
 #pragma unroll
-  for (int k = 0; k < 24; ++k) xv[k] += alpha * pv[k];
-  SpinorIO<PX>::store(A.cg_x[slot], f, cb, s, xv, A.nt_store);
+  for (int k = 0; k < 3; ++k) {  // a third at a time: a few registers
+    R p0[8], p1[8], xv[8];
+    SpinorAt<P>::load8(io.p, f, at, k, p0);
+    SpinorAt<P>::load8(io.p2, f, at, k, p1);
+    SpinorAt<PX>::load8(io.x, f, at, k, xv);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) xv[i] = (xv[i] + a0 * p0[i]) + a1 * p1[i];
+    SpinorAt<PX>::store8(io.x, f, at, k, xv, A.nt_store);
+  }
 }
 
 // FP64 needs ~180 VGPRs per thread (2 waves per SIMD), the 32-bit
@@ -538,16 +545,10 @@ __device__ __forceinline__ void x_update(const DslashArgs& A, const FieldDesc& f
 template <int P> constexpr int kMaxThreads = P == F64 ? 512 : 1024;
 
 // Resident waves per SIMD the register allocation must leave room for.  The
-// 16-bit kernels are asked for 6 (67-80 VGPRs instead of 83-102, no spills in
-// FP16, a few in BF16/int16): 6-9 % faster on 32^3 x 64, 0-3 % on 24^3 x 64.
-// The FP32 and FP64 kernels are asked for the floor their launch bound
-// implies (FP32 at 6 spills and ran 9 % slower).  The build option
-// MDWF_WAVES_PER_EU sets the 16-bit request.
-#ifndef MDWF_WAVES_PER_EU
-#define MDWF_WAVES_PER_EU 0
-#endif
-template <int P> constexpr int kWavesPerEU =
-    (P == F16 || P == BF16 || P == I16) ? (MDWF_WAVES_PER_EU > 0 ? MDWF_WAVES_PER_EU : 6) : kMaxThreads<P> / 256;
+// 16-bit kernels are asked for 5 (96 VGPRs, no spills; at 6 they spill 5-10
+// registers: int16 on 10 x 6 x 14 x 18, L5 = 10, 17.0 -> 15.5 us a launch); the FP32 and FP64 kernels for the floor their launch bound
+// implies (FP32 at 6 spills and ran 9 % slower).
+template <int P> constexpr int kWavesPerEU = (P == F16 || P == BF16 || P == I16) ? 5 : kMaxThreads<P> / 256;
 
 template <int P, bool HOP, bool DAG, bool STAGE, bool CGU, bool SPLIT>
 __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<P>))) void dslash5_kernel(
@@ -573,7 +574,7 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
   int slot, blk;
   block_slot(A, lb, slot, blk);
   const int cb0 = block_first_site(A, blk, CB);
-  if (A.active != nullptr && A.active[(size_t)slot * A.active_stride] == 0) return;
+  const SlotIO io = slot_io<true, CGU, DAG>(A, slot);
   const int cb = cb0 + cbl;
   const bool valid = cb < A.g.Vh;
   const Coef5 c = A.coef[slot];
@@ -584,8 +585,9 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
               reinterpret_cast<R*>(smem + A.lds_stage_off + stage_nbr_bytes(CB))};
   if constexpr (HOP && STAGE) {
     stage_fill<P, SPLIT>(A, st, CB, A.cb_log2, cb0, tid, nthr);
-    __syncthreads();
   }
+  if (io.active == 0) return;  // after the stage: its loads do not wait for the flag
+  if constexpr (HOP && STAGE) __syncthreads();
 
   R v[24];
 #pragma unroll
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) acc[a][b] = {0, 0};
-      const char* in = A.in[slot];
+      const char* in = io.in;
       if constexpr (STAGE && kHopBatch<P, CGU> > 0) {
         hop_batches<P, DAG, SPLIT, kHopBatch<P, CGU>, 0>(f, in, s, acc, st, CB, cbl);
       } else {
@@ -614,7 +616,7 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
         v[2 * k + 1] = acc[k / 3][k % 3].im;
       }
     } else {
-      SpinorIO<P>::load(A.in[slot], f, cb, s, v);
+      SpinorIO<P>::load(io.in, f, cb, s, v);
     }
   }
 
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
   const R cy = (R)A.coef_y;
   if (A.aux_mode != AUX_NONE && valid) {
     R w[24];
-    const char* aux = A.aux[slot];
+    const char* aux = io.aux;
     if (A.aux_mode == AUX_PLAIN) SpinorIO<P>::load(aux, f, cb, s, w);
     else load_bidiag<P>(aux, f, cb, s, L5, (R)c.alpha, (R)c.beta, (R)c.mq, A.aux_mode == AUX_M5DAG, w);
 #pragma unroll
@@ -646,16 +648,16 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
     // r -= alpha q with q = v (and x += alpha p unless a previous launch of
     // the iteration did it); v becomes r for the reduction
     if (valid) {
-      const R alpha = (R)A.cg_st[slot].alpha;
+      const R alpha = (R)io.alpha;
       R rv[24];
-      SpinorIO<P>::load(A.cg_r[slot], f, cb, s, rv);
+      SpinorIO<P>::load(io.r, f, cb, s, rv);
 #pragma unroll
       for (int k = 0; k < 24; ++k) {
         rv[k] -= alpha * v[k];
         v[k] = rv[k];
       }
-      SpinorIO<P>::store(A.cg_r[slot], f, cb, s, rv, A.nt_store);
-      if (A.cg_update == 1) x_update<P>(A, f, slot, cb, s, alpha);
+      SpinorIO<P>::store(io.r, f, cb, s, rv, A.nt_store);
+      if (A.cg_update == 1) x_update<P>(A, io, f, cb, s);
     }
   }
 
@@ -692,8 +694,8 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
     __syncthreads();
     lds_get(lds, CB, cbl, s, v);
   }
-  if (valid && !CGU) SpinorIO<P>::store(A.out[slot], f, cb, s, v, A.nt_store);
-  if (!CGU && A.cg_update == 3 && valid) x_update<P>(A, f, slot, cb, s, (R)A.cg_st[slot].alpha);
+  if (valid && !CGU) SpinorIO<P>::store(io.out, f, cb, s, v, A.nt_store);
+  if (!CGU && DAG && A.cg_update == 3 && valid) x_update<P>(A, io, f, cb, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -715,10 +717,10 @@ template <int P, bool STAGE>
 static hipError_t launch_s(const DslashArgs& A, bool dag, int threads, size_t smem, int grid,
                            hipStream_t st) {
   // the CG update is fused into M^+ only: r (and x) into its second launch
-  // (B2), x alone possibly into its first (B1)
+  // (B2), x alone possibly into its first (B1); M^ takes p by its phase
   if (dag && (A.cg_update == 1 || A.cg_update == 2))
     return launch_t<P, true, true, STAGE, true>(A, threads, smem, grid, st);
-  if (A.cg_update != 0 && !(dag && A.cg_update == 3)) return hipErrorInvalidValue;
+  if (A.cg_update != 0 && !(dag ? A.cg_update == 3 : A.cg_update == 4)) return hipErrorInvalidValue;
   if (dag) return launch_t<P, true, true, STAGE>(A, threads, smem, grid, st);
   return launch_t<P, true, false, STAGE>(A, threads, smem, grid, st);
 }

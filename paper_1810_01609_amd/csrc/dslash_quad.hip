@@ -73,8 +73,8 @@ struct Base {
   char* d;
   char* s;
 };
-template <int P> __device__ __forceinline__ Base field_base(const PtrTab& table, int slot, const Geom& g, int w) {
-  char* p = uniform_ptr(table[slot]);
+template <int P> __device__ __forceinline__ Base field_base(char* field, const Geom& g, int w) {
+  char* p = uniform_ptr(field);
   Base b;
   b.d = p + (size_t)w * 4 * kSliceBytes<P>;
   b.s = p;
@@ -98,26 +98,28 @@ template <int P> __device__ __forceinline__ void pin_raw(Raw<P>& r) {
   for (int k = 0; k < kGroups<P>; ++k) asm volatile("" : "+v"(r.g[k]) : : "memory");
   if constexpr (is16(P)) asm volatile("" : "+v"(r.sc) : : "memory");
 }
-template <int P> __device__ __forceinline__ void unpack(const Raw<P>& r, float v[24]) {
+// one stored group: 4 (FP32) or 8 reals
+template <int P> __device__ __forceinline__ void unpack_group(const v4u& g, float sc, float* v) {
+  const uint32_t w[4] = {g.x, g.y, g.z, g.w};
 #pragma unroll
-  for (int k = 0; k < kGroups<P>; ++k) {
-    const uint32_t w[4] = {r.g[k].x, r.g[k].y, r.g[k].z, r.g[k].w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (P == F32) {
-        v[4 * k + j] = __uint_as_float(w[j]);
-      } else if constexpr (P == I16) {
-        const float scq = r.sc * (1.0f / 32767.0f);
-        v[8 * k + 2 * j] = (float)(int16_t)(uint16_t)(w[j] & 0xffffu) * scq;
-        v[8 * k + 2 * j + 1] = (float)(int16_t)(uint16_t)(w[j] >> 16) * scq;
-      } else {
-        float a, b;
-        unpack2<P>(w[j], a, b);
-        v[8 * k + 2 * j] = a * r.sc;
-        v[8 * k + 2 * j + 1] = b * r.sc;
-      }
+  for (int j = 0; j < 4; ++j) {
+    if constexpr (P == F32) {
+      v[j] = __uint_as_float(w[j]);
+    } else if constexpr (P == I16) {
+      const float scq = sc * (1.0f / 32767.0f);
+      v[2 * j] = (float)(int16_t)(uint16_t)(w[j] & 0xffffu) * scq;
+      v[2 * j + 1] = (float)(int16_t)(uint16_t)(w[j] >> 16) * scq;
+    } else {
+      float a, b;
+      unpack2<P>(w[j], a, b);
+      v[2 * j] = a * sc;
+      v[2 * j + 1] = b * sc;
     }
   }
+}
+template <int P> __device__ __forceinline__ void unpack(const Raw<P>& r, float v[24]) {
+#pragma unroll
+  for (int k = 0; k < kGroups<P>; ++k) unpack_group<P>(r.g[k], r.sc, v + k * (24 / kGroups<P>));
 }
 template <int P>
 __device__ __forceinline__ void store_own(const Base& b, uint32_t off, uint32_t soff, const float v[24], bool nt) {
@@ -551,7 +553,8 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   if (lb >= A.nslots * A.nblk) return;
   int slot, blk;
   block_slot(A, lb, slot, blk);
-  if (A.active != nullptr && A.active[(size_t)slot * A.active_stride] == 0) return;
+  constexpr bool kAux = PROG != QP_HOP && PROG != QP_A1 && PROG != QP_B1;
+  const SlotIO io = slot_io<kAux, PROG == QP_B2C, PROG == QP_B1 || PROG == QP_B2C>(A, slot);
   const int cb0 = block_first_site(A, blk, CB);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int sub = wave / nw;  // 16-site tile of the workgroup
@@ -572,6 +575,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   const size_t tot_tile = (size_t)sub * nw * 16 * kTotRow;
 
   fill_stage<P>(A, nbr, lnk, CB, A.cb_log2, cb0, tid, nthr);
+  if (io.active == 0) return;  // after the stage: its loads do not wait for the flag
   __syncthreads();
 
   float v[24];
@@ -581,7 +585,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int b = 0; b < 3; ++b) acc[a][b] = {0, 0};
-    const Base in = field_base<P>(A.in, slot, A.g, w);
+    const Base in = field_base<P>(io.in, A.g, w);
     hop_all<P, DAG, kQuadBatch, 0>(in, nbr + cbl * kNbrRow, lnk + cbl * kLinkRow<P>, q, lo, ls, acc);
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
@@ -603,14 +607,14 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     quad_chain<true, true, true>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
   } else if constexpr (PROG == QP_A2 || PROG == QP_A2C) {
     Raw<P> ar{};
-    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(A.aux, slot, A.g, w), tile, L5), oo, os, ar);
+    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
     float aux[24];
     unpack<P>(ar, aux);
     quad_chain<true, false, false>(v, aux, Q, kappa, mq, inv_c, (float)(A.coef_y * cf.inv_alpha), 0.f);
   } else if constexpr (PROG == QP_B2 || PROG == QP_B2C) {
     // M5^T aux + coef_y M_phi^T h = (alpha aux + coef_y b5 h) + shift(beta aux + coef_y c5 h)
     Raw<P> ar{};
-    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(A.aux, slot, A.g, w), tile, L5), oo, os, ar);
+    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
     float aux[24], add[24];
     unpack<P>(ar, aux);
     const float al = (float)cf.alpha, be = (float)cf.beta;
@@ -623,7 +627,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     quad_chain<false, true, true>(v, add, Q, 0.f, mq, 1.f, 0.f, 1.f);
   } else if constexpr (PROG == QP_D || PROG == QP_PRE) {
     Raw<P> ar{};
-    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(A.aux, slot, A.g, w), tile, L5), oo, os, ar);
+    if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
     float aux[24], add[24];
     unpack<P>(ar, aux);
     const float al = (float)cf.alpha, be = (float)cf.beta, cy = (float)A.coef_y;
@@ -638,8 +642,8 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
 
   if constexpr (PROG == QP_B2C) {
     if (valid) {
-      const float alpha = (float)A.cg_st[slot].alpha;
-      const Base rb = at_tile<P>(field_base<P>(A.cg_r, slot, A.g, w), tile, L5);
+      const float alpha = (float)io.alpha;
+      const Base rb = at_tile<P>(field_base<P>(io.r, A.g, w), tile, L5);
       Raw<P> rr;
       load_raw<P>(rb, oo, os, rr);
       float rv[24];
@@ -673,23 +677,36 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     quad_chain<true, false, true>(v, nullptr, Q2, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
   if constexpr (PROG != QP_B2C) {
-    if (valid) store_own<P>(at_tile<P>(field_base<P>(A.out, slot, A.g, w), tile, L5), oo, os, v, A.nt_store);
+    if (valid) store_own<P>(at_tile<P>(field_base<P>(io.out, A.g, w), tile, L5), oo, os, v, A.nt_store);
   }
   if ((PROG == QP_B1 && A.cg_update == 3) || (PROG == QP_B2C && A.cg_update == 1)) {
-    if (valid) {  // x += alpha p
-      const float alpha = (float)A.cg_st[slot].alpha;
-      Raw<P> pr;
-      Raw<F32> xr;
-      const Base xb = at_tile<F32>(field_base<F32>(A.cg_x, slot, A.g, w), tile, L5);
+    if (valid && io.phase != 0) {  // x += alpha_prev p + alpha p2
+      const float a0 = (float)io.alpha_prev, a1 = (float)io.alpha;
+      const Base b0 = at_tile<P>(field_base<P>(io.p, A.g, w), tile, L5);
+      const Base b1 = at_tile<P>(field_base<P>(io.p2, A.g, w), tile, L5);
+      const Base xb = at_tile<F32>(field_base<F32>(io.x, A.g, w), tile, L5);
       const uint32_t xo = (lane >> 4) * kSliceBytes<F32> + (lane & 15) * 16;
-      load_raw<P>(at_tile<P>(field_base<P>(A.cg_p, slot, A.g, w), tile, L5), oo, os, pr);
-      load_raw<F32>(xb, xo, 0, xr);
-      float pv[24], xv[24];
-      unpack<P>(pr, pv);
-      unpack<F32>(xr, xv);
+      // group by group: a few registers at a time
+      Raw<P> r0, r1;
+      if constexpr (is16(P)) {
+        r0.sc = ldo<float>(b0.s, os, 0);
+        r1.sc = ldo<float>(b1.s, os, 0);
+      }
 #pragma unroll
-      for (int k = 0; k < 24; ++k) xv[k] += alpha * pv[k];
-      store_own<F32>(xb, xo, 0, xv, A.nt_store);
+      for (int k = 0; k < kGroups<P>; ++k) {
+        constexpr int N = 24 / kGroups<P>;
+        float p0[N], p1[N];
+        unpack_group<P>(ldo<v4u>(b0.d, oo, k * 16 * kSiteTile), r0.sc, p0);
+        unpack_group<P>(ldo<v4u>(b1.d, oo, k * 16 * kSiteTile), r1.sc, p1);
+#pragma unroll
+        for (int j = 0; j < N / 4; ++j) {
+          const int imm = (k * (N / 4) + j) * 16 * kSiteTile;
+          v4f x = ldo<v4f>(xb.d, xo, imm);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[i] = (x[i] + a0 * p0[4 * j + i]) + a1 * p1[4 * j + i];
+          sto<v4f>(xb.d, xo, imm, x, A.nt_store);
+        }
+      }
     }
   }
 }
@@ -710,7 +727,7 @@ hipError_t launch_q(const DslashArgs& A, int threads, int grid, hipStream_t st) 
 // the program of a launch, or -1 where it has none here
 int quad_prog(const DslashArgs& A, bool dag) {
   if (!dag) {
-    if (A.cg_update != 0) return -1;
+    if (A.cg_update != 0 && !(A.cg_update == 4 && A.c1 == CH_M5INV)) return -1;
     if (A.c1 == CH_NONE && A.c2 == CH_NONE && A.aux_mode == AUX_NONE && A.coef_y == 1.0) return QP_HOP;
     if (A.c1 == CH_MPHI_M5INV && A.c2 == CH_NONE && A.aux_mode == AUX_NONE && A.coef_y == 1.0) return QP_A1;
     if (A.c1 == CH_M5INV && A.aux_mode == AUX_PLAIN && (A.c2 == CH_NONE || A.c2 == CH_M5INV_DAG))

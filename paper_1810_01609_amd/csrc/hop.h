@@ -227,6 +227,43 @@ __device__ __forceinline__ int block_first_site(const DslashArgs& A, int q, int 
   return ((t * g.Lz + z) * g.Ly + yb * rows) * g.Lxh + k * CB;
 }
 
+// What a workgroup reads of its right-hand side's tables and CG state, loaded
+// together at the start of the kernel: there the loads are scalar and overlap
+// the link stage; behind the first barrier each would be a vector load and one
+// more memory latency in the chain (about a microsecond of the 7-17 us a launch
+// takes on a small lattice).
+struct SlotIO {
+  char *in, *aux, *out, *r, *x, *p, *p2;
+  double alpha, alpha_prev;
+  int active, phase;
+};
+// AUX: the launch may have an aux field; R, X: it may update r, x
+template <bool AUX, bool R, bool X> __device__ __forceinline__ SlotIO slot_io(const DslashArgs& A, int slot) {
+  char *in = A.in[slot], *out = nullptr, *aux = nullptr, *r = nullptr, *x = nullptr, *p = nullptr, *p2 = nullptr;
+  double alpha = 0, alpha_prev = 0;
+  int active = 1, phase = 0;
+  if (A.active != nullptr) active = A.active[(size_t)slot * A.active_stride];
+  if (!R) out = A.out[slot];
+  if (AUX) aux = A.aux[slot];
+  if (AUX && !R && A.cg_update == 4) {  // aux is p, which alternates
+    p2 = A.cg_p2[slot];
+    phase = A.cg_st[slot].phase;
+  }
+  if (R || (X && A.cg_update == 3)) {
+    phase = A.cg_st[slot].phase;
+    alpha = A.cg_st[slot].alpha;
+    alpha_prev = A.cg_st[slot].alpha_prev;
+  }
+  if (R) r = A.cg_r[slot];
+  if (X && (A.cg_update == 1 || A.cg_update == 3)) {
+    x = A.cg_x[slot];
+    p = A.cg_p[slot];
+    p2 = A.cg_p2[slot];
+  }
+  if (AUX && !R && phase != 0) aux = p2;
+  return SlotIO{in, aux, out, r, x, p, p2, alpha, alpha_prev, active, phase};
+}
+
 // (RHS slot, site block) of logical workgroup lb in the launch's RHS order.
 // The XCD remap hands XCD k the logical range [k, k + 1) * gridDim.x / 8, so
 // order 2 keeps one eighth of the site blocks on each XCD and walks its RHS

@@ -112,7 +112,9 @@ struct mdwf_job {
   void* block = nullptr;
   size_t block_bytes = 0;
   bool keep_block = false;  // mdwf_solve: on mdwf_job_end the block goes back to the context's cache
-  std::vector<char*> fx, fr, fp, fpt, ft, fv, fxh, feh;  // fpt = M_phi p
+  // the two directions, and M_phi p (later v = M5^-T M^ p, whose launch no longer
+  // reads it) and t (later w of M^+)
+  std::vector<char*> fx, fr, fp, fp2, fu, ft, fxh, feh;
   std::vector<mdwf::CGState> st;
   std::vector<mdwf_cg_stats> stats;
   std::vector<int> finished;
@@ -149,7 +151,7 @@ void reset_tables(mdwf_ctx* c);
 
 // CG update fused into a stencil launch (see DslashArgs::cg_update)
 struct CgFuse {
-  PtrTab x, r, p;
+  PtrTab x, r, p, p2;
   const CGState* st;
   int mode;  // DslashArgs::cg_update
 };

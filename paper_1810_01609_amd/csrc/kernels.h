@@ -88,15 +88,16 @@ struct DslashArgs {
   int c1, c2, aux_mode, reduce;
   double coef_y;
   // CG update fused into the epilogue.  cg_update = 1: with q the combined
-  // value, x += alpha p, r -= alpha q, and the reduction takes |r|^2; q and
-  // `out` are not written.  2: the same without x (r -= alpha q only).  3:
-  // `out` is written as usual, and x += alpha p is applied on the launch's
-  // (checkerboard index, slice) pairs of x and p (fields of the other parity).
-  // x is FP64 for an FP64 kernel, FP32 otherwise.
+  // value, r -= alpha q, and the reduction takes |r|^2; q and `out` are not
+  // written; and x += alpha_prev p + alpha p2 where the state's phase is 1.  2:
+  // the same without x (r -= alpha q only).  3: `out` is written as usual, and
+  // the update of x is applied on the launch's (checkerboard index, slice)
+  // pairs of x and p (fields of the other parity).  4: no update; aux is p, or
+  // p2 in phase 1.  x is FP64 for an FP64 kernel, FP32 otherwise.
   int cg_update;
   PtrTab cg_x;
   PtrTab cg_r;
-  PtrTab cg_p;
+  PtrTab cg_p, cg_p2;
   const CGState* cg_st;
 };
 
@@ -147,25 +148,28 @@ struct BlasArgs {
   PtrTab b;
   PtrTab c;
   PtrTab d;
-  PtrTab e;
+  PtrTab e, f;
   CGState* st;      // [nslots] (CG kernels)
   double* partials; // [nslots][nblk]
   int nblk;         // filled by launcher
   int nslots;
-  double ca;        // beta of blas_cg_p without a CG state
+  double ca;        // beta of blas_cg_p without a CG state, alpha of blas_update
   CoefTab coef;    // [nslots] (k_cg_p, k_update)
   int nt_store;      // streaming stores
 };
 constexpr int kBlasThreads = 256;
 
-// CG: p = r + beta p and pt = M_phi p.   a=p b=r c=pt, coef.  beta and the
-// active flag come from the CG state; without one (st null) beta is A.ca, and
-// p is not read where that is zero.
+// CG: p' = r + beta p and pt = M_phi p'.   b=r c=pt, coef.  beta, the active
+// flag and the phase come from the CG state: in phase 1 p is a and p' goes to
+// d, in phase 0 the other way round.  Without a state (st null) p' goes to d,
+// beta is A.ca, and p (a) is not read where that is zero.
 hipError_t blas_cg_p(BlasArgs A, int ps, hipStream_t st);
 // Start of a reliable update, FP64 xh, eta^, z and pt, x of precision px:
-//   xh += x, x = 0 (without x, px < 0: xh stays), z = eta^ - xh, pt = M_phi xh.
-// a=x b=xh c=eta^ d=z e=pt, coef
-hipError_t blas_update(BlasArgs A, int px, hipStream_t st);
+//   x += ca p, xh += x, x = 0, z = eta^ - xh, pt = M_phi xh
+// with p in precision ps (an empty table: x is complete).  The plain FP64 solver
+// has no x of its own (an empty table): xh += ca p.
+// a=x b=xh c=eta^ d=z e=pt f=p, coef
+hipError_t blas_update(BlasArgs A, int ps, hipStream_t st);
 // b = a rounded from FP64 to precision pout; partials of |a|^2
 hipError_t blas_round(BlasArgs A, int pout, hipStream_t st);
 // partials of |a - b|^2 (|a|^2 where b's entry is null).  both precision p

@@ -57,7 +57,7 @@ SlotLayout slot_layout(const Geom& g, int ps) {
   L.fx = round_up(spinor_field_bytes(inner_x_prec(ps), g.L5, g.Vh), 256);
   L.fxh = ps == F64 ? 0 : round_up(spinor_field_bytes(F64, g.L5, g.Vh), 256);
   L.feh = round_up(spinor_field_bytes(F64, g.L5, g.Vh), 256);  // eta^_e, kept for reliable updates
-  L.total = 5 * L.fs + L.fx + L.fxh + L.feh;  // r, p, M_phi p, t, v
+  L.total = 5 * L.fs + L.fx + L.fxh + L.feh;  // r, p, p2, M_phi p / v, t / w
   return L;
 }
 
@@ -66,9 +66,10 @@ void iter_model(const Geom& g, int ps, double& bytes, double& flops) {
   const double ne = (double)g.Vh * g.L5;
   const double sb = spinor_site_bytes(ps), sx = spinor_site_bytes(inner_x_prec(ps));
   const double links = 8.0 * g.Vh * 12.0 * link_real_bytes(ps);
-  // A1 2, A2 3, B1 2, B2 with the fused update 5 spinor transfers + x read/write,
-  // 4 link sweeps; p = r + beta p with M_phi p 4 transfers
-  bytes = ne * sb * 12 + 2 * ne * sx + 4 * links + ne * 4 * sb;
+  // A1 2, A2 3, B1 2, B2 with the fused update 4 spinor transfers, 4 link sweeps;
+  // p = r + beta p with M_phi p 4 transfers; every second iteration two p and
+  // x read and x written
+  bytes = ne * sb * 11 + ne * (sb + sx) + 4 * links + ne * 4 * sb;
   // hop 1320/site x4, M_phi 72 x4 (A1, B1, B2, p-update), M5^-1 96 x4, M5 72,
   // xpay 48 x2, CG BLAS 192
   flops = ne * (4 * 1320.0 + 4 * 72 + 4 * 96 + 72 + 2 * 48 + 192);
@@ -191,13 +192,14 @@ struct One {
     rr = n.empty() ? 0.0 : n[0];
     return s;
   }
-  // p = r + beta p, pt = M_phi p in precision ps (beta = 0: p = r)
-  void direction(void* p, const void* r, void* pt, int ps, double beta) {
+  // out = r + beta p, pt = M_phi of it in precision ps (beta = 0: out = r)
+  void direction(const void* p, const void* r, void* out, void* pt, int ps, double beta) {
     if (e != hipSuccess) return;
     BlasArgs B = args();
     B.a = tab(p);
     B.b = tab(r);
     B.c = tab(pt);
+    B.d = tab(out);
     B.ca = beta;
     hipEvent_t ev;
     prof_begin(c, &ev);
@@ -205,8 +207,8 @@ struct One {
     // with the inner operator's launches, where M_phi p outside the loop is counted
     prof_end(c, MDWF_PROF_DSLASH_INNER, ne() * spinor_site_bytes(ps) * (beta != 0 ? 4 : 3), ev);
   }
-  // xh += x, x = 0 (x null: neither), z = eta_hat - xh, pt = M_phi xh
-  void update(void* x, int px, void* xh, const void* eta_hat, void* z, void* pt) {
+  // x += alpha p, xh += x, x = 0 (blas_update), z = eta_hat - xh, pt = M_phi xh
+  void update(void* x, const void* p, double alpha, int ps, void* xh, const void* eta_hat, void* z, void* pt) {
     if (e != hipSuccess) return;
     BlasArgs B = args();
     B.a = tab(x);
@@ -214,10 +216,15 @@ struct One {
     B.c = tab(eta_hat);
     B.d = tab(z);
     B.e = tab(pt);
+    B.f = tab(p);
+    B.ca = alpha;
     hipEvent_t ev;
     prof_begin(c, &ev);
-    e = blas_update(B, x != nullptr ? px : -1, c->stream);
-    prof_end(c, MDWF_PROF_BLAS, ne() * (192 * 4 + (x != nullptr ? 192 + 2 * spinor_site_bytes(px) : 0)), ev);
+    e = blas_update(B, ps, c->stream);
+    prof_end(c, MDWF_PROF_BLAS,
+             ne() * (192 * 4 + (x != nullptr ? 192 + 2 * 96 : p != nullptr ? 192 : 0) +
+                     (p != nullptr ? spinor_site_bytes(ps) : 0)),
+             ev);
   }
   double ne() const { return (double)geom.Vh * geom.L5; }
   BlasArgs args() const {
@@ -234,12 +241,13 @@ struct One {
   }
 };
 
-// rh (in T.t1) = M^+ (eta^ - M^ xh), with eta^_e kept by the job; xh += x and
-// x = 0 first where x is not null.  One streaming pass prepares z = eta^ - xh
-// and M_phi xh; then eta^ - M^ xh = z + 1/4 M5^-1 H t needs no pass of its own,
-// nor does v = M5^-T of it.
-static void true_residual(One& o, const FP64Temps& T, char* x, int px, char* xh, const char* eta_hat) {
-  o.update(x, px, xh, eta_hat, T.t1, T.t2);
+// rh (in T.t1) = M^+ (eta^ - M^ xh), with eta^_e kept by the job; x += alpha p,
+// xh += x and x = 0 first (p, x null: not).  One streaming pass prepares z =
+// eta^ - xh and M_phi xh; then eta^ - M^ xh = z + 1/4 M5^-1 H t needs no pass of
+// its own, nor does v = M5^-T of it.
+static void true_residual(One& o, const FP64Temps& T, void* x, const void* p, double alpha, int ps, char* xh,
+                          const char* eta_hat) {
+  o.update(x, p, alpha, ps, xh, eta_hat, T.t1, T.t2);
   o.prog(prog_A1(), T.t2, nullptr, T.t3);                    // t = M_phi M5^-1 H_oe M_phi xh
   Prog a2 = prog_A2(true, false);
   a2.coef = 0.25;
@@ -329,7 +337,10 @@ static mdwf_status reliable_update(mdwf_ctx* c, mdwf_job* j, int r, double& rr) 
   if (st != MDWF_OK) return st;
   One o{c, j->g, j->geom, CoefTab::single(j->coef)};
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
-  true_residual(o, T, j->ps != F64 ? j->fx[r] : nullptr, j->px, xh, j->feh[r]);
+  // an iteration that ended in phase 0 has not entered x yet
+  const CGState& s = j->st[r];
+  const char* due = s.phase == 0 && s.iters > 0 ? j->fp[r] : nullptr;
+  true_residual(o, T, j->ps != F64 ? j->fx[r] : nullptr, due, s.alpha, j->ps, xh, j->feh[r]);
   if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
   st = o.round_norm(T.t1, j->fr[r], j->ps, rr);
   j->stats[r].reliable_updates += 1;
@@ -409,9 +420,9 @@ extern "C" mdwf_status mdwf_job_begin(mdwf_ctx* c, const mdwf_gauge* g, const md
   for (int r = 0; r < nrhs; ++r) {
     j->fr.push_back(p); p += L.fs;
     j->fp.push_back(p); p += L.fs;
-    j->fpt.push_back(p); p += L.fs;
+    j->fp2.push_back(p); p += L.fs;
+    j->fu.push_back(p); p += L.fs;
     j->ft.push_back(p); p += L.fs;
-    j->fv.push_back(p); p += L.fs;
     j->fx.push_back(p); p += L.fx;
     j->fxh.push_back(L.fxh ? p : nullptr); p += L.fxh;
     j->feh.push_back(p); p += L.feh;
@@ -445,7 +456,7 @@ extern "C" mdwf_status mdwf_job_begin(mdwf_ctx* c, const mdwf_gauge* g, const md
     rr = bb;
     if (opts->use_initial_guess) {
       o.to_half(j->psi + ub * r, xh, 0);
-      true_residual(o, T, nullptr, -1, xh, j->feh[r]);
+      true_residual(o, T, nullptr, nullptr, 0.0, F64, xh, j->feh[r]);
       if (o.e != hipSuccess) { st = hip_err(c, o.e, "job setup"); break; }
       st = o.round_norm(T.t1, j->fr[r], j->ps, rr);
       if (st != MDWF_OK) break;
@@ -453,7 +464,7 @@ extern "C" mdwf_status mdwf_job_begin(mdwf_ctx* c, const mdwf_gauge* g, const md
       o.zero(xh, spinor_field_bytes(F64, geom.L5, geom.Vh));
     }
     if (j->ps != F64) o.zero(j->fx[r], spinor_field_bytes(j->px, geom.L5, geom.Vh));
-    o.direction(j->fp[r], j->fr[r], j->fpt[r], j->ps, 0.0);  // p = r
+    o.direction(nullptr, j->fr[r], j->fp[r], j->fu[r], j->ps, 0.0);  // p = r
     if (o.e != hipSuccess) { st = hip_err(c, o.e, "job setup"); break; }
     CGState& s = j->st[r];
     s.active = 1;
@@ -516,25 +527,25 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
   gather();
   if (slots.empty() || iters == 0) return MDWF_OK;
 
-  PtrTab X, R, P, PT, T, V;
+  PtrTab X, R, P, P2, U, T;
   CoefTab coef;
   CGState* S_d = nullptr;
   double* pd = nullptr;
   double* pb = nullptr;
   auto build = [&]() -> mdwf_status {
     const int n = (int)slots.size();
-    std::vector<const void*> x(n), r(n), p(n), pt(n), t(n), v(n);
+    std::vector<const void*> x(n), r(n), p(n), p2(n), u(n), t(n);
     std::vector<Coef5> cf(n);
     for (int i = 0; i < n; ++i) {
       mdwf_job* j = slots[i].job;
       const int k = slots[i].r;
-      x[i] = j->fx[k]; r[i] = j->fr[k]; p[i] = j->fp[k]; pt[i] = j->fpt[k];
-      t[i] = j->ft[k]; v[i] = j->fv[k];
+      x[i] = j->fx[k]; r[i] = j->fr[k]; p[i] = j->fp[k]; p2[i] = j->fp2[k];
+      u[i] = j->fu[k]; t[i] = j->ft[k];
       cf[i] = j->coef;
     }
     LaunchTables lt;
-    if (!make_tables(c, {x, r, p, pt, t, v}, cf, lt)) return set_err(c, MDWF_EHIP, "mdwf_job_step: table upload");
-    X = lt.tab[0]; R = lt.tab[1]; P = lt.tab[2]; PT = lt.tab[3]; T = lt.tab[4]; V = lt.tab[5];
+    if (!make_tables(c, {x, r, p, p2, u, t}, cf, lt)) return set_err(c, MDWF_EHIP, "mdwf_job_step: table upload");
+    X = lt.tab[0]; R = lt.tab[1]; P = lt.tab[2]; P2 = lt.tab[3]; U = lt.tab[4]; T = lt.tab[5];
     coef = lt.coef;
     mdwf_status s2 = ensure(c, c->states, n * sizeof(CGState));
     if (s2 == MDWF_OK) s2 = ensure(c, c->partials_d, (size_t)n * ntiles * sizeof(double));
@@ -566,11 +577,13 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
 
   const int stride = (int)(sizeof(CGState) / sizeof(int));
   const double ne = (double)geom.Vh * geom.L5;
-  // x += alpha p rides in the first M^+ launch (B1), whose hop leaves memory
-  // bandwidth unused, rather than in the second (B2), already bound by its
-  // streams of r and x: single RHS FP16 4 % and 12 fused FP32 RHS 1.4 % faster
-  // per iteration on 32^3 x 64, L5 = 12; the same arithmetic, bitwise the same
-  // solve (MDWF_X_IN_B1=0 keeps it in B2)
+  // x is updated every second iteration with two directions at once (the same
+  // sums; 24^3 x 64 x 16 FP16 solve 768 -> 730 ms, 16^3 x 32 x 12 FP32 83.9 ->
+  // 79.5 ms against every iteration), in
+  // the first M^+ launch (B1), whose hop leaves memory bandwidth unused, rather
+  // than in the second (B2), bound by its streams of r (MDWF_X_IN_B1=0 puts it
+  // there; the same arithmetic, bitwise the same solve).  The second direction
+  // takes no memory: M_phi p is dead once A1 has read it, so A2 writes v over it.
   const char* xe = getenv("MDWF_X_IN_B1");
   const bool x_in_b1 = !(xe != nullptr && xe[0] == '0');
   // One CG iteration is seven launches whose arguments stay fixed while the
@@ -612,27 +625,29 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
     for (int i = 0; i < n; ++i) it0[i] = slots[i].job->st[slots[i].r].iters;
     prof_chunk_begin(c, chunk);
     auto iteration = [&]() -> hipError_t {
-      hipError_t e = run_prog(c, j0->g, geom, ps, prog_A1(), PT, PtrTab(), T, coef, n, act, stride, nullptr, 0,
+      hipError_t e = run_prog(c, j0->g, geom, ps, prog_A1(), U, PtrTab(), T, coef, n, act, stride, nullptr, 0,
                               MDWF_PROF_DSLASH_INNER, true);
-      if (e == hipSuccess)
-        e = run_prog(c, j0->g, geom, ps, prog_A2(true, true), T, P, V, coef, n, act, stride, pd, ntiles,
-                     MDWF_PROF_DSLASH_INNER, true);
+      if (e == hipSuccess) {  // u = M^ p from the current p, v over M_phi p
+        const CgFuse fa{PtrTab(), PtrTab(), P, P2, S_d, 4};
+        e = run_prog(c, j0->g, geom, ps, prog_A2(true, true), T, P, U, coef, n, act, stride, pd, ntiles,
+                     MDWF_PROF_DSLASH_INNER, true, &fa);
+      }
       hipEvent_t ev;
       if (e == hipSuccess) {  // alpha = rho / <p, A p>, <p, A p> = |M^ p|^2 from A2
         prof_begin(c, &ev);
         e = scalar_cg_alpha(S_d, pd, ntiles, n, c->stream);
         prof_end(c, MDWF_PROF_SCALAR, 0, ev);
       }
-      if (e == hipSuccess) {  // w_o = M_phi^T M5^-T H^+_oe v (and x += alpha p)
-        const CgFuse fx{X, PtrTab(), P, S_d, 3};
-        e = run_prog(c, j0->g, geom, ps, prog_B1(), V, PtrTab(), T, coef, n, act, stride, nullptr, 0,
+      if (e == hipSuccess) {  // w_o = M_phi^T M5^-T H^+_oe v (and the update of x)
+        const CgFuse fx{X, PtrTab(), P, P2, S_d, 3};
+        e = run_prog(c, j0->g, geom, ps, prog_B1(), U, PtrTab(), T, coef, n, act, stride, nullptr, 0,
                      MDWF_PROF_DSLASH_INNER, true, x_in_b1 ? &fx : nullptr);
       }
-      if (e == hipSuccess) {  // q = M^+ M^ p, fused with r -= alpha q, |r|^2 (and x += alpha p)
-        const CgFuse fz{X, R, P, S_d, x_in_b1 ? 2 : 1};
+      if (e == hipSuccess) {  // q = M^+ M^ p, fused with r -= alpha q, |r|^2 (and the update of x)
+        const CgFuse fz{X, R, P, P2, S_d, x_in_b1 ? 2 : 1};
         Prog b2 = prog_B2();
         b2.reduce = 1;
-        e = run_prog(c, j0->g, geom, ps, b2, T, V, T, coef, n, act, stride, pd, ntiles, MDWF_PROF_DSLASH_INNER,
+        e = run_prog(c, j0->g, geom, ps, b2, T, U, T, coef, n, act, stride, pd, ntiles, MDWF_PROF_DSLASH_INNER,
                      false, &fz);
       }
       if (e == hipSuccess) {
@@ -644,7 +659,7 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
         BlasArgs B{};
         B.g = geom;
         B.nslots = n;
-        B.a = P; B.b = R; B.c = PT;
+        B.a = P; B.b = R; B.c = U; B.d = P2;
         B.st = S_d;
         B.coef = coef;
         B.nt_store = streaming_stores(geom, ps, n);
@@ -731,7 +746,8 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
           // continue: beta from the true residual, p = r + beta p
           const double beta = rr / s.rho;
           One o{c, j->g, geom, CoefTab::single(j->coef)};
-          o.direction(j->fp[r], j->fr[r], j->fpt[r], ps, beta);
+          o.direction(s.phase == 0 ? j->fp[r] : j->fp2[r], j->fr[r], j->fp[r], j->fu[r], ps, beta);
+          s.phase = 0;
           if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
           s.rho = rr;
           s.rho_new = rr;
