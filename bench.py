@@ -39,7 +39,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("dslash.hip", "dev_common.h"):
+    for f in ("dslash.hip", "dslash_quad.hip", "hop.h", "dev_common.h"):
         with open(os.path.join(ROOT, "paper_1810_01609_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -592,7 +592,7 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS if achieved else None,
             "traffic": traffic,
-            "kernel": "dslash5_kernel (fused hop + 5th-dim, inner precision)",
+            "kernel": "fused stencil (hop + 5th-dim, inner precision): dslash_quad_kernel, or dslash5_kernel for FP64",
             "avg_launch_ms": avg_ms,
             "algorithmic_bytes_per_launch": bytes_per_launch,
             "launches": d["launches"],

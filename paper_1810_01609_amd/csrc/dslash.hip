@@ -5,10 +5,12 @@
 // on slice s of site cbl (spin projection to half-spinors, SU(3) x two colour
 // vectors, reconstruction, 8 directions), with the links rebuilt from 12
 // stored reals.  The site-local 5th-dimension operators M_phi, M5, M5^-1
-// (and transposes) that surround the hop in the even-odd operator are fused
-// as a prologue (M_phi on the input, applied while loading neighbours) and
-// as epilogue chains that run in LDS on whole fifth-dimension columns.  The
-// xpay of M^ = 1 - (...) and the |.|^2 reduction CG needs are fused too.
+// (and transposes) that follow the hop in the even-odd operator are fused
+// as epilogue chains that run in LDS on whole fifth-dimension columns; the
+// M_phi in front of a hop is applied by the kernel that writes its input.
+// The xpay of M^ = 1 - (...) and the |.|^2 reduction CG needs are fused too.
+// FP64, an L5 that is no multiple of 4 and the split hop run here; the other
+// types run in dslash_quad.hip where dslash_quad_ok allows.
 // Fusing these steps into one pass over the fields, with the operator never
 // stored as a matrix, is the approach the paper's performance discussion
 // takes for this operator (Current State of the Art, Performance related).
@@ -272,8 +274,7 @@ __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldD
 // the eight directions (mu-major, forward then backward, the order of the
 // one-at-a-time form, so the sums round identically) are taken in batches of
 // NB; a batch first loads its NB neighbours (NB loads in flight per thread),
-// then projects, multiplies and accumulates them one by one.  Used for the
-// staged hop without the M_phi prologue.
+// then projects, multiplies and accumulates them one by one.
 // ---------------------------------------------------------------------------
 template <int P> struct NbrLoad {
   using R = typename PrecTraits<P>::Real;
@@ -371,9 +372,8 @@ __device__ __forceinline__ void hop_batches(const FieldDesc& f, const char* in, 
 }
 
 // Neighbours loaded together per thread (0: the one-at-a-time form) in the
-// staged hop without the M_phi prologue; the build options MDWF_HOP_BATCH and
-// MDWF_HOP_BATCH_CGU (launches with the fused CG update) set it.  FP64 stays
-// at one.
+// staged hop; the build options MDWF_HOP_BATCH and MDWF_HOP_BATCH_CGU
+// (launches with the fused CG update) set it.  FP64 stays at one.
 #ifndef MDWF_HOP_BATCH
 #define MDWF_HOP_BATCH 2
 #endif
