@@ -384,8 +384,8 @@ int streaming_stores(const Geom& g, int prec, int nslots) {
 
 static std::string tune_key(const Geom& g, int prec, const Prog& p, int nslots, int cg) {
   char buf[256];
-  snprintf(buf, sizeof(buf), "dslash5 p%d h%d d%d pr0 c%d.%d a%d r%d u%d s%d L%dx%dx%dx%d L5=%d n%d gfx950",
-           prec, (int)p.hop, (int)p.dag, p.c1, p.c2, p.aux, p.reduce, (int)cg,
+  snprintf(buf, sizeof(buf), "dslash5 p%d h%d d%d pr%d c%d.%d a%d r%d u%d s%d L%dx%dx%dx%d L5=%d n%d gfx950",
+           prec, (int)p.hop, (int)p.dag, (int)p.pro, p.c1, p.c2, p.aux, p.reduce, (int)cg,
            p.hop ? default_stage() : 0, g.Lx, g.Ly, g.Lz, g.Lt, g.L5, nslots);
   std::string k = buf;
   if (p.split != 0) k += " x" + std::to_string(p.split);
@@ -503,6 +503,7 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   traversal(geom, prec, nslots, A.order_bt, A.order_yb, A.rhs_order);
   A.nt_store = streaming_stores(geom, prec, nslots);
   A.split_mask = pr.split;
+  A.pro = pr.pro;
   if (fuse != nullptr) {
     A.cg_update = fuse->mode;
     A.cg_x = fuse->x;

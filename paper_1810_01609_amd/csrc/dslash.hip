@@ -7,10 +7,12 @@
 // stored reals.  The site-local 5th-dimension operators M_phi, M5, M5^-1
 // (and transposes) that follow the hop in the even-odd operator are fused
 // as epilogue chains that run in LDS on whole fifth-dimension columns; the
-// M_phi in front of a hop is applied by the kernel that writes its input.
-// The xpay of M^ = 1 - (...) and the |.|^2 reduction CG needs are fused too.
-// FP64, an L5 that is no multiple of 4 and the split hop run here; the other
-// types run in dslash_quad.hip where dslash_quad_ok allows.
+// M_phi in front of a hop is applied by the kernel that writes its input, or,
+// for the operators on 16-bit user fields, here as a prologue on each
+// neighbour.  The xpay of M^ = 1 - (...) and the |.|^2 reduction CG needs are fused too.
+// FP64, an L5 that is no multiple of 4, the split hop and the launches with the
+// prologue run here; the others run in dslash_quad.hip where dslash_quad_ok
+// allows.
 // Fusing these steps into one pass over the fields, with the operator never
 // stored as a matrix, is the approach the paper's performance discussion
 // takes for this operator (Current State of the Art, Performance related).
@@ -162,9 +164,42 @@ __device__ __forceinline__ void stage_fill(const DslashArgs& A, Stage<typename P
   }
 }
 
-template <int P, bool DAG, int MU, bool SPLIT>
-__device__ __forceinline__ void hop_dir_packed(const FieldDesc& f, const char* in, int s, Cplx<float> acc[4][3],
-                                               Stage<float> st, int CB, int cbl) {
+// load_bidiag (dag = 0) for 16-bit storage, with the three sites' scales
+// divided by their maximum m, which is returned: the combination stays O(1)
+// whatever the field's magnitude, so it can be rounded back to 16 bits.
+//
+// M_phi psi stays in FP32 until it is projected, and only the half-spinors are
+// rounded to 16 bits.  A 16-bit field of M_phi psi, projected in 16 bits, would
+// let the quad stencil take these launches, but loses what two nearly equal
+// spins differ by.
+template <int P>
+__device__ __forceinline__ float load_bidiag_norm(const char* base, const FieldDesc& f, int cb, int s, float a, float b,
+                                                  float mq, float v[24]) {
+  int s_up = s - 1, s_dn = s + 1;
+  float b_up = b, b_dn = b;
+  if (s_up < 0) { s_up = f.L5 - 1; b_up = -b * mq; }
+  if (s_dn >= f.L5) { s_dn = 0; b_dn = -b * mq; }
+  using IO = SpinorIO<P>;
+  const float c0 = IO::scale(base, f, cb, s), cu = IO::scale(base, f, cb, s_up), cd = IO::scale(base, f, cb, s_dn);
+  const float m = fmaxf(c0, fmaxf(cu, cd));
+  const float im = m >= kMinNormalF32 ? 1.0f / m : 0.f;  // stored scales are 0 or normal
+#pragma unroll
+  for (int g = 0; g < 3; ++g) IO::group(base, f, cb, s, g, a * c0 * im, v + 8 * g);
+  float t[16];
+  IO::group(base, f, cb, s_up, 0, b_up * cu * im, t);
+  IO::group(base, f, cb, s_up, 1, b_up * cu * im, t + 8);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) v[k] += t[k];
+  IO::group(base, f, cb, s_dn, 1, b_dn * cd * im, t);
+  IO::group(base, f, cb, s_dn, 2, b_dn * cd * im, t + 8);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) v[12 + k] += t[4 + k];
+  return m;
+}
+
+template <int P, bool DAG, bool PRO, int MU, bool SPLIT>
+__device__ __forceinline__ void hop_dir_packed(const FieldDesc& f, const char* in, int s, const Coef5& c,
+                                               Cplx<float> acc[4][3], Stage<float> st, int CB, int cbl) {
   using K = Packed<P>;
   using T2 = typename K::T2;
   constexpr int SF = DAG ? +1 : -1;
@@ -178,13 +213,27 @@ __device__ __forceinline__ void hop_dir_packed(const FieldDesc& f, const char* i
     }
     T2 h[2][3];
     float sc;
-    uint32_t q[12];
-    SpinorIO<P>::load_packed(in, f, nb, s, q, sc);
-    T2 psi[4][3];
+    if constexpr (PRO) {
+      float v[24];
+      sc = load_bidiag_norm<P>(in, f, nb, s, (float)c.b5, (float)c.c5, (float)c.mq, v);
+      Cplx<float> pf[4][3], hf[2][3];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = __builtin_bit_cast(T2, q[k]);
-    if (fb == 0) project<MU, SF>(psi, h);
-    else project<MU, SB>(psi, h);
+      for (int k = 0; k < 12; ++k) pf[k / 3][k % 3] = {v[2 * k], v[2 * k + 1]};
+      if (fb == 0) project<MU, SF>(pf, hf);
+      else project<MU, SB>(pf, hf);
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) h[k][a] = K::make(hf[k][a].re, hf[k][a].im);
+    } else {
+      uint32_t q[12];
+      SpinorIO<P>::load_packed(in, f, nb, s, q, sc);
+      T2 psi[4][3];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = __builtin_bit_cast(T2, q[k]);
+      if (fb == 0) project<MU, SF>(psi, h);
+      else project<MU, SB>(psi, h);
+    }
     Cplx<float> w[2][3];
     colour_mul_packed<P>(lnk, MU + 4 * fb, CB, cbl, h, w);
     if (fb == 0) accumulate_scaled<MU, SF>(acc, w, sc);
@@ -193,9 +242,9 @@ __device__ __forceinline__ void hop_dir_packed(const FieldDesc& f, const char* i
   }
 }
 
-template <int P, bool DAG, bool STAGE, int MU, bool SPLIT>
+template <int P, bool DAG, bool PRO, bool STAGE, int MU, bool SPLIT>
 __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldDesc& f, const char* in, int cb, int s,
-                                        const int X[4], Cplx<typename PrecTraits<P>::Real> acc[4][3],
+                                        const int X[4], const Coef5& c, Cplx<typename PrecTraits<P>::Real> acc[4][3],
                                         Stage<typename PrecTraits<P>::Real> st, int CB, int cbl) {
   using R = typename PrecTraits<P>::Real;
   const Geom& g = A.g;
@@ -233,7 +282,7 @@ __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldD
     // product unscaled; the site's scale (and 1/32767) joins in the
     // accumulation, one multiply-add per result instead of one multiply per
     // loaded value
-    constexpr bool kI16Raw = P == I16 && STAGE;
+    constexpr bool kI16Raw = P == I16 && STAGE && !PRO;
     float sc16 = 1.f;
     if constexpr (kI16Raw) {
       uint32_t q[12];
@@ -243,7 +292,8 @@ __device__ __forceinline__ void hop_dir_single(const DslashArgs& A, const FieldD
       for (int k = 0; k < 12; ++k)
         psi[k / 3][k % 3] = {(R)(int16_t)(uint16_t)(q[k] & 0xffffu), (R)(int16_t)(uint16_t)(q[k] >> 16)};
     } else {
-      SpinorIO<P>::load(in, f, nb, s, v);
+      if constexpr (PRO) load_bidiag<P>(in, f, nb, s, f.L5, (R)c.b5, (R)c.c5, (R)c.mq, false, v);
+      else SpinorIO<P>::load(in, f, nb, s, v);
 #pragma unroll
       for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = {v[2 * k], v[2 * k + 1]};
     }
@@ -372,7 +422,7 @@ __device__ __forceinline__ void hop_batches(const FieldDesc& f, const char* in, 
 }
 
 // Neighbours loaded together per thread (0: the one-at-a-time form) in the
-// staged hop; the build options MDWF_HOP_BATCH and MDWF_HOP_BATCH_CGU
+// staged hop without the M_phi prologue; the build options MDWF_HOP_BATCH and MDWF_HOP_BATCH_CGU
 // (launches with the fused CG update) set it.  FP64 stays at one.
 #ifndef MDWF_HOP_BATCH
 #define MDWF_HOP_BATCH 2
@@ -380,15 +430,15 @@ __device__ __forceinline__ void hop_batches(const FieldDesc& f, const char* in, 
 #ifndef MDWF_HOP_BATCH_CGU
 #define MDWF_HOP_BATCH_CGU 0
 #endif
-template <int P, bool CGU> constexpr int kHopBatch =
-    P == F64 ? 0 : CGU ? MDWF_HOP_BATCH_CGU : MDWF_HOP_BATCH;
+template <int P, bool PRO, bool CGU> constexpr int kHopBatch =
+    (P == F64 || PRO) ? 0 : CGU ? MDWF_HOP_BATCH_CGU : MDWF_HOP_BATCH;
 
-template <int P, bool DAG, bool STAGE, int MU, bool SPLIT>
+template <int P, bool DAG, bool PRO, bool STAGE, int MU, bool SPLIT>
 __device__ __forceinline__ void hop_dir(const DslashArgs& A, const FieldDesc& f, const char* in, int cb, int s,
-                                        const int X[4], Cplx<typename PrecTraits<P>::Real> acc[4][3],
+                                        const int X[4], const Coef5& c, Cplx<typename PrecTraits<P>::Real> acc[4][3],
                                         Stage<typename PrecTraits<P>::Real> st, int CB, int cbl) {
-  if constexpr (STAGE && Packed<P>::enabled) hop_dir_packed<P, DAG, MU, SPLIT>(f, in, s, acc, st, CB, cbl);
-  else hop_dir_single<P, DAG, STAGE, MU, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
+  if constexpr (STAGE && Packed<P>::enabled) hop_dir_packed<P, DAG, PRO, MU, SPLIT>(f, in, s, c, acc, st, CB, cbl);
+  else hop_dir_single<P, DAG, PRO, STAGE, MU, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
 }
 
 // ---------------------------------------------------------------------------
@@ -550,7 +600,7 @@ template <int P> constexpr int kMaxThreads = P == F64 ? 512 : 1024;
 // implies (FP32 at 6 spills and ran 9 % slower).
 template <int P> constexpr int kWavesPerEU = (P == F16 || P == BF16 || P == I16) ? 5 : kMaxThreads<P> / 256;
 
-template <int P, bool HOP, bool DAG, bool STAGE, bool CGU, bool SPLIT>
+template <int P, bool HOP, bool DAG, bool PRO, bool STAGE, bool CGU, bool SPLIT>
 __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<P>))) void dslash5_kernel(
     DslashArgs A) {
   using R = typename PrecTraits<P>::Real;
@@ -602,13 +652,13 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int b = 0; b < 3; ++b) acc[a][b] = {0, 0};
       const char* in = io.in;
-      if constexpr (STAGE && kHopBatch<P, CGU> > 0) {
-        hop_batches<P, DAG, SPLIT, kHopBatch<P, CGU>, 0>(f, in, s, acc, st, CB, cbl);
+      if constexpr (STAGE && kHopBatch<P, PRO, CGU> > 0) {
+        hop_batches<P, DAG, SPLIT, kHopBatch<P, PRO, CGU>, 0>(f, in, s, acc, st, CB, cbl);
       } else {
-        hop_dir<P, DAG, STAGE, 0, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
-        hop_dir<P, DAG, STAGE, 1, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
-        hop_dir<P, DAG, STAGE, 2, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
-        hop_dir<P, DAG, STAGE, 3, SPLIT>(A, f, in, cb, s, X, acc, st, CB, cbl);
+        hop_dir<P, DAG, PRO, STAGE, 0, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
+        hop_dir<P, DAG, PRO, STAGE, 1, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
+        hop_dir<P, DAG, PRO, STAGE, 2, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
+        hop_dir<P, DAG, PRO, STAGE, 3, SPLIT>(A, f, in, cb, s, X, c, acc, st, CB, cbl);
       }
 #pragma unroll
       for (int k = 0; k < 12; ++k) {
@@ -701,9 +751,9 @@ __global__ __launch_bounds__(kMaxThreads<P>) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 // launcher
 // ---------------------------------------------------------------------------
-template <int P, bool HOP, bool DAG, bool STAGE, bool CGU = false, bool SPLIT = false>
+template <int P, bool HOP, bool DAG, bool PRO, bool STAGE, bool CGU = false, bool SPLIT = false>
 static hipError_t launch_t(const DslashArgs& A, int threads, size_t smem, int grid, hipStream_t st) {
-  auto k = dslash5_kernel<P, HOP, DAG, STAGE, CGU, SPLIT>;
+  auto k = dslash5_kernel<P, HOP, DAG, PRO, STAGE, CGU, SPLIT>;
   if (smem > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -719,10 +769,18 @@ static hipError_t launch_s(const DslashArgs& A, bool dag, int threads, size_t sm
   // the CG update is fused into M^+ only: r (and x) into its second launch
   // (B2), x alone possibly into its first (B1); M^ takes p by its phase
   if (dag && (A.cg_update == 1 || A.cg_update == 2))
-    return launch_t<P, true, true, STAGE, true>(A, threads, smem, grid, st);
+    return launch_t<P, true, true, false, STAGE, true>(A, threads, smem, grid, st);
   if (A.cg_update != 0 && !(dag ? A.cg_update == 3 : A.cg_update == 4)) return hipErrorInvalidValue;
-  if (dag) return launch_t<P, true, true, STAGE>(A, threads, smem, grid, st);
-  return launch_t<P, true, false, STAGE>(A, threads, smem, grid, st);
+  if (A.pro) {  // 16-bit storage only
+    if constexpr (P == F64 || P == F32) {
+      return hipErrorInvalidValue;
+    } else {
+      if (dag || A.cg_update != 0) return hipErrorInvalidValue;
+      return launch_t<P, true, false, true, STAGE>(A, threads, smem, grid, st);
+    }
+  }
+  if (dag) return launch_t<P, true, true, false, STAGE>(A, threads, smem, grid, st);
+  return launch_t<P, true, false, false, STAGE>(A, threads, smem, grid, st);
 }
 
 template <int P>
@@ -730,10 +788,10 @@ static hipError_t launch_p(const DslashArgs& A, bool hop, bool dag, int threads,
                            hipStream_t st) {
   if (A.split_mask != 0) {
     // the split interior exists for the plain staged hop only
-    if (!hop || dag || !A.stage || A.cg_update) return hipErrorInvalidValue;
-    return launch_t<P, true, false, true, false, true>(A, threads, smem, grid, st);
+    if (!hop || dag || A.pro || !A.stage || A.cg_update) return hipErrorInvalidValue;
+    return launch_t<P, true, false, false, true, false, true>(A, threads, smem, grid, st);
   }
-  if (!hop) return A.cg_update ? hipErrorInvalidValue : launch_t<P, false, false, false>(A, threads, smem, grid, st);
+  if (!hop) return A.cg_update ? hipErrorInvalidValue : launch_t<P, false, false, false, false>(A, threads, smem, grid, st);
   if (A.stage) return launch_s<P, true>(A, dag, threads, smem, grid, st);
   return launch_s<P, false>(A, dag, threads, smem, grid, st);
 }

@@ -761,11 +761,12 @@ template <int P> hipError_t launch_qp(const DslashArgs& A, bool dag, int threads
 
 }  // namespace
 
-// The launches this kernel takes: the staged hop without the split, 32- and 16-bit storage, L5 a multiple of 4, neighbour offsets
+// The launches this kernel takes: the staged hop without the split and without
+// the M_phi prologue, 32- and 16-bit storage, L5 a multiple of 4, neighbour offsets
 // that fit 32 bits (fields under 4 GB), and a second chain's totals that fit
 // the stage they overlay (all but L5 = 32 of FP32 and int16).
 bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag) {
-  if (!hop || !A.stage || A.split_mask != 0 || prec == F64 || A.g.L5 % 4 != 0 || kSiteTile != 16) return false;
+  if (!hop || A.pro || !A.stage || A.split_mask != 0 || prec == F64 || A.g.L5 % 4 != 0 || kSiteTile != 16) return false;
   if (spinor_field_bytes(prec, A.g.L5, A.g.Vh) >= ((size_t)1 << 32)) return false;
   const size_t stage = prec == F32 || prec == I16 ? stage_bytes<F32>(16) : stage_bytes<F16>(16);
   if (totals_bytes(16, A.g.L5) > stage) return false;

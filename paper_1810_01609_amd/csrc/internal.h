@@ -35,6 +35,7 @@ struct Prog {
   double coef;
   int out_par;
   int split = 0;  // split_mask of the domain-decomposed interior hop
+  bool pro = false;  // M_phi on the hop's input
 };
 
 }  // namespace mdwf

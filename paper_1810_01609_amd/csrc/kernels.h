@@ -51,7 +51,7 @@ enum AuxMode : int {
   AUX_M5DAG = 3,  // + M5^T aux
 };
 
-// out = c2( coef_y * c1( H (or H^dag) in ) + auxterm )
+// out = c2( coef_y * c1( H (or H^dag) [M_phi] in ) + auxterm )
 // with an optional |.|^2 reduction of the value before c2.
 struct DslashArgs {
   Geom g;
@@ -86,6 +86,7 @@ struct DslashArgs {
   uint32_t m_bpp, m_bt, m_lz, m_ntb, m_nslots, m_nblk, m_per;
   int split_mask;          // bit mu: hops across the mu boundary come from halo buffers (skipped here)
   int c1, c2, aux_mode, reduce;
+  int pro;                 // 1: M_phi on the input of the hop (16-bit storage, no CG update)
   double coef_y;
   // CG update fused into the epilogue.  cg_update = 1: with q the combined
   // value, r -= alpha q, and the reduction takes |r|^2; q and `out` are not
@@ -191,8 +192,7 @@ hipError_t scalar_cg_beta(CGState* st_, const double* partials, int n, int nslot
 // precision p (an empty table: that parity is not wanted)
 hipError_t layout_user_to_half(const Geom& g, const PtrTab& user, const PtrTab& even, const PtrTab& odd, int p,
                                int nslots, hipStream_t st);
-// one parity of it, as half and phi = M_phi of it (formed before any rounding
-// to 16-bit storage); half may be empty
+// one parity of it, as half and phi = M_phi of it (FP64 and FP32)
 hipError_t layout_user_to_half_phi(const Geom& g, const PtrTab& user, const PtrTab& half, const PtrTab& phi,
                                    const CoefTab& coef, int par, int p, int nslots, hipStream_t st);
 // half-fields of precision p (a null entry: zeros) -> user field, both parities

@@ -89,11 +89,11 @@ __global__ __launch_bounds__(kConvThreads) void k_user_to_half(Geom g, PtrTab us
 
 // One parity with M_phi applied: whole columns of a 16-site tile per
 // workgroup, so that slices s - 1 and s + 1 are in LDS beside s; M_phi is
-// formed in the field's arithmetic from values rounded to that arithmetic (not
-// to 16-bit storage).  The hop then reads a field that already
-// holds M_phi psi; forming it on each of its eight neighbours took a 32^3 x 64
-// x 12 hop from 700 to 1310 us in FP32 and a 24^3 x 64 x 16 one of two RHS from
-// 504 to 1102 us in FP16, against one more half-field written here.
+// formed in the field's arithmetic from values rounded to that arithmetic.  The
+// hop then reads a field that already holds M_phi psi; forming it on each of its
+// eight neighbours took a 32^3 x 64 x 12 hop from 700 to 1310 us in FP32, against
+// one more half-field written here.  FP64 and FP32: 16-bit storage would round
+// M_phi psi.
 template <int P>
 __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, PtrTab user, PtrTab half, PtrTab phi,
                                                           CoefTab coef, int par) {
@@ -544,9 +544,6 @@ hipError_t layout_user_to_half_phi(const Geom& g, const PtrTab& user, const PtrT
   switch (p) {
     case F64: return user_to_half_phi<F64>(g, user, half, phi, coef, par, nslots, st);
     case F32: return user_to_half_phi<F32>(g, user, half, phi, coef, par, nslots, st);
-    case F16: return user_to_half_phi<F16>(g, user, half, phi, coef, par, nslots, st);
-    case BF16: return user_to_half_phi<BF16>(g, user, half, phi, coef, par, nslots, st);
-    case I16: return user_to_half_phi<I16>(g, user, half, phi, coef, par, nslots, st);
   }
   return hipErrorInvalidValue;
 }

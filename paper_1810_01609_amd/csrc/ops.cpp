@@ -11,7 +11,9 @@ namespace mdwf {
 
 // The programs that compose the operators (see DslashArgs); the inputs of the
 // first three hold M_phi of the field already (the conversion from the user
-// layout, the CG's p-update and the reliable update write it):
+// layout, the CG's p-update and the reliable update write it), or the hop
+// applies it (with_phi: mdwf_dslash on 16-bit storage, where a stored M_phi psi
+// would round it to 16 bits before the projection):
 //   D    : M5 aux - 1/2 H in                          (aux M5, coef -1/2)
 //   A1   : t_o = M_phi M5^-1 H_oe in_e                (c1 M_phi M5^-1)
 //   PRE  : out = M5^-1 (aux + 1/2 H in)               (aux, c2 M5^-1)
@@ -29,6 +31,10 @@ Prog prog_A2(bool with_c2, bool reduce) {
 Prog prog_B1() { return Prog{true, true, CH_MPHIDAG_M5INVDAG, CH_NONE, AUX_NONE, 0, 1.0, 1}; }
 Prog prog_B2() { return Prog{true, true, CH_MPHI_DAG, CH_NONE, AUX_M5DAG, 0, -0.25, 0}; }
 Prog prog_PRE(int par) { return Prog{true, false, CH_NONE, CH_M5INV, AUX_PLAIN, 0, 0.5, par}; }
+static Prog with_phi(Prog p) {
+  p.pro = true;
+  return p;
+}
 Prog prog_HOP(int par, bool dag) { return Prog{true, dag, CH_NONE, CH_NONE, AUX_NONE, 0, 1.0, par}; }
 Prog prog_5D(int chain) { return Prog{false, false, chain, CH_NONE, AUX_NONE, 0, 1.0, 0}; }
 
@@ -107,6 +113,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
   const PtrTab& NUL = t.NUL;
   const CoefTab& coef = t.coef;
   const int cls = prec == MDWF_F64 ? MDWF_PROF_DSLASH_F64 : MDWF_PROF_DSLASH_INNER;
+  const bool pro = prec != MDWF_F64 && prec != MDWF_F32;  // M_phi in the hop, not in a stored field
   hipError_t e = hipSuccess;
   hipEvent_t ev;
   auto conv_in = [&](const PtrTab& even, const PtrTab& odd) {
@@ -126,9 +133,27 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
     if (e != hipSuccess) return;
     e = run_prog(c, g, geom, prec, p, i, a, o, coef, nrhs, nullptr, 0, nullptr, 0, cls, i != o && a != o);
   };
+  // IE = the even half, T = M_phi M5^-1 H_oe M_phi of it
+  auto mhat_first = [&]() {
+    if (pro) {
+      conv_in(IE, PtrTab());
+      run(with_phi(prog_A1()), IE, PtrTab(), T);
+    } else {
+      conv_phi(0, IE, IO);
+      run(prog_A1(), IO, PtrTab(), T);
+    }
+  };
   PtrTab res_e = NUL, res_o = NUL;
   switch (op) {
     case MDWF_OP_D:
+      if (pro) {
+        conv_in(IE, IO);
+        run(with_phi(prog_D(0)), IO, IE, OE);
+        run(with_phi(prog_D(1)), IE, IO, OO);
+        res_e = OE;
+        res_o = OO;
+        break;
+      }
       conv_phi(1, IO, T);
       conv_phi(0, IE, OO);
       run(prog_D(0), T, IE, OE);
@@ -144,8 +169,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       res_o = OO;
       break;
     case MDWF_OP_MHAT:
-      conv_phi(0, IE, IO);
-      run(prog_A1(), IO, PtrTab(), T);
+      mhat_first();
       run(prog_A2(false, false), T, IE, OE);
       res_e = OE;
       break;
@@ -157,8 +181,7 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
       res_e = OE;
       break;
     case MDWF_OP_NORMAL:
-      conv_phi(0, IE, IO);
-      run(prog_A1(), IO, PtrTab(), T);
+      mhat_first();
       run(prog_A2(true, false), T, IE, OO);
       run(prog_B1(), OO, PtrTab(), T);
       run(prog_B2(), T, OO, OE);
@@ -197,8 +220,8 @@ static mdwf_status dslash_body(mdwf_ctx* c, const mdwf_gauge* g, const Geom& geo
     }
     case MDWF_OP_PREP:
       conv_in(IE, IO);
-      run(prog_5D(CH_MPHI_M5INV), IO, PtrTab(), T);
-      run(prog_PRE(0), T, IE, OE);
+      run(prog_5D(pro ? CH_M5INV : CH_MPHI_M5INV), IO, PtrTab(), T);
+      run(pro ? with_phi(prog_PRE(0)) : prog_PRE(0), T, IE, OE);
       res_e = OE;
       break;
     default:
