@@ -406,10 +406,10 @@ __global__ __launch_bounds__(kScalarThreads) void k_cg_alpha(CGState* S, const d
     CGState& s = S[slot];
     s.pq = pq;
     if (!finite_d(pq)) {
-      s.flags |= CG_FLAG_NAN;
+      s.flags |= CG_FLAG_NAN | CG_FLAG_ALPHA;
       s.active = 0;
     } else if (!(pq > 0.0)) {
-      s.flags |= CG_FLAG_BREAKDOWN;
+      s.flags |= CG_FLAG_BREAKDOWN | CG_FLAG_ALPHA;
       s.active = 0;
     } else {
       s.alpha_prev = s.alpha;

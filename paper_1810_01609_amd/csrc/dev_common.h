@@ -644,6 +644,7 @@ enum : int {
   CG_FLAG_BREAKDOWN = 2,  // <p, Ap> <= 0
   CG_FLAG_NAN = 4,
   CG_FLAG_MAXIT = 8,
+  CG_FLAG_ALPHA = 16,     // stopped at alpha: the current direction makes no step
 };
 
 }  // namespace mdwf

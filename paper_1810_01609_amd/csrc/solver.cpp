@@ -329,6 +329,30 @@ static mdwf_status finalize(mdwf_ctx* c, mdwf_job* j, int r) {
   return MDWF_OK;
 }
 
+// The direction whose step alpha p a stopped RHS still has to enter in x, or
+// null: x takes two directions at a time, in phase 1.
+static const char* due_direction(const mdwf_job* j, int r) {
+  const CGState& s = j->st[r];
+  // stopped at alpha: the last complete iteration was one phase earlier, and
+  // alpha is still its own
+  const int phase = s.flags & CG_FLAG_ALPHA ? s.phase ^ 1 : s.phase;
+  return phase == 0 && s.iters > 0 ? j->fp[r] : nullptr;
+}
+
+// x of a RHS that NaN or breakdown ended, with every complete iteration in it.
+// Only the plain FP64 solver returns x; otherwise psi is that of the last
+// reliable update, xh.
+static mdwf_status fold_due(mdwf_ctx* c, mdwf_job* j, int r) {
+  const char* due = due_direction(j, r);
+  if (j->ps != F64 || due == nullptr) return MDWF_OK;
+  FP64Temps T;
+  mdwf_status st = get_temps(c, j->geom, T);
+  if (st != MDWF_OK) return st;
+  One o{c, j->g, j->geom, CoefTab::single(j->coef)};
+  o.update(nullptr, due, j->st[r].alpha, F64, j->fx[r], j->feh[r], T.t1, T.t2);
+  return hip_err(c, o.e, "solution of a stopped iteration");
+}
+
 // Reliable update of one RHS: xh += x, x = 0, rh = M^+(eta^ - M^ xh) in FP64,
 // r = lo(rh).  Returns |rh|^2 in rr.
 static mdwf_status reliable_update(mdwf_ctx* c, mdwf_job* j, int r, double& rr) {
@@ -337,10 +361,7 @@ static mdwf_status reliable_update(mdwf_ctx* c, mdwf_job* j, int r, double& rr) 
   if (st != MDWF_OK) return st;
   One o{c, j->g, j->geom, CoefTab::single(j->coef)};
   char* xh = j->ps == F64 ? j->fx[r] : j->fxh[r];
-  // an iteration that ended in phase 0 has not entered x yet
-  const CGState& s = j->st[r];
-  const char* due = s.phase == 0 && s.iters > 0 ? j->fp[r] : nullptr;
-  true_residual(o, T, j->ps != F64 ? j->fx[r] : nullptr, due, s.alpha, j->ps, xh, j->feh[r]);
+  true_residual(o, T, j->ps != F64 ? j->fx[r] : nullptr, due_direction(j, r), j->st[r].alpha, j->ps, xh, j->feh[r]);
   if (o.e != hipSuccess) return hip_err(c, o.e, "reliable update");
   st = o.round_norm(T.t1, j->fr[r], j->ps, rr);
   j->stats[r].reliable_updates += 1;
@@ -721,7 +742,8 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
       if (s.flags & (CG_FLAG_NAN | CG_FLAG_BREAKDOWN)) {
         const mdwf_status fs = (s.flags & CG_FLAG_NAN) ? MDWF_ENAN : MDWF_EBREAKDOWN;
         j->stats[r].rel_res_normal = s.bb > 0 ? std::sqrt(std::fabs(s.rho) / s.bb) : 0.0;
-        st = finalize(c, j, r);
+        st = fold_due(c, j, r);
+        if (st == MDWF_OK) st = finalize(c, j, r);
         finish_slot(j, r, fs);
         if (first_fail == MDWF_OK) first_fail = fs;
         continue;
