@@ -406,53 +406,91 @@ struct QuadPos {
   float* tot;  // [w][site][24] of this 16-site tile
 };
 
-// Walks the columns of v: with SCAN first y = the recurrence S_i = x_i -
-// kappa S_{i-1} (alpha M5 y without the wall), then
-//   out_i = add_i + t0 y_i + t1 y_{i-1}   (without SCAN, add_i + t1 y_{i-1}),
-// where y includes the wall (y_{-1} = -mq y_{L5-1}).  DAG exchanges the walk
-// directions of the two chiralities (spins 0,1: reals 0..11; 2,3: 12..23).
+// The last values along the walk, for the next wavefront: lane 3 holds those of
+// the lower columns, lane 0 those of the upper ones.
+template <bool DAG> __device__ __forceinline__ void put_ends(const float v[24], const QuadPos& Q) {
+  float* t = Q.tot + ((size_t)Q.w * 16 + Q.site) * kTotRow;
+  constexpr int lo = DAG ? 12 : 0, up = DAG ? 0 : 12;
+  if (Q.q == 3) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *reinterpret_cast<v4f*>(t + lo + 4 * k) = v4f{v[lo + 4 * k], v[lo + 4 * k + 1], v[lo + 4 * k + 2], v[lo + 4 * k + 3]};
+  }
+  if (Q.q == 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *reinterpret_cast<v4f*>(t + up + 4 * k) = v4f{v[up + 4 * k], v[up + 4 * k + 1], v[up + 4 * k + 2], v[up + 4 * k + 3]};
+  }
+}
+
+// v_i = add_i + v_{i-1} along the walk, with v_{-1} = -mq v_{L5-1}.  DAG
+// exchanges the walk directions of the two chiralities (spins 0,1: reals 0..11;
+// 2,3: 12..23).  The lane at a quad's end takes its neighbour from LDS and no
+// other lane multiplies it, so a slice that is not finite reaches the slices
+// next to it and no more.
+template <bool DAG>
+__device__ __forceinline__ void quad_shift(float v[24], const float add[24], const QuadPos& Q, float mq) {
+  constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;  // first lower and upper real
+  put_ends<DAG>(v, Q);
+  float u[24];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    u[lc + k] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v[lc + k]), 0x90, 0xf, 0xf, false));  // [0,0,1,2]
+    u[uc + k] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v[uc + k]), 0xf9, 0xf, 0xf, false));  // [1,2,3,3]
+  }
+  __syncthreads();
+  const bool fl = Q.w == 0, fu = Q.w == Q.nw - 1;  // the walk's first wavefront
+  const float* t = Q.tot + Q.site * kTotRow;
+  float wl = 1.f, wu = 1.f;
+  if (Q.q == 0) {
+    const float* x = t + (size_t)(fl ? Q.nw - 1 : Q.w - 1) * 16 * kTotRow + lc;
+    wl = fl ? -mq : 1.f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) u[lc + k] = x[k];
+  }
+  if (Q.q == 3) {
+    const float* x = t + (size_t)(fu ? 0 : Q.w + 1) * 16 * kTotRow + uc;
+    wu = fu ? -mq : 1.f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) u[uc + k] = x[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    v[lc + k] = fmaf(wl, u[lc + k], add[lc + k]);
+    v[uc + k] = fmaf(wu, u[uc + k], add[uc + k]);
+  }
+}
+
+// Walks the columns of v: y = the recurrence S_i = x_i - kappa S_{i-1} (alpha
+// M5 y without the wall), then
+//   out_i = add_i + t0 y_i + t1 y_{i-1}   (t1 with SHIFT),
+// where y includes the wall (y_{-1} = -mq y_{L5-1}).
 // In the quad S takes two steps; the wavefronts' last values T_w then give
 // every wavefront the value E before its first slice,
 //   E_w = sum_{w' < w} k4^(w-1-w') T_w' - mq/c k4^w sum_w' k4^(nw-1-w') T_w'
 // (k4 = kappa^4, c = 1 + mq (-kappa)^L5), and y_i = S_i + (-kappa)^(i+1) E.
 // Each lane forms E of six of the 24 reals and the quad shares them by DPP.
-template <bool SCAN, bool SHIFT, bool DAG>
-__device__ __forceinline__ void quad_chain(float v[24], const float* add, const QuadPos& Q, float kappa, float mq,
+template <bool SHIFT, bool DAG>
+__device__ __forceinline__ void quad_solve(float v[24], const float* add, const QuadPos& Q, float kappa, float mq,
                                            float inv_c, float t0, float t1) {
+  constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;  // first lower and upper real
   const int pl = Q.q, pu = 3 - Q.q;  // place along the walk
   const float nk = -kappa, k2 = kappa * kappa;
-  if constexpr (SCAN) {
+  {
     const float l1 = pl >= 1 ? nk : 0.f, l2 = pl >= 2 ? k2 : 0.f;
     const float u1 = pu >= 1 ? nk : 0.f, u2 = pu >= 2 ? k2 : 0.f;
-    constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;  // first lower and upper real
     quad_scan6<true>(v + lc, l1, l2);
     quad_scan6<true>(v + lc + 6, l1, l2);
     quad_scan6<false>(v + uc, u1, u2);
     quad_scan6<false>(v + uc + 6, u1, u2);
   }
-  // last values along the walk: lane 3 holds those of the lower comps, lane 0
-  // those of the upper ones
-  {
-    float* t = Q.tot + ((size_t)Q.w * 16 + Q.site) * kTotRow;
-    constexpr int lo = DAG ? 12 : 0, up = DAG ? 0 : 12;
-    if (Q.q == 3) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        *reinterpret_cast<v4f*>(t + lo + 4 * k) = v4f{v[lo + 4 * k], v[lo + 4 * k + 1], v[lo + 4 * k + 2], v[lo + 4 * k + 3]};
-    }
-    if (Q.q == 0) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        *reinterpret_cast<v4f*>(t + up + 4 * k) = v4f{v[up + 4 * k], v[up + 4 * k + 1], v[up + 4 * k + 2], v[up + 4 * k + 3]};
-    }
-  }
+  put_ends<DAG>(v, Q);
   // what needs no neighbour wavefront goes before the barrier
   float out[24];
-  const float l1 = pl >= 1 ? t1 : 0.f, u1 = pu >= 1 ? t1 : 0.f;
 #pragma unroll
-  for (int k = 0; k < 24; ++k) out[k] = add == nullptr ? t0 * v[k] : SCAN ? fmaf(t0, v[k], add[k]) : add[k];
+  for (int k = 0; k < 24; ++k) out[k] = add == nullptr ? t0 * v[k] : fmaf(t0, v[k], add[k]);
   if constexpr (SHIFT) {
-    constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;
+    const float l1 = pl >= 1 ? t1 : 0.f, u1 = pu >= 1 ? t1 : 0.f;
     MDWF_QUAD_FMA6("[0,0,1,2]", out + lc, v + lc, l1);
     MDWF_QUAD_FMA6("[0,0,1,2]", out + lc + 6, v + lc + 6, l1);
     MDWF_QUAD_FMA6("[1,2,3,3]", out + uc, v + uc, u1);
@@ -464,7 +502,7 @@ __device__ __forceinline__ void quad_chain(float v[24], const float* add, const 
   const int wl = lower6 ? Q.w : Q.nw - 1 - Q.w;  // place along these reals' walk
   const float* t = Q.tot + Q.site * kTotRow + 6 * Q.q;
   float E[6] = {0, 0, 0, 0, 0, 0};
-  if constexpr (SCAN) {
+  {
     const float k4 = k2 * k2;
     float wall = -mq * inv_c;
     for (int j = 0; j < wl; ++j) wall *= k4;
@@ -483,16 +521,10 @@ __device__ __forceinline__ void quad_chain(float v[24], const float* add, const 
       wall *= k4;
       carry = o < wl ? carry * k4 : carry;
     }
-  } else {
-    const int prev = wl == 0 ? Q.nw - 1 : wl - 1;
-    const float c = wl == 0 ? -mq : 1.f;
-    const float* x = t + (size_t)(lower6 ? prev : Q.nw - 1 - prev) * 16 * kTotRow;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) E[k] = c * x[k];
   }
   // y_i = S_i + (-kappa)^(i+1) E enters out_i with t0, y_{i-1} with t1
   float el, eu;
-  if constexpr (SCAN) {
+  {
     const float k3 = nk * k2, k4 = k2 * k2;
     const float pw[5] = {1.f, nk, k2, k3, k4};
     auto pick = [&](int p, int d) {  // (-kappa)^(p + d)
@@ -504,9 +536,6 @@ __device__ __forceinline__ void quad_chain(float v[24], const float* add, const 
       el = fmaf(t1, pick(pl, 0), el);
       eu = fmaf(t1, pick(pu, 0), eu);
     }
-  } else {
-    el = pl == 0 ? t1 : 0.f;
-    eu = pu == 0 ? t1 : 0.f;
   }
   MDWF_QUAD_FMA6("[0,0,0,0]", out, E, DAG ? eu : el);
   MDWF_QUAD_FMA6("[1,1,1,1]", out + 6, E, DAG ? eu : el);
@@ -602,15 +631,15 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   const float b5a = (float)(cf.b5 * cf.inv_alpha), c5a = (float)(cf.c5 * cf.inv_alpha);
   const bool in_tile = tile < ((A.g.Vh + 15) >> 4);
   if constexpr (PROG == QP_A1) {
-    quad_chain<true, true, false>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+    quad_solve<true, false>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
   } else if constexpr (PROG == QP_B1) {
-    quad_chain<true, true, true>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+    quad_solve<true, true>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
   } else if constexpr (PROG == QP_A2 || PROG == QP_A2C) {
     Raw<P> ar{};
     if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
     float aux[24];
     unpack<P>(ar, aux);
-    quad_chain<true, false, false>(v, aux, Q, kappa, mq, inv_c, (float)(A.coef_y * cf.inv_alpha), 0.f);
+    quad_solve<false, false>(v, aux, Q, kappa, mq, inv_c, (float)(A.coef_y * cf.inv_alpha), 0.f);
   } else if constexpr (PROG == QP_B2 || PROG == QP_B2C) {
     // M5^T aux + coef_y M_phi^T h = (alpha aux + coef_y b5 h) + shift(beta aux + coef_y c5 h)
     Raw<P> ar{};
@@ -624,7 +653,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
       add[k] = fmaf(al, aux[k], b5y * v[k]);
       v[k] = fmaf(be, aux[k], c5y * v[k]);
     }
-    quad_chain<false, true, true>(v, add, Q, 0.f, mq, 1.f, 0.f, 1.f);
+    quad_shift<true>(v, add, Q, mq);
   } else if constexpr (PROG == QP_D || PROG == QP_PRE) {
     Raw<P> ar{};
     if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
@@ -636,8 +665,8 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
       add[k] = fmaf(PROG == QP_D ? al : 1.f, aux[k], cy * v[k]);
       v[k] = PROG == QP_D ? be * aux[k] : add[k];
     }
-    if constexpr (PROG == QP_D) quad_chain<false, true, false>(v, add, Q, 0.f, mq, 1.f, 0.f, 1.f);
-    else quad_chain<true, false, false>(v, nullptr, Q, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
+    if constexpr (PROG == QP_D) quad_shift<false>(v, add, Q, mq);
+    else quad_solve<false, false>(v, nullptr, Q, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
 
   if constexpr (PROG == QP_B2C) {
@@ -674,7 +703,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   if constexpr (PROG == QP_A2C) {
     QuadPos Q2 = Q;
     Q2.tot = reinterpret_cast<float*>(smem) + tot_tile;  // over the stage, dead since the first chain's barrier
-    quad_chain<true, false, true>(v, nullptr, Q2, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
+    quad_solve<false, true>(v, nullptr, Q2, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
   if constexpr (PROG != QP_B2C) {
     if (valid) store_own<P>(at_tile<P>(field_base<P>(io.out, A.g, w), tile, L5), oo, os, v, A.nt_store);
