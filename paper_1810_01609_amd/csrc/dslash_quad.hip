@@ -399,6 +399,50 @@ template <bool LOWER> __device__ __forceinline__ void quad_scan6(float* v, float
       : "+v"((o)[0]), "+v"((o)[1]), "+v"((o)[2]), "+v"((o)[3]), "+v"((o)[4]), "+v"((o)[5])                       \
       : "v"((x)[0]), "v"((x)[1]), "v"((x)[2]), "v"((x)[3]), "v"((x)[4]), "v"((x)[5]), "v"(k))
 
+// o[i] = k * perm(x[i]), i < 6
+#define MDWF_QUAD_MUL6(PERM, o, x, k)                                                                            \
+  asm("s_nop 1\n\t"                                                                                              \
+      "v_mul_f32_dpp %0, %6, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                              \
+      "v_mul_f32_dpp %1, %7, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                              \
+      "v_mul_f32_dpp %2, %8, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                              \
+      "v_mul_f32_dpp %3, %9, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                              \
+      "v_mul_f32_dpp %4, %10, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                             \
+      "v_mul_f32_dpp %5, %11, %12 quad_perm:" PERM " row_mask:0xf bank_mask:0xf"                                 \
+      : "=&v"((o)[0]), "=&v"((o)[1]), "=&v"((o)[2]), "=&v"((o)[3]), "=&v"((o)[4]), "=&v"((o)[5])                 \
+      : "v"((x)[0]), "v"((x)[1]), "v"((x)[2]), "v"((x)[3]), "v"((x)[4]), "v"((x)[5]), "v"(k))
+
+// o = or += coefficient times the slice before along the walk (LOWER columns
+// 0..11 of o and x are walked upwards, LC the first of them)
+template <int LC> __device__ __forceinline__ void quad_back_mul(float o[24], const float x[24], float l, float u) {
+  constexpr int UC = 12 - LC;
+  MDWF_QUAD_MUL6("[0,0,1,2]", o + LC, x + LC, l);
+  MDWF_QUAD_MUL6("[0,0,1,2]", o + LC + 6, x + LC + 6, l);
+  MDWF_QUAD_MUL6("[1,2,3,3]", o + UC, x + UC, u);
+  MDWF_QUAD_MUL6("[1,2,3,3]", o + UC + 6, x + UC + 6, u);
+}
+template <int LC> __device__ __forceinline__ void quad_back_fma(float o[24], const float x[24], float l, float u) {
+  constexpr int UC = 12 - LC;
+  MDWF_QUAD_FMA6("[0,0,1,2]", o + LC, x + LC, l);
+  MDWF_QUAD_FMA6("[0,0,1,2]", o + LC + 6, x + LC + 6, l);
+  MDWF_QUAD_FMA6("[1,2,3,3]", o + UC, x + UC, u);
+  MDWF_QUAD_FMA6("[1,2,3,3]", o + UC + 6, x + UC + 6, u);
+}
+// the same two slices back
+template <int LC> __device__ __forceinline__ void quad_back2_fma(float o[24], const float x[24], float l, float u) {
+  constexpr int UC = 12 - LC;
+  MDWF_QUAD_FMA6("[0,0,0,1]", o + LC, x + LC, l);
+  MDWF_QUAD_FMA6("[0,0,0,1]", o + LC + 6, x + LC + 6, l);
+  MDWF_QUAD_FMA6("[2,3,3,3]", o + UC, x + UC, u);
+  MDWF_QUAD_FMA6("[2,3,3,3]", o + UC + 6, x + UC + 6, u);
+}
+// o += coefficient times E, of which lane j holds reals 6j .. 6j + 5
+template <int LC> __device__ __forceinline__ void quad_share_fma(float o[24], const float E[6], float l, float u) {
+  MDWF_QUAD_FMA6("[0,0,0,0]", o, E, LC == 0 ? l : u);
+  MDWF_QUAD_FMA6("[1,1,1,1]", o + 6, E, LC == 0 ? l : u);
+  MDWF_QUAD_FMA6("[2,2,2,2]", o + 12, E, LC == 0 ? u : l);
+  MDWF_QUAD_FMA6("[3,3,3,3]", o + 18, E, LC == 0 ? u : l);
+}
+
 struct QuadPos {
   int q;       // lane's slice inside the quad
   int w, nw;   // wavefront's place along the fifth dimension, and how many
@@ -470,31 +514,43 @@ __device__ __forceinline__ void quad_shift(float v[24], const float add[24], con
 //   E_w = sum_{w' < w} k4^(w-1-w') T_w' - mq/c k4^w sum_w' k4^(nw-1-w') T_w'
 // (k4 = kappa^4, c = 1 + mq (-kappa)^L5), and y_i = S_i + (-kappa)^(i+1) E.
 // Each lane forms E of six of the 24 reals and the quad shares them by DPP.
-template <bool SHIFT, bool DAG>
+//
+// CAREFUL (32-bit storage) sums everything the recurrence adds to x first and
+// rounds y = x + c once; the plain form rounds S twice, the product with t0 and
+// the term in E, each at full size.  16-bit storage, whose own rounding is 1e3
+// times larger, saves the registers and 72 instructions.  FP32 M^+M^ on 32^3 x
+// 64 x 12: 9.2e-8 from 64 bits and 6.89 ms, plain 1.03e-7 and 6.93 ms (the
+// columns in LDS of the general kernel: 9.7e-8).
+template <bool SHIFT, bool DAG, bool CAREFUL>
 __device__ __forceinline__ void quad_solve(float v[24], const float* add, const QuadPos& Q, float kappa, float mq,
                                            float inv_c, float t0, float t1) {
   constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;  // first lower and upper real
   const int pl = Q.q, pu = 3 - Q.q;  // place along the walk
   const float nk = -kappa, k2 = kappa * kappa;
-  {
-    const float l1 = pl >= 1 ? nk : 0.f, l2 = pl >= 2 ? k2 : 0.f;
-    const float u1 = pu >= 1 ? nk : 0.f, u2 = pu >= 2 ? k2 : 0.f;
+  const float l1 = pl >= 1 ? nk : 0.f, l2 = pl >= 2 ? k2 : 0.f;
+  const float u1 = pu >= 1 ? nk : 0.f, u2 = pu >= 2 ? k2 : 0.f;
+  const float lt = pl >= 1 ? t1 : 0.f, ut = pu >= 1 ? t1 : 0.f;
+  // what needs no neighbour wavefront goes before the barrier: S, and of the
+  // result c (CAREFUL) or all but the terms in E
+  float out[24];
+  if constexpr (CAREFUL) {
+    quad_back_mul<lc>(out, v, l1, u1);
+    float S[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) S[k] = v[k] + out[k];
+    quad_back2_fma<lc>(out, S, l2, u2);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) S[k] = v[k] + out[k];
+    put_ends<DAG>(S, Q);
+  } else {
     quad_scan6<true>(v + lc, l1, l2);
     quad_scan6<true>(v + lc + 6, l1, l2);
     quad_scan6<false>(v + uc, u1, u2);
     quad_scan6<false>(v + uc + 6, u1, u2);
-  }
-  put_ends<DAG>(v, Q);
-  // what needs no neighbour wavefront goes before the barrier
-  float out[24];
+    put_ends<DAG>(v, Q);
 #pragma unroll
-  for (int k = 0; k < 24; ++k) out[k] = add == nullptr ? t0 * v[k] : fmaf(t0, v[k], add[k]);
-  if constexpr (SHIFT) {
-    const float l1 = pl >= 1 ? t1 : 0.f, u1 = pu >= 1 ? t1 : 0.f;
-    MDWF_QUAD_FMA6("[0,0,1,2]", out + lc, v + lc, l1);
-    MDWF_QUAD_FMA6("[0,0,1,2]", out + lc + 6, v + lc + 6, l1);
-    MDWF_QUAD_FMA6("[1,2,3,3]", out + uc, v + uc, u1);
-    MDWF_QUAD_FMA6("[1,2,3,3]", out + uc + 6, v + uc + 6, u1);
+    for (int k = 0; k < 24; ++k) out[k] = add == nullptr ? t0 * v[k] : fmaf(t0, v[k], add[k]);
+    if constexpr (SHIFT) quad_back_fma<lc>(out, v, lt, ut);
   }
   __syncthreads();
   // E of reals 6q .. 6q+5
@@ -522,27 +578,35 @@ __device__ __forceinline__ void quad_solve(float v[24], const float* add, const 
       carry = o < wl ? carry * k4 : carry;
     }
   }
-  // y_i = S_i + (-kappa)^(i+1) E enters out_i with t0, y_{i-1} with t1
-  float el, eu;
-  {
-    const float k3 = nk * k2, k4 = k2 * k2;
-    const float pw[5] = {1.f, nk, k2, k3, k4};
-    auto pick = [&](int p, int d) {  // (-kappa)^(p + d)
-      return p == 0 ? pw[d] : p == 1 ? pw[1 + d] : p == 2 ? pw[2 + d] : pw[3 + d];
-    };
-    el = t0 * pick(pl, 1);
-    eu = t0 * pick(pu, 1);
+  const float k3 = nk * k2, k4 = k2 * k2;
+  const float pw[5] = {1.f, nk, k2, k3, k4};
+  auto pick = [&](int p, int d) {  // (-kappa)^(p + d)
+    return p == 0 ? pw[d] : p == 1 ? pw[1 + d] : p == 2 ? pw[2 + d] : pw[3 + d];
+  };
+  if constexpr (CAREFUL) {
+    quad_share_fma<lc>(out, E, pick(pl, 1), pick(pu, 1));
+#pragma unroll
+    for (int k = 0; k < 24; ++k) v[k] += out[k];  // y
+    if constexpr (SHIFT) {  // y_{i-1}: the lane before, or E
+      quad_back_mul<lc>(out, v, lt, ut);
+      quad_share_fma<lc>(out, E, pl == 0 ? t1 : 0.f, pu == 0 ? t1 : 0.f);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = fmaf(t0, v[k], out[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = add == nullptr ? t0 * v[k] : fmaf(t0, v[k], add[k]);
+    }
+  } else {
+    // y_i = S_i + (-kappa)^(i+1) E enters out_i with t0, y_{i-1} with t1
+    float el = t0 * pick(pl, 1), eu = t0 * pick(pu, 1);
     if constexpr (SHIFT) {
       el = fmaf(t1, pick(pl, 0), el);
       eu = fmaf(t1, pick(pu, 0), eu);
     }
-  }
-  MDWF_QUAD_FMA6("[0,0,0,0]", out, E, DAG ? eu : el);
-  MDWF_QUAD_FMA6("[1,1,1,1]", out + 6, E, DAG ? eu : el);
-  MDWF_QUAD_FMA6("[2,2,2,2]", out + 12, E, DAG ? el : eu);
-  MDWF_QUAD_FMA6("[3,3,3,3]", out + 18, E, DAG ? el : eu);
+    quad_share_fma<lc>(out, E, el, eu);
 #pragma unroll
-  for (int k = 0; k < 24; ++k) v[k] = out[k];
+    for (int k = 0; k < 24; ++k) v[k] = out[k];
+  }
 }
 
 // Fixed-order FP64 sum over a wavefront: DPP rows, then across the rows.
@@ -629,17 +693,18 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   const float kappa = (float)cf.kappa, inv_c = (float)cf.inv_c;
   // M_phi M5^-1 and its transpose: coefficients rounded to FP32 once
   const float b5a = (float)(cf.b5 * cf.inv_alpha), c5a = (float)(cf.c5 * cf.inv_alpha);
+  constexpr bool kCareful = P == F32;
   const bool in_tile = tile < ((A.g.Vh + 15) >> 4);
   if constexpr (PROG == QP_A1) {
-    quad_solve<true, false>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+    quad_solve<true, false, kCareful>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
   } else if constexpr (PROG == QP_B1) {
-    quad_solve<true, true>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+    quad_solve<true, true, kCareful>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
   } else if constexpr (PROG == QP_A2 || PROG == QP_A2C) {
     Raw<P> ar{};
     if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
     float aux[24];
     unpack<P>(ar, aux);
-    quad_solve<false, false>(v, aux, Q, kappa, mq, inv_c, (float)(A.coef_y * cf.inv_alpha), 0.f);
+    quad_solve<false, false, kCareful>(v, aux, Q, kappa, mq, inv_c, (float)(A.coef_y * cf.inv_alpha), 0.f);
   } else if constexpr (PROG == QP_B2 || PROG == QP_B2C) {
     // M5^T aux + coef_y M_phi^T h = (alpha aux + coef_y b5 h) + shift(beta aux + coef_y c5 h)
     Raw<P> ar{};
@@ -650,10 +715,14 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     const float b5y = (float)(A.coef_y * cf.b5), c5y = (float)(A.coef_y * cf.c5);
 #pragma unroll
     for (int k = 0; k < 24; ++k) {
-      add[k] = fmaf(al, aux[k], b5y * v[k]);
+      add[k] = kCareful ? b5y * v[k] : fmaf(al, aux[k], b5y * v[k]);
       v[k] = fmaf(be, aux[k], c5y * v[k]);
     }
     quad_shift<true>(v, add, Q, mq);
+    if constexpr (kCareful) {  // the largest term last
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = fmaf(al, aux[k], v[k]);
+    }
   } else if constexpr (PROG == QP_D || PROG == QP_PRE) {
     Raw<P> ar{};
     if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
@@ -662,11 +731,16 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     const float al = (float)cf.alpha, be = (float)cf.beta, cy = (float)A.coef_y;
 #pragma unroll
     for (int k = 0; k < 24; ++k) {
-      add[k] = fmaf(PROG == QP_D ? al : 1.f, aux[k], cy * v[k]);
+      add[k] = PROG == QP_D ? (kCareful ? cy * v[k] : fmaf(al, aux[k], cy * v[k])) : aux[k] + cy * v[k];
       v[k] = PROG == QP_D ? be * aux[k] : add[k];
     }
-    if constexpr (PROG == QP_D) quad_shift<false>(v, add, Q, mq);
-    else quad_solve<false, false>(v, nullptr, Q, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
+    if constexpr (PROG == QP_D) {
+      quad_shift<false>(v, add, Q, mq);
+      if constexpr (kCareful) {
+#pragma unroll
+        for (int k = 0; k < 24; ++k) v[k] = fmaf(al, aux[k], v[k]);
+      }
+    } else quad_solve<false, false, kCareful>(v, nullptr, Q, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
 
   if constexpr (PROG == QP_B2C) {
@@ -703,7 +777,7 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   if constexpr (PROG == QP_A2C) {
     QuadPos Q2 = Q;
     Q2.tot = reinterpret_cast<float*>(smem) + tot_tile;  // over the stage, dead since the first chain's barrier
-    quad_solve<false, true>(v, nullptr, Q2, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
+    quad_solve<false, true, kCareful>(v, nullptr, Q2, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
   if constexpr (PROG != QP_B2C) {
     if (valid) store_own<P>(at_tile<P>(field_base<P>(io.out, A.g, w), tile, L5), oo, os, v, A.nt_store);
