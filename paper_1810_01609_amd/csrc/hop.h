@@ -78,27 +78,30 @@ __device__ __forceinline__ void accumulate(Cplx<R> acc[4][3], const Cplx<R> w[2]
   }
 }
 
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return fma(a, b, c); }
+
 // acc += sc * (spin reconstruction of w): the accumulate above with the
-// neighbour's per-site scale applied in the FP32 sum
-template <int MU, int SIG>
-__device__ __forceinline__ void accumulate_scaled(Cplx<float> acc[4][3], const Cplx<float> w[2][3], float sc) {
-  const float ps = SIG > 0 ? sc : -sc;  // +SIG*sc
+// neighbour's per-site scale applied in the sum
+template <int MU, int SIG, class R>
+__device__ __forceinline__ void accumulate_scaled(Cplx<R> acc[4][3], const Cplx<R> w[2][3], R sc) {
+  const R ps = SIG > 0 ? sc : -sc;  // +SIG*sc
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    acc[0][c] = {fmaf(sc, w[0][c].re, acc[0][c].re), fmaf(sc, w[0][c].im, acc[0][c].im)};
-    acc[1][c] = {fmaf(sc, w[1][c].re, acc[1][c].re), fmaf(sc, w[1][c].im, acc[1][c].im)};
+    acc[0][c] = {fma_r(sc, w[0][c].re, acc[0][c].re), fma_r(sc, w[0][c].im, acc[0][c].im)};
+    acc[1][c] = {fma_r(sc, w[1][c].re, acc[1][c].re), fma_r(sc, w[1][c].im, acc[1][c].im)};
     if constexpr (MU == 0) {  // acc2 += -SIG i w1, acc3 += -SIG i w0
-      acc[2][c] = {fmaf(ps, w[1][c].im, acc[2][c].re), fmaf(-ps, w[1][c].re, acc[2][c].im)};
-      acc[3][c] = {fmaf(ps, w[0][c].im, acc[3][c].re), fmaf(-ps, w[0][c].re, acc[3][c].im)};
+      acc[2][c] = {fma_r(ps, w[1][c].im, acc[2][c].re), fma_r(-ps, w[1][c].re, acc[2][c].im)};
+      acc[3][c] = {fma_r(ps, w[0][c].im, acc[3][c].re), fma_r(-ps, w[0][c].re, acc[3][c].im)};
     } else if constexpr (MU == 1) {  // acc2 += SIG w1, acc3 -= SIG w0
-      acc[2][c] = {fmaf(ps, w[1][c].re, acc[2][c].re), fmaf(ps, w[1][c].im, acc[2][c].im)};
-      acc[3][c] = {fmaf(-ps, w[0][c].re, acc[3][c].re), fmaf(-ps, w[0][c].im, acc[3][c].im)};
+      acc[2][c] = {fma_r(ps, w[1][c].re, acc[2][c].re), fma_r(ps, w[1][c].im, acc[2][c].im)};
+      acc[3][c] = {fma_r(-ps, w[0][c].re, acc[3][c].re), fma_r(-ps, w[0][c].im, acc[3][c].im)};
     } else if constexpr (MU == 2) {  // acc2 += -SIG i w0, acc3 += SIG i w1
-      acc[2][c] = {fmaf(ps, w[0][c].im, acc[2][c].re), fmaf(-ps, w[0][c].re, acc[2][c].im)};
-      acc[3][c] = {fmaf(-ps, w[1][c].im, acc[3][c].re), fmaf(ps, w[1][c].re, acc[3][c].im)};
+      acc[2][c] = {fma_r(ps, w[0][c].im, acc[2][c].re), fma_r(-ps, w[0][c].re, acc[2][c].im)};
+      acc[3][c] = {fma_r(-ps, w[1][c].im, acc[3][c].re), fma_r(ps, w[1][c].re, acc[3][c].im)};
     } else {  // acc2 += SIG w0, acc3 += SIG w1
-      acc[2][c] = {fmaf(ps, w[0][c].re, acc[2][c].re), fmaf(ps, w[0][c].im, acc[2][c].im)};
-      acc[3][c] = {fmaf(ps, w[1][c].re, acc[3][c].re), fmaf(ps, w[1][c].im, acc[3][c].im)};
+      acc[2][c] = {fma_r(ps, w[0][c].re, acc[2][c].re), fma_r(ps, w[0][c].im, acc[2][c].im)};
+      acc[3][c] = {fma_r(ps, w[1][c].re, acc[3][c].re), fma_r(ps, w[1][c].im, acc[3][c].im)};
     }
   }
 }
