@@ -461,6 +461,9 @@ template <class R> struct Column {
 // y = M5^-1 x on a column, in place; with BIDIAG the column is then replaced
 // by z = a*y + b*(shift y) (the lower bidiagonal with the -mq wall), fused
 // into the same sweep: z_i needs y_i and y_{i-1}, z_0 needs y_{L5-1}.
+// y_i = (x_i - kappa p_{i-1}) / alpha, p = alpha y, is formed from x_i with one
+// rounding at full size rather than from p_i: M_phi y is stored, and rounded,
+// where a hop that formed it on its neighbours would round only what it projects.
 // The sweeps read four column entries before writing any, so the LDS reads
 // of a batch are in flight together (the in-place writes would otherwise
 // order every read behind the previous write).
@@ -481,9 +484,10 @@ __device__ __forceinline__ void col_m5inv(const Column<R>& col, const Coef5& c, 
   const Cplx<R> y0 = {prev.re * ia, prev.im * ia};
   Cplx<R> ym = y0;
   if constexpr (!BIDIAG) col.set(0, y0);
+  const R ika = ia * kappa;
   auto step = [&](int i, Cplx<R> x) {
+    const Cplx<R> y = {fma_r(ia, x.re, -(ika * prev.re)), fma_r(ia, x.im, -(ika * prev.im))};
     prev = {x.re - kappa * prev.re, x.im - kappa * prev.im};
-    const Cplx<R> y = {prev.re * ia, prev.im * ia};
     if constexpr (BIDIAG) col.set(i, {a * y.re + b * ym.re, a * y.im + b * ym.im});
     else col.set(i, y);
     ym = y;

@@ -507,7 +507,7 @@ __device__ __forceinline__ void quad_shift(float v[24], const float add[24], con
 
 // Walks the columns of v: y = the recurrence S_i = x_i - kappa S_{i-1} (alpha
 // M5 y without the wall), then
-//   out_i = add_i + t0 y_i + t1 y_{i-1}   (t1 with SHIFT),
+//   out_i = add_i + t0 y_i, or with SHIFT t0 y_i + t1 y_{i-1},
 // where y includes the wall (y_{-1} = -mq y_{L5-1}).
 // In the quad S takes two steps; the wavefronts' last values T_w then give
 // every wavefront the value E before its first slice,
@@ -515,15 +515,16 @@ __device__ __forceinline__ void quad_shift(float v[24], const float add[24], con
 // (k4 = kappa^4, c = 1 + mq (-kappa)^L5), and y_i = S_i + (-kappa)^(i+1) E.
 // Each lane forms E of six of the 24 reals and the quad shares them by DPP.
 //
-// CAREFUL (32-bit storage) sums everything the recurrence adds to x first and
-// rounds y = x + c once; the plain form rounds S twice, the product with t0 and
-// the term in E, each at full size.  16-bit storage, whose own rounding is 1e3
-// times larger, saves the registers and 72 instructions.  FP32 M^+M^ on 32^3 x
-// 64 x 12: 9.2e-8 from 64 bits and 6.89 ms, plain 1.03e-7 and 6.93 ms (the
-// columns in LDS of the general kernel: 9.7e-8).
+// CAREFUL (32-bit storage) sums everything the recurrence adds to x first, so
+// that the result is x times its coefficient plus that, rounded once at full
+// size (twice with add or SHIFT); the plain form rounds S twice, the product
+// with t0 and the term in E, each at full size.  16-bit storage, whose own
+// rounding is 1e3 times larger, saves the registers and some 90 instructions.
+// FP32 M^+M^ on 32^3 x 64 x 12: 8.8e-8 from 64 bits and 6.92 ms, plain 1.03e-7
+// and 6.95 ms (columns in LDS, as the general kernel did then: 9.7e-8).
 template <bool SHIFT, bool DAG, bool CAREFUL>
 __device__ __forceinline__ void quad_solve(float v[24], const float* add, const QuadPos& Q, float kappa, float mq,
-                                           float inv_c, float t0, float t1) {
+                                           float inv_c, float t0, float t1, float ia = 1.f) {
   constexpr int lc = DAG ? 12 : 0, uc = 12 - lc;  // first lower and upper real
   const int pl = Q.q, pu = 3 - Q.q;  // place along the walk
   const float nk = -kappa, k2 = kappa * kappa;
@@ -585,16 +586,20 @@ __device__ __forceinline__ void quad_solve(float v[24], const float* add, const 
   };
   if constexpr (CAREFUL) {
     quad_share_fma<lc>(out, E, pick(pl, 1), pick(pu, 1));
+    if constexpr (SHIFT) {  // of ia y; y_{i-1} is the lane before, or E
 #pragma unroll
-    for (int k = 0; k < 24; ++k) v[k] += out[k];  // y
-    if constexpr (SHIFT) {  // y_{i-1}: the lane before, or E
+      for (int k = 0; k < 24; ++k) v[k] = fmaf(ia, v[k], ia * out[k]);
       quad_back_mul<lc>(out, v, lt, ut);
-      quad_share_fma<lc>(out, E, pl == 0 ? t1 : 0.f, pu == 0 ? t1 : 0.f);
+      const float te = ia * t1;
+      quad_share_fma<lc>(out, E, pl == 0 ? te : 0.f, pu == 0 ? te : 0.f);
 #pragma unroll
       for (int k = 0; k < 24; ++k) v[k] = fmaf(t0, v[k], out[k]);
+    } else if (add == nullptr) {
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = fmaf(t0, v[k], t0 * out[k]);
     } else {
 #pragma unroll
-      for (int k = 0; k < 24; ++k) v[k] = add == nullptr ? t0 * v[k] : fmaf(t0, v[k], add[k]);
+      for (int k = 0; k < 24; ++k) v[k] = fmaf(t0, v[k] + out[k], add[k]);
     }
   } else {
     // y_i = S_i + (-kappa)^(i+1) E enters out_i with t0, y_{i-1} with t1
@@ -691,14 +696,15 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
   // last tile is allocated, so its reads stay inside the field
   const QuadPos Q{q, w, nw, site, tot + tot_tile};
   const float kappa = (float)cf.kappa, inv_c = (float)cf.inv_c;
-  // M_phi M5^-1 and its transpose: coefficients rounded to FP32 once
-  const float b5a = (float)(cf.b5 * cf.inv_alpha), c5a = (float)(cf.c5 * cf.inv_alpha);
   constexpr bool kCareful = P == F32;
+  // M_phi M5^-1 and its transpose: coefficients rounded to FP32 once
+  const float ia = (float)cf.inv_alpha;
+  const float b5a = (float)(kCareful ? cf.b5 : cf.b5 * cf.inv_alpha), c5a = (float)(kCareful ? cf.c5 : cf.c5 * cf.inv_alpha);
   const bool in_tile = tile < ((A.g.Vh + 15) >> 4);
   if constexpr (PROG == QP_A1) {
-    quad_solve<true, false, kCareful>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+    quad_solve<true, false, kCareful>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a, ia);
   } else if constexpr (PROG == QP_B1) {
-    quad_solve<true, true, kCareful>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a);
+    quad_solve<true, true, kCareful>(v, nullptr, Q, kappa, mq, inv_c, b5a, c5a, ia);
   } else if constexpr (PROG == QP_A2 || PROG == QP_A2C) {
     Raw<P> ar{};
     if (in_tile) load_raw<P>(at_tile<P>(field_base<P>(io.aux, A.g, w), tile, L5), oo, os, ar);
