@@ -150,17 +150,18 @@ void release(DevBuf& b) {
 
 static constexpr size_t kTableBytes = 1 << 20;
 
-// Small uploads (pointer tables, coefficients) go through a pinned mirror of
-// a device region, bump-allocated per top-level call.  A region offset is
-// rewritten only after the copies of the previous call have executed
-// (reset_tables waits for the event recorded after the latest upload).
+// The tables of a call with several right-hand sides (pointers, coefficients)
+// go through a pinned mirror of a device region, bump-allocated per top-level
+// call.  A region offset is rewritten only after the copies of the previous call
+// have executed (reset_tables waits for the event recorded after the latest
+// upload), and never within a call: one that needs more than the region holds
+// is refused.
 void reset_tables(mdwf_ctx* c) {
   if (c->tables_ev != nullptr) (void)hipEventSynchronize(c->tables_ev);
   c->tables_used = 0;
-  c->tables_floor = 0;
 }
 
-void* upload_bytes(mdwf_ctx* c, const void* data, size_t n) {
+static void* upload_bytes(mdwf_ctx* c, const void* data, size_t n) {
   const size_t bytes = round_up(n > 0 ? n : 1, 256);
   if (c->tables.p == nullptr) {
     if (ensure(c, c->tables, kTableBytes) != MDWF_OK) return nullptr;
@@ -170,14 +171,7 @@ void* upload_bytes(mdwf_ctx* c, const void* data, size_t n) {
     }
     if (hipEventCreateWithFlags(&c->tables_ev, hipEventDisableTiming) != hipSuccess) return nullptr;
   }
-  if (bytes > kTableBytes) return nullptr;
-  if (c->tables_used + bytes > kTableBytes) {
-    // exhausted within one call: drain the stream, then start over above the
-    // tables the running CG loop keeps reading (tables_floor)
-    (void)hipStreamSynchronize(c->stream);
-    c->tables_used = c->tables_floor;
-    if (c->tables_used + bytes > kTableBytes) return nullptr;
-  }
+  if (bytes > kTableBytes - c->tables_used) return nullptr;
   char* dst = static_cast<char*>(c->tables.p) + c->tables_used;
   char* src = static_cast<char*>(c->tables_host) + c->tables_used;
   c->tables_used += bytes;
@@ -187,28 +181,24 @@ void* upload_bytes(mdwf_ctx* c, const void* data, size_t n) {
   return dst;
 }
 
-char* const* upload_table(mdwf_ctx* c, const std::vector<const void*>& ptrs) {
-  return static_cast<char* const*>(upload_bytes(c, ptrs.data(), ptrs.size() * sizeof(void*)));
-}
-
 bool make_tables(mdwf_ctx* c, const std::vector<std::vector<const void*>>& ptrs, const std::vector<Coef5>& coefs,
                  LaunchTables& out) {
-  const size_t n = coefs.size(), tb = n * sizeof(void*);
+  const size_t n = ptrs[0].size(), tb = n * sizeof(void*);
+  const size_t cb = coefs.size() > 1 ? n * sizeof(Coef5) : 0;
   out.tab.clear();
+  out.coef = CoefTab::single(coefs[0]);
   if (n == 1) {
     for (const auto& p : ptrs) out.tab.push_back(PtrTab::single(p[0]));
-    out.coef = CoefTab::single(coefs[0]);
     return true;
   }
-  std::vector<char> buf(n * sizeof(Coef5) + ptrs.size() * tb);
-  memcpy(buf.data(), coefs.data(), n * sizeof(Coef5));
-  char* w = buf.data() + n * sizeof(Coef5);
+  std::vector<char> buf(cb + ptrs.size() * tb);
+  memcpy(buf.data(), coefs.data(), cb);
+  char* w = buf.data() + cb;
   for (size_t k = 0; k < ptrs.size(); ++k) memcpy(w + k * tb, ptrs[k].data(), tb);
   const char* d = static_cast<const char*>(upload_bytes(c, buf.data(), buf.size()));
   if (d == nullptr) return false;
-  out.coef = CoefTab(reinterpret_cast<const Coef5*>(d));
-  for (size_t k = 0; k < ptrs.size(); ++k)
-    out.tab.push_back(PtrTab(reinterpret_cast<char* const*>(d + n * sizeof(Coef5) + k * tb)));
+  if (cb > 0) out.coef = CoefTab(reinterpret_cast<const Coef5*>(d));
+  for (size_t k = 0; k < ptrs.size(); ++k) out.tab.push_back(PtrTab(reinterpret_cast<char* const*>(d + cb + k * tb)));
   return true;
 }
 

@@ -73,7 +73,6 @@ struct mdwf_ctx {
   mdwf::DevBuf tables;     // pointer tables / small arrays, bump-allocated per call
   void* tables_host = nullptr;  // pinned mirror of `tables`
   size_t tables_used = 0;
-  size_t tables_floor = 0;  // bytes below which a wrapped region must not reuse (tables a running loop still reads)
   hipEvent_t tables_ev = nullptr;  // recorded after the latest table upload
   mdwf::DevBuf partials_d; // dslash 16-site tile partials
   mdwf::DevBuf partials_b; // blas block partials
@@ -137,17 +136,15 @@ Coef5 make_coef(const mdwf_action* a);
 // device memory
 mdwf_status ensure(mdwf_ctx* c, DevBuf& b, size_t n);
 void release(DevBuf& b);
-// upload a pointer table / small array (stream-ordered); returns device address
-char* const* upload_table(mdwf_ctx* c, const std::vector<const void*>& ptrs);
-// `count` pointer tables of n entries each, and n coefficients, in one upload
-// (none for n = 1, where they travel in the launches); false on failure
+// pointer tables of n entries each, and n coefficients or one for all, in one
+// upload (pointers of n = 1 and a single coefficient travel in the launches);
+// false on failure
 struct LaunchTables {
   std::vector<PtrTab> tab;
   CoefTab coef;
 };
 bool make_tables(mdwf_ctx* c, const std::vector<std::vector<const void*>>& ptrs, const std::vector<Coef5>& coefs,
                  LaunchTables& out);
-void* upload_bytes(mdwf_ctx* c, const void* data, size_t n);
 void reset_tables(mdwf_ctx* c);
 
 // CG update fused into a stencil launch (see DslashArgs::cg_update)

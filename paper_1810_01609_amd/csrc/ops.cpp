@@ -95,7 +95,7 @@ extern "C" mdwf_status mdwf_dslash(mdwf_ctx* c, const mdwf_gauge* g, const mdwf_
     for (int k = 0; k < 5; ++k) p[2 + k][r] = w + fb * (5 * r + k);
   }
   LaunchTables lt;
-  if (!make_tables(c, p, std::vector<Coef5>(nrhs, coef), lt))
+  if (!make_tables(c, p, {coef}, lt))
     return set_err(c, MDWF_EHIP, "mdwf_dslash: table upload failed");
   const DslashTables t{lt.tab[0], lt.tab[1], lt.tab[2], lt.tab[3], lt.tab[4], lt.tab[5], lt.tab[6], lt.tab[7], lt.coef};
   return dslash_body(c, g, geom, op, prec, nrhs, t);
@@ -400,8 +400,6 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
   mdwf_status st = ensure(c, c->dws, (fb * 2 + hb_r) * nrhs);
   if (st != MDWF_OK) return st;
   const Coef5 coef = make_coef(act);
-  std::vector<Coef5> coefs(nrhs, coef);
-  const Coef5* coef_d = static_cast<const Coef5*>(upload_bytes(c, coefs.data(), coefs.size() * sizeof(Coef5)));
   std::vector<const void*> uin(nrhs), uout(nrhs), io(nrhs), oe(nrhs), hal(nrhs), nul(nrhs, nullptr);
   char* w = static_cast<char*>(c->dws.p);
   for (int r = 0; r < nrhs; ++r) {
@@ -411,14 +409,10 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
     oe[r] = w + (fb * 2 + hb_r) * r + fb;
     hal[r] = w + (fb * 2 + hb_r) * r + 2 * fb;
   }
-  char* const* UIN = upload_table(c, uin);
-  char* const* UOUT = upload_table(c, uout);
-  char* const* IO = upload_table(c, io);
-  char* const* OE = upload_table(c, oe);
-  char* const* HAL = upload_table(c, hal);
-  char* const* NUL = upload_table(c, nul);
-  if (!coef_d || !UIN || !UOUT || !IO || !OE || !HAL || !NUL)
+  LaunchTables lt;
+  if (!make_tables(c, {uin, uout, io, oe, hal, nul}, {coef}, lt))
     return set_err(c, MDWF_EHIP, "mdwf_hop_split: table upload failed");
+  const PtrTab &UIN = lt.tab[0], &UOUT = lt.tab[1], &IO = lt.tab[2], &OE = lt.tab[3], &HAL = lt.tab[4], &NUL = lt.tab[5];
   D.in = IO;
   D.out = OE;
   D.send = HAL;
@@ -427,19 +421,19 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   if (phase_ms != nullptr)
     for (auto& x : ev) (void)hipEventCreate(&x);
-  hipError_t e = layout_user_to_half(geom, PtrTab(UIN), PtrTab(), PtrTab(IO), prec, nrhs, c->stream);
+  hipError_t e = layout_user_to_half(geom, UIN, PtrTab(), IO, prec, nrhs, c->stream);
   if (e == hipSuccess && ev[0]) e = hipEventRecord(ev[0], c->stream);
   if (e == hipSuccess && split_mask != 0) e = dd_pack(D, prec, c->stream);
   if (e == hipSuccess && ev[1]) e = hipEventRecord(ev[1], c->stream);
   if (e == hipSuccess) {
     Prog p = prog_HOP(0, false);
     p.split = split_mask;
-    e = run_prog(c, g, geom, prec, p, PtrTab(IO), PtrTab(), PtrTab(OE), CoefTab(coef_d), nrhs, nullptr, 0, nullptr, 0, cls, false);
+    e = run_prog(c, g, geom, prec, p, IO, PtrTab(), OE, lt.coef, nrhs, nullptr, 0, nullptr, 0, cls, false);
   }
   if (e == hipSuccess && ev[2]) e = hipEventRecord(ev[2], c->stream);
   if (e == hipSuccess && split_mask != 0) e = dd_exterior(D, prec, c->stream);
   if (e == hipSuccess && ev[3]) e = hipEventRecord(ev[3], c->stream);
-  if (e == hipSuccess) e = layout_half_to_user(geom, PtrTab(OE), PtrTab(NUL), PtrTab(UOUT), prec, nrhs, c->stream);
+  if (e == hipSuccess) e = layout_half_to_user(geom, OE, NUL, UOUT, prec, nrhs, c->stream);
   if (phase_ms != nullptr) {
     if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
     for (int k = 0; k < 3; ++k) {

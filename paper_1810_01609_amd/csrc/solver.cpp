@@ -110,30 +110,35 @@ static mdwf_status read_sums(mdwf_ctx* c, int n, std::vector<double>& out) {
   return MDWF_OK;
 }
 
-// |a - b|^2 (|a|^2 where b is null) of half-fields in FP64, to the host
-static mdwf_status norms_f64(mdwf_ctx* c, const Geom& g, const std::vector<const void*>& a,
-                             const std::vector<const void*>& b, std::vector<double>& out) {
-  const int n = (int)a.size();
+// |a - b|^2 and |a|^2 of FP64 half-fields, to the host
+static mdwf_status norms_f64(mdwf_ctx* c, const Geom& g, const void* a, const void* b, double& diff, double& norm) {
   BlasArgs B{};
   B.g = g;
-  B.nslots = n;
+  B.nslots = 1;
   const int nblk = blas_nblk(g);
-  mdwf_status s = ensure(c, c->partials_b, (size_t)nblk * n * sizeof(double));
+  mdwf_status s = ensure(c, c->partials_b, (size_t)nblk * 2 * sizeof(double));
+  if (s == MDWF_OK) s = ensure(c, c->red_out, 2 * sizeof(double));
   if (s != MDWF_OK) return s;
-  s = ensure(c, c->red_out, (size_t)n * sizeof(double));
-  if (s != MDWF_OK) return s;
-  B.a = PtrTab(upload_table(c, a));
-  B.b = PtrTab(upload_table(c, b));
-  B.partials = static_cast<double*>(c->partials_b.p);
+  double* p = static_cast<double*>(c->partials_b.p);
+  B.a = PtrTab::single(a);
   hipEvent_t ev;
   prof_begin(c, &ev);
+  B.b = PtrTab::single(b);
+  B.partials = p;
   hipError_t e = blas_norm_diff(B, F64, c->stream);
-  if (e == hipSuccess) e = scalar_reduce(B.partials, nblk, n, static_cast<double*>(c->red_out.p), c->stream);
-  int fields = n;
-  for (const void* q : b) fields += q != nullptr;
-  prof_end(c, MDWF_PROF_BLAS, (double)g.Vh * g.L5 * 192.0 * fields, ev);
+  B.b = PtrTab();
+  B.partials = p + nblk;
+  if (e == hipSuccess) e = blas_norm_diff(B, F64, c->stream);
+  if (e == hipSuccess) e = scalar_reduce(p, nblk, 2, static_cast<double*>(c->red_out.p), c->stream);
+  prof_end(c, MDWF_PROF_BLAS, (double)g.Vh * g.L5 * 192.0 * 3, ev);
   if (e != hipSuccess) return hip_err(c, e, "FP64 norm");
-  return read_sums(c, n, out);
+  std::vector<double> n;
+  s = read_sums(c, 2, n);
+  if (s == MDWF_OK) {
+    diff = n[0];
+    norm = n[1];
+  }
+  return s;
 }
 
 // single-slot helpers (the pointers travel in the launches)
@@ -305,12 +310,10 @@ static mdwf_status finalize(mdwf_ctx* c, mdwf_job* j, int r) {
   // parity by parity: |eta - D psi|^2 and |eta|^2, with D psi in t4
   auto norms = [&]() -> mdwf_status {
     if (o.e != hipSuccess) return hip_err(c, o.e, "finalize");
-    std::vector<double> n;
-    const mdwf_status s = norms_f64(c, j->geom, {T.t1, T.t1}, {t4, nullptr}, n);
-    if (s == MDWF_OK) {
-      res += n[0];
-      nrm += n[1];
-    }
+    double d = 0, n = 0;
+    const mdwf_status s = norms_f64(c, j->geom, T.t1, t4, d, n);
+    res += d;
+    nrm += n;
     return s;
   };
   o.prog(prog_5D(CH_MPHI), xh, nullptr, T.t3);
@@ -592,7 +595,6 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
   };
   st = build();
   if (st != MDWF_OK) return st;
-  c->tables_floor = c->tables_used;  // the batch's tables stay put for the whole step
   hipError_t e = upload_states();
   if (e != hipSuccess) return hip_err(c, e, "state upload");
 
@@ -790,7 +792,6 @@ extern "C" mdwf_status mdwf_job_step(mdwf_ctx* c, mdwf_job* const* jobs, int32_t
         reset_tables(c);
         st = build();
         if (st != MDWF_OK) return st;
-        c->tables_floor = c->tables_used;
       }
       e = upload_states();
       if (e != hipSuccess) return hip_err(c, e, "state upload");
