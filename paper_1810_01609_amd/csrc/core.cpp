@@ -372,10 +372,13 @@ int streaming_stores(const Geom& g, int prec, int nslots) {
   return nslots * half > 48.0e6 ? 1 : 0;
 }
 
-static std::string tune_key(const Geom& g, int prec, const Prog& p, int nslots, int cg) {
+// The kernel is part of the key: a width or traversal measured on the general
+// kernel says nothing about the quad one, nor does one measured on an earlier
+// storage order (keys of "dslash5", of no order of their own, are not looked up).
+static std::string tune_key(const Geom& g, int prec, const Prog& p, int nslots, int cg, bool quad) {
   char buf[256];
-  snprintf(buf, sizeof(buf), "dslash5 p%d h%d d%d pr%d c%d.%d a%d r%d u%d s%d L%dx%dx%dx%d L5=%d n%d gfx950",
-           prec, (int)p.hop, (int)p.dag, (int)p.pro, p.c1, p.c2, p.aux, p.reduce, (int)cg,
+  snprintf(buf, sizeof(buf), "%s p%d h%d d%d pr%d c%d.%d a%d r%d u%d s%d L%dx%dx%dx%d L5=%d n%d gfx950",
+           quad ? "quad" : quad_layout(g.L5) ? "general-quads" : "general", prec, (int)p.hop, (int)p.dag, (int)p.pro, p.c1, p.c2, p.aux, p.reduce, (int)cg,
            p.hop ? default_stage() : 0, g.Lx, g.Ly, g.Lz, g.Lt, g.L5, nslots);
   std::string k = buf;
   if (p.split != 0) k += " x" + std::to_string(p.split);
@@ -509,10 +512,15 @@ hipError_t run_prog(mdwf_ctx* c, const mdwf_gauge* gf, const Geom& geom, int pre
   int lg = dflt;
   // the fused CG update is destructive (x, r in place): never tuned on live data
   const bool destructive = fuse != nullptr && fuse->mode != 4;
-  const std::string key = tune_key(geom, prec, pr, nslots, destructive ? fuse->mode : 0);
+  DslashArgs K = A;
+  apply_candidate(K, dflt);
+  const std::string key =
+      tune_key(geom, prec, pr, nslots, destructive ? fuse->mode : 0, dslash_quad_ok(K, prec, pr.hop, pr.dag));
   if (destructive) tunable = false;
   auto it = c->tune.find(key);
-  if (it != c->tune.end()) {
+  // a stored choice this launch does not admit (a table edited or written for
+  // other limits) is not taken
+  if (it != c->tune.end() && std::find(cand.begin(), cand.end(), it->second) != cand.end()) {
     lg = it->second;
   } else if (c->tune_mode == 1 && tunable && cand.size() > 1) {
     hipEvent_t e0, e1;
