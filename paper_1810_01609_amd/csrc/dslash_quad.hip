@@ -18,11 +18,14 @@
 //  * a neighbour is addressed by a 32-bit byte offset staged in LDS, on a
 //    uniform base that holds the wavefront's slices.
 //
-// What bounds it (32^3 x 64, L5 = 12, FP16, the plain hop, 434 us against 465
-// of dslash5_kernel; 24^3 x 64 x 16: 259 against 291, 16^3 x 32 x 12: 29
-// against 36): no single unit.  600 VALU instructions per wavefront take 200
-// us by themselves, the neighbour loads add 170, the stores 130 and the link
-// stage 25; the L1 answers 0.41 accesses of 64 bytes per clock.  With lanes on
+// What bounds it (32^3 x 64, L5 = 12, the plain hop; dslash5_kernel took 465 us
+// in FP16 and 791 in FP32): the reads of the eight neighbours on their way from
+// L2 to L1.  FP16 makes 502 accesses of 64 bytes to the L1 per wavefront and takes 442 us, FP32
+// 897 and 786 us, FP64 (dslash5_kernel) 1794 and 1664 us: 0.37 accesses per
+// clock and CU (0.40 with 12 RHS), 11-12 TB/s out of the L2.  The times follow
+// the accesses (FP16 : FP32 0.56 both) and not what misses the L2 (0.46), nor
+// the arithmetic: int16 issues 1393 VALU instructions per wavefront where FP16
+// issues 574 and takes 459 us.  With lanes on
 // 16 sites of one slice (256 contiguous bytes per 16 lanes) replaced by a quad
 // reading 64-byte pieces of four slices the same kernel took 680 us, which is
 // why the fields are stored quad by quad (dev_common.h).  Fewer or more
@@ -631,8 +634,8 @@ enum QuadProg : int {
   QP_B1 = 4,    // M_phi^T M5^-T h
   QP_B2 = 5,    // M5^T aux + coef_y M_phi^T h
   QP_B2C = 6,   // the same into r -= alpha (.) instead of out
-  QP_D = 7,     // M5 aux + coef_y h
-  QP_PRE = 8,   // M5^-1 (aux + coef_y h)
+  QP_D = 7,     // M5 aux + coef_y h (32-bit storage: with 16 bits M_phi is a prologue of the general kernel)
+  QP_PRE = 8,   // M5^-1 (aux + coef_y h) (likewise)
 };
 constexpr bool prog_dag(int p) { return p == QP_B1 || p == QP_B2 || p == QP_B2C; }
 
@@ -737,15 +740,13 @@ __global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(kQ
     const float al = (float)cf.alpha, be = (float)cf.beta, cy = (float)A.coef_y;
 #pragma unroll
     for (int k = 0; k < 24; ++k) {
-      add[k] = PROG == QP_D ? (kCareful ? cy * v[k] : fmaf(al, aux[k], cy * v[k])) : aux[k] + cy * v[k];
+      add[k] = PROG == QP_D ? cy * v[k] : aux[k] + cy * v[k];
       v[k] = PROG == QP_D ? be * aux[k] : add[k];
     }
     if constexpr (PROG == QP_D) {
       quad_shift<false>(v, add, Q, mq);
-      if constexpr (kCareful) {
 #pragma unroll
-        for (int k = 0; k < 24; ++k) v[k] = fmaf(al, aux[k], v[k]);
-      }
+      for (int k = 0; k < 24; ++k) v[k] = fmaf(al, aux[k], v[k]);
     } else quad_solve<false, false, kCareful>(v, nullptr, Q, kappa, mq, inv_c, (float)cf.inv_alpha, 0.f);
   }
 
@@ -862,8 +863,12 @@ template <int P> hipError_t launch_qp(const DslashArgs& A, bool dag, int threads
     case QP_B1: return launch_q<P, QP_B1, true>(A, threads, grid, st);
     case QP_B2: return launch_q<P, QP_B2, true>(A, threads, grid, st);
     case QP_B2C: return launch_q<P, QP_B2C, true>(A, threads, grid, st);
-    case QP_D: return launch_q<P, QP_D, false>(A, threads, grid, st);
-    case QP_PRE: return launch_q<P, QP_PRE, false>(A, threads, grid, st);
+    case QP_D:
+      if constexpr (P == F32) return launch_q<P, QP_D, false>(A, threads, grid, st);
+      break;
+    case QP_PRE:
+      if constexpr (P == F32) return launch_q<P, QP_PRE, false>(A, threads, grid, st);
+      break;
   }
   return hipErrorInvalidValue;
 }
@@ -879,7 +884,8 @@ bool dslash_quad_ok(const DslashArgs& A, int prec, bool hop, bool dag) {
   if (spinor_field_bytes(prec, A.g.L5, A.g.Vh) >= ((size_t)1 << 32)) return false;
   const size_t stage = prec == F32 || prec == I16 ? stage_bytes<F32>(16) : stage_bytes<F16>(16);
   if (totals_bytes(16, A.g.L5) > stage) return false;
-  return quad_prog(A, dag) >= 0;
+  const int prog = quad_prog(A, dag);
+  return prog >= 0 && (prec == F32 || (prog != QP_D && prog != QP_PRE));
 }
 
 size_t dslash_quad_lds_bytes(int prec, int CB, int L5) {

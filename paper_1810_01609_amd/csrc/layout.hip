@@ -126,14 +126,12 @@ __global__ __launch_bounds__(512) void k_user_to_half_phi(Geom g, PtrTab user, P
   const FieldDesc f{g.Vh, L5};
   const Vec2<R>* r = row + (s * 16 + in) * kRowU;
   R v[24];
-  if (!half.empty()) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      v[2 * k] = r[k].x;
-      v[2 * k + 1] = r[k].y;
-    }
-    SpinorAt<P>::store(half[slot], f, at, v);
+  for (int k = 0; k < 12; ++k) {
+    v[2 * k] = r[k].x;
+    v[2 * k + 1] = r[k].y;
   }
+  SpinorAt<P>::store(half[slot], f, at, v);
   const Coef5 c = coef[slot];
   const R b5 = (R)c.b5, c5 = (R)c.c5, wall = (R)(-c.c5 * c.mq);
   const R cu = s == 0 ? wall : c5, cd = s == L5 - 1 ? wall : c5;
