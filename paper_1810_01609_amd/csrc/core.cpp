@@ -182,12 +182,12 @@ static void* upload_bytes(mdwf_ctx* c, const void* data, size_t n) {
 }
 
 bool make_tables(mdwf_ctx* c, const std::vector<std::vector<const void*>>& ptrs, const std::vector<Coef5>& coefs,
-                 LaunchTables& out) {
+                 LaunchTables& out, bool in_memory) {
   const size_t n = ptrs[0].size(), tb = n * sizeof(void*);
   const size_t cb = coefs.size() > 1 ? n * sizeof(Coef5) : 0;
   out.tab.clear();
   out.coef = CoefTab::single(coefs[0]);
-  if (n == 1) {
+  if (n == 1 && !in_memory) {
     for (const auto& p : ptrs) out.tab.push_back(PtrTab::single(p[0]));
     return true;
   }

@@ -137,14 +137,14 @@ Coef5 make_coef(const mdwf_action* a);
 mdwf_status ensure(mdwf_ctx* c, DevBuf& b, size_t n);
 void release(DevBuf& b);
 // pointer tables of n entries each, and n coefficients or one for all, in one
-// upload (pointers of n = 1 and a single coefficient travel in the launches);
-// false on failure
+// upload (pointers of n = 1, unless in_memory, and a single coefficient travel in
+// the launches); false on failure
 struct LaunchTables {
   std::vector<PtrTab> tab;
   CoefTab coef;
 };
 bool make_tables(mdwf_ctx* c, const std::vector<std::vector<const void*>>& ptrs, const std::vector<Coef5>& coefs,
-                 LaunchTables& out);
+                 LaunchTables& out, bool in_memory = false);
 void reset_tables(mdwf_ctx* c);
 
 // CG update fused into a stencil launch (see DslashArgs::cg_update)

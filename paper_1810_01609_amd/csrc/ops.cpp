@@ -410,13 +410,13 @@ extern "C" mdwf_status mdwf_hop_split(mdwf_ctx* c, const mdwf_gauge* g, const md
     hal[r] = w + (fb * 2 + hb_r) * r + 2 * fb;
   }
   LaunchTables lt;
-  if (!make_tables(c, {uin, uout, io, oe, hal, nul}, {coef}, lt))
+  if (!make_tables(c, {uin, uout, io, oe, hal, nul}, {coef}, lt, true))
     return set_err(c, MDWF_EHIP, "mdwf_hop_split: table upload failed");
   const PtrTab &UIN = lt.tab[0], &UOUT = lt.tab[1], &IO = lt.tab[2], &OE = lt.tab[3], &HAL = lt.tab[4], &NUL = lt.tab[5];
-  D.in = IO;
-  D.out = OE;
-  D.send = HAL;
-  D.recv = HAL;  // every split neighbour is the lattice itself
+  D.in = IO.t;
+  D.out = OE.t;
+  D.send = HAL.t;
+  D.recv = HAL.t;  // every split neighbour is the lattice itself
   const int cls = prec == MDWF_F64 ? MDWF_PROF_DSLASH_F64 : MDWF_PROF_DSLASH_INNER;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   if (phase_ms != nullptr)
