@@ -344,7 +344,7 @@ static SpinPerm gamma_perm(int mask) {
 // two colour vectors per link), and hands its rows to coalesced stores through
 // LDS.  The hop is bound by L1 accesses (xi is read 192 bytes apart) and by
 // latency at three wavefronts per SIMD.  Twelve sources on 16^3 x 32, L5 = 12:
-// 510 + 647 us (3233 with one thread per site that wrote its 12 slices 192 bytes
+// 510 + 658 us (3233 with one thread per site that wrote its 12 slices 192 bytes
 // at a time and kept both walls in scratch memory; the writes alone take 615 us
 // at the copy kernel's rate).
 // ---------------------------------------------------------------------------
@@ -396,9 +396,9 @@ __device__ __forceinline__ void accumulate_wall(Cplx<double> acc[4][3], const Cp
 }
 
 // w = U h or U^dag h, two colour vectors.  Each complex product is rounded
-// before it joins the sum, which keeps the sources 1 to 4 % closer to the exact
-// ones than colour_mul's chain of multiply-adds does (1.73e-16 against 1.77e-16
-// at b5, c5 = 1.5, 0.5); the chain saves no time here.
+// before it joins the sum, which keeps the sources 1 to 3 % closer to the exact
+// ones than colour_mul's chain of multiply-adds does (1.75e-16 against 1.77e-16
+// at b5, c5 = 1.5, 0.5); the chain took 647 us for the hop below.
 template <bool ADJ>
 __device__ __forceinline__ void colour_mul_sum(const Cplx<double> U[3][3], const Cplx<double> h[2][3],
                                                Cplx<double> w[2][3]) {

@@ -5,7 +5,7 @@ source: the arithmetic repeated here in numpy.
 Multiply-adds are formed in long double (64-bit mantissa) and rounded to FP64:
 one in 2^10 comes out one unit off, so with some 50 of them behind a value about
 5 % of the values may differ.  A chain of multiply-adds over the whole colour
-sum, 1 to 4 % further from the exact source, agrees in less than half of them.
+sum, 1 to 3 % further from the exact source, agrees in less than half of them.
 The bar is 90 %.
 """
 import numpy as np
